@@ -31,6 +31,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int BM = 128, BN = 128, BK = 64, LDK = BK + 8;  // LDS row pitch (bf16)
 constexpr int kTileElems = BM * LDK;
@@ -292,99 +293,90 @@ __global__ __launch_bounds__(256) void ld_gemm_f32_k(GemmArgs g) {
 constexpr size_t kGemmLds = 4 * kTileElems * sizeof(bf16);
 
 // ===================================================================== big
-// 256x256 workgroup tile, four waves in a 2x2 grid each owning 128x128 (4x4
-// MFMA blocks, 256 fp32 accumulators per lane), k walked in tiles of 32.
+// 256x256 workgroup tile, eight waves in a 4x2 grid each owning 64x128 (4x8
+// blocks of v_mfma_f32_16x16x32_bf16, 128 fp32 accumulators per lane), k
+// walked in steps of 64.
+//
+// What bounds it: on random data the chip lowers its clock under sustained
+// MFMA load (the same kernel runs ~20% faster on zeros), so energy counts as
+// much as stalls.  Two waves per SIMD instead of one wave of 128x128: when a
+// wave stalls issuing a load or waits at its epilogue, the other one's MFMAs
+// go on; that outweighs the half more LDS reads.  16x16x32 rather than
+// 32x32x16 MFMAs: half the accumulator traffic per product, 2-4% faster at
+// the clock limit.  Against the four-wave kernel with 32x32x16 MFMAs that
+// this replaced, same box, random data: NT 8192^3 802 -> 727 us (1512
+// TFLOP/s), 14336 x 11008 x 2048 533 -> 472 us (1369 TFLOP/s); NN 14336 x
+// 2048 x 11008 516 -> 485 us; TN 2048 x 2048 x 14336 116 -> 108 us.
 //
 // Operand tiles go from global memory straight into LDS: buffer loads with an
 // LDS destination, so no register staging and no LDS write instructions.
 // Such a load writes the 16 bytes of lane i at LDS offset 16*i from a
 // wave-uniform base, so the LDS layout is set by which global chunk each lane
-// fetches.  Each operand has a region of the ring:
-//   mn-contiguous operand: four stages of one k tile, [32 k][256 mn] as in
-//     memory, chunks XOR-swizzled by k; a load instruction fetches two whole
-//     512-byte k rows.  A fragment is two transposing reads
-//     (ds_read_b64_tr_b16: in each group of 16 lanes, lane j receives element
-//     j%4 of the four-element rows read by lanes j/4, j/4+4, j/4+8 and
-//     j/4+12, so 16 lanes reading rows k..k+3 at mn offsets 0, 4, 8, 12 give
-//     lane j the values k..k+3 at mn j).
-//   k-contiguous operand: slots of a PAIR of k tiles, [256 rows][64 k], so
-//     a load instruction fetches 8 rows as whole 128-byte lines (a single k
-//     tile is 64 bytes of a row: half lines, twice the cache requests for
-//     the same bytes).  Two slots, or three for A when both operands are
-//     k-contiguous (96 KB; the ring is then the whole 160 KB of LDS).  The
-//     16-byte chunks of a row are XOR-swizzled by the row; a fragment is one
-//     16-byte read per lane.
+// fetches.  The ring (the whole 160 KB of LDS) holds three slots of A and two
+// of B, each one k step of 256 rows or columns (32 KB):
+//   mn-contiguous operand: [64 k][256 mn] as in memory, chunks XOR-swizzled
+//     by k; a load instruction fetches two whole 512-byte k rows.  A fragment
+//     is two transposing reads (ds_read_b64_tr_b16: in each group of 16
+//     lanes, lane j receives element j%4 of the four-element rows read by
+//     lanes j/4, j/4+4, j/4+8 and j/4+12, so 16 lanes reading rows k..k+3 at
+//     mn offsets 0, 4, 8, 12 give lane j the values k..k+3 at mn j).
+//   k-contiguous operand: [256 rows][64 k], so a load instruction fetches 8
+//     rows as whole 128-byte lines.  The 16-byte chunks of a row are
+//     XOR-swizzled by the row; a fragment is one 16-byte read per lane.
 // Rows past the operand's end, and k chunks past the split's end, are
 // fetched from an offset outside the buffer descriptor's range and land in
 // LDS as zeros.  The loads are issued as inline assembly (ld_internal.h),
 // so the compiler does not track them; the kernel waits for them itself
 // (s_waitcnt vmcnt) before the barriers.
 //
-// Per k tile (two k-substeps of 16): one barrier at the top, where each wave
-// has waited until the next tile has landed; then the tile's 32 MFMAs run on
-// fragments read during the previous tile, next to the reads of all of the
-// next tile's fragments and the loads for later tiles: an mn-contiguous
-// stage is reloaded (tile kt+4) during the tile kt it holds, whose fragments
-// were read before the barrier; a k-contiguous slot is reloaded once both
-// of its tiles have been read: with two slots, pair kt+3, kt+4 during odd
-// tiles kt; A's third slot lets its pair kt+5, kt+6 load half during odd
-// tile kt and half during kt+1.  Every load has at least one tile-time,
-// most two or more, to land.  No MFMA waits on a recent LDS read.
+// A k step is four quarters h of 16 MFMAs per wave: k-substep (32) h / 2 and
+// four of the eight B blocks.  Each quarter reads the fragments of the next
+// one, so no MFMA waits on a recent LDS read.  The one barrier of step t
+// stands before its last quarter, where every wave has read all of step t's
+// fragments and step t+1 has landed; after it B's slot of step t takes step
+// t+2 (four loads spread over the last quarter) and A's slot of step t-1 takes
+// step t+2 (spread over the next quarter).  Spread evenly and issued right
+// after the barrier the loads have most of a step to land: two quarters later
+// they cost 5% (NT 8192^3), in a burst 2-4%.
 //
 // The MFMA is issued as B x A so each lane ends with 4 consecutive output
 // columns of one row.  Tiles are ordered XCD-aware: consecutive workgroup ids
 // go to different XCDs, so ids are remapped to give each XCD a contiguous
-// range of tiles, walked in groups of 8 tile-rows for L2 reuse.  Split-K
+// range of tiles, walked in groups of 4 or 8 tile-rows for L2 reuse.  Split-K
 // (grid.y) writes fp32 partials that a second kernel sums in split order.
 
-constexpr int GB = 256, GK = 32;
-constexpr int kBigTile = GB * GK;       // elements of one operand's k tile
-constexpr int kLoadsMC = 4;             // load instructions per wave per mn-contiguous tile
-constexpr int kLoadsKC = 8;             // load instructions per wave per k-contiguous pair
+constexpr int GB = 256, GK = 64;
+constexpr int kBigThreads = 512;        // eight waves
+constexpr int kSlot = GB * GK;          // elements of one operand's k step
+constexpr int kLoads = 4;               // load instructions per wave per slot
+constexpr int kSlotsA = 3, kSlotsB = 2;
+constexpr int kWaitVm0 = 0x0F70;        // s_waitcnt vmcnt(0), the other counters untouched
+constexpr int kRingElems = (kSlotsA + kSlotsB) * kSlot;
 constexpr int kStagePitch = 132;        // floats per staged epilogue row (128 + 4 pad)
 constexpr int kStagePitch16 = 132;      // bf16 per staged row of a bf16 epilogue (264 bytes)
 constexpr uint32_t kOob = kDmaOob;
 constexpr int64_t kBigMaxSpan = kDmaMaxSpan;
-// Ring regions (elements): a k-contiguous A takes three pair slots when B
-// is k-contiguous too, every other operand four tile stages or two pair
-// slots (64 KB).
-template <bool AK, bool BKC>
-constexpr int slots_a() { return AK && BKC ? 3 : 2; }
-template <bool AK, bool BKC>
-constexpr int region_a() { return AK ? slots_a<AK, BKC>() * 2 * kBigTile : 4 * kBigTile; }
-template <bool AK, bool BKC>
-constexpr int ring_elems() { return region_a<AK, BKC>() + 4 * kBigTile; }
-static_assert(ring_elems<true, true>() * 2 <= 160 * 1024, "the ring fits the LDS");
-static_assert(ring_elems<false, false>() * 2 >= 4 * 32 * kStagePitch * 4, "epilogue staging fits the ring");
+static_assert(kRingElems * 2 <= 160 * 1024, "the ring fits the LDS");
+static_assert(kRingElems * 2 >= 8 * 32 * kStagePitch * 4, "epilogue staging fits the ring");
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef dma_rsrc v4i;
 #define LD_LDS(T, p) ((__attribute__((address_space(3))) T*)(p))
 
-// Element offset, in an operand's region, of the stage (mn-contiguous) or
-// pair slot (k-contiguous, NS slots) holding k tile kt.
-template <bool KC, int NS>
-__device__ __forceinline__ int tile_base(int kt) {
-  if constexpr (KC)
-    return ((kt >> 1) % NS) * (2 * kBigTile);
-  else
-    return (kt & 3) * kBigTile;
-}
-
-// k-contiguous pair slot: element (row, k) of a [256][64] slot.  The chunk
+// k-contiguous slot: element (row, k) of [256][64].  The chunk
 // swizzle uses row bits 1-3: of 16 lanes reading one chunk of 16
 // consecutive rows, the two rows of each pair sit 128 bytes apart and the 8
 // pairs on 8 different chunks, so all 16 hit different 16-byte bank groups;
 // moving by a multiple of 16 rows is a plain offset.
 __device__ __forceinline__ int kc_swz(int row) { return (row >> 1) & 7; }
 __device__ __forceinline__ int swz_off(int row, int k) {
-  return row * (2 * GK) + ((((k >> 3) ^ kc_swz(row)) << 3) | (k & 7));
+  return row * GK + ((((k >> 3) ^ kc_swz(row)) << 3) | (k & 7));
 }
 
-// mn-contiguous tile: element (k, m) of a [32][256] tile.  The swizzle puts
-// the 4 k rows a 16-lane transposing read touches (32 bytes each) on 4
-// different 64-byte bank groups, and rows k and k+8 on different halves; it
-// depends on k bits 0, 1 and 3 only, so k steps of 4 and 16 are plain offsets.
+// mn-contiguous slot: element (k, m) of [64][256].  The swizzle puts the 4 k
+// rows a 16-lane transposing read touches (32 bytes each) on 4 different
+// 64-byte bank groups, and rows k and k+8 on different halves; it depends on
+// k bits 0, 1 and 3 only, so k steps of 4 and 16 are plain offsets.
 __device__ __forceinline__ int mc_swz(int k) { return ((k & 3) << 2) | (((k >> 3) & 1) << 1); }
 __device__ __forceinline__ int mc_off(int k, int m) {
   return k * GB + ((((m >> 3) ^ mc_swz(k)) << 3) | (m & 7));
@@ -393,96 +385,85 @@ __device__ __forceinline__ int mc_off(int k, int m) {
 // Per-lane constants of one operand's tile loads and fragment reads.
 template <bool KC>
 struct OpLanes {
-  uint32_t ld_off[2];  // byte offset of the lane's first 16-byte chunk (mn: per k-row parity)
-  int kchunk;          // k-contiguous: k offset of the lane's chunk in the pair
-  int frag[4];         // element offsets of fragment reads: per (k half, k-substep) (KC) or block (MC)
+  uint32_t ld_off;  // byte offset of the lane's first 16-byte chunk
+  int kchunk;       // k-contiguous: k offset of the lane's chunk in the slot
+  int frag[8];      // element offsets of fragment reads: per k-substep (KC) or block (MC)
 };
 
-// `r`: the first of the wave's 128 fragment rows (0 or 128).
+// `r`: the first of the wave's fragment rows.
 template <bool KC>
 __device__ __forceinline__ OpLanes<KC> op_lanes(int64_t ld, int lane, int wave, int r) {
   OpLanes<KC> o;
   if constexpr (KC) {
-    // load instruction p fills slot rows 8 (4p + wave) .. +7, lane -> row
+    // load instruction p fills slot rows 64p + 8 wave .. +7, lane -> row
     // + lane/8, physical chunk lane%8; the swizzle is the same for every p
     const int row = wave * 8 + (lane >> 3);
     o.kchunk = ((lane & 7) ^ kc_swz(row)) << 3;
-    o.ld_off[0] = o.ld_off[1] = static_cast<uint32_t>((static_cast<int64_t>(row) * ld + o.kchunk) * 2);
+    o.ld_off = static_cast<uint32_t>((static_cast<int64_t>(row) * ld + o.kchunk) * 2);
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-        o.frag[2 * h + ks] = swz_off(r + (lane & 31), h * GK + ks * 16 + (lane >> 5) * 8);
+    for (int ks = 0; ks < 2; ++ks) o.frag[ks] = swz_off(r + (lane & 15), ks * 32 + (lane >> 4) * 8);
   } else {
-    // load instruction p fills k rows 8p + 2*wave + lane/32, physical chunk
-    // lane%32; the swizzle depends on p only through its parity (k bit 3)
+    // load instruction p fills k rows 16p + 2*wave + lane/32, physical chunk
+    // lane%32; the swizzle is the same for every p
     const int kr = 2 * wave + (lane >> 5);
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const int m = ((lane & 31) ^ mc_swz(8 * par + kr)) << 3;
-      o.ld_off[par] = static_cast<uint32_t>((static_cast<int64_t>(kr) * ld + m) * 2);
-    }
+    const int m = ((lane & 31) ^ mc_swz(kr)) << 3;
+    o.ld_off = static_cast<uint32_t>((static_cast<int64_t>(kr) * ld + m) * 2);
     o.kchunk = 0;
     // transposing reads: lane reads k row kl, 4 elements from mn ml
-    const int kl = (lane >> 5) * 8 + ((lane >> 2) & 3);
-    const int ml = ((lane >> 4) & 1) * 16 + 4 * (lane & 3);
+    const int kl = (lane >> 4) * 8 + ((lane >> 2) & 3);
+    const int ml = 4 * (lane & 3);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o.frag[i] = mc_off(kl, r + ml + 32 * i);
+    for (int i = 0; i < 8; ++i) o.frag[i] = mc_off(kl, r + ml + 16 * i);
   }
   return o;
 }
 
-// Load instruction p of operand X's rows r0.. into `lds` (its stage or
-// slot), 16 bytes per lane.  mn-contiguous: instruction p (0-3) fills 2 k
-// rows per wave of the tile at k0.  k-contiguous: instruction p (0-7) fills
-// 8 rows per wave of the pair at k0 (64 k).  Columns past the end of a valid
-// row read real memory; they only reach outputs that are never stored,
-// except a k tail of a k-contiguous operand, which is fetched out of range
-// (zeros), as is everything of a tile that starts at or past K.
+// Load instruction p (0-3) of operand X's rows r0.. (k-contiguous: slot rows
+// 64p..64p+63; mn-contiguous: k rows 16p..16p+15) of the k step at k0 into the
+// slot at `lds`, 16 bytes per lane.  Columns past the end of a valid row read
+// real memory; they only reach outputs that are never stored, except a k tail
+// of a k-contiguous operand, which is fetched out of range (zeros), as is
+// everything of a step that starts at or past K.
 template <bool KC>
 __device__ __forceinline__ void tile_part(bf16* lds, const OpLanes<KC>& o, const bf16* X, int64_t ld,
                                           int r0, int R, int k0, int K, int wave, int p) {
   if constexpr (KC) {
     const v4i rs = dma_make_rsrc(X + static_cast<int64_t>(r0) * ld, (static_cast<int64_t>(R) - r0) * ld * 2);
-    const uint32_t u = static_cast<uint32_t>((static_cast<int64_t>(p) * 32 * ld + k0) * 2);
-    const uint32_t off = k0 + o.kchunk < K ? o.ld_off[0] + u : kOob;
-    dma16(rs, lds + (p * 4 + wave) * 512, off);
+    const uint32_t u = static_cast<uint32_t>((static_cast<int64_t>(p) * 64 * ld + k0) * 2);
+    const uint32_t off = k0 + o.kchunk < K ? o.ld_off + u : kOob;
+    dma16(rs, lds + (p * 8 + wave) * 512, off);
   } else {
     const v4i rs = dma_make_rsrc(X + static_cast<int64_t>(k0) * ld, (static_cast<int64_t>(K) - k0) * ld * 2);
-    const uint32_t u = static_cast<uint32_t>((static_cast<int64_t>(p) * 8 * ld + r0) * 2);
-    dma16(rs, lds + (p * 4 + wave) * 512, o.ld_off[p & 1] + u);
+    const uint32_t u = static_cast<uint32_t>((static_cast<int64_t>(p) * 16 * ld + r0) * 2);
+    dma16(rs, lds + (p * 8 + wave) * 512, o.ld_off + u);
   }
   (void)R;
 }
 
-// B slot of the fused SwiGLU forward: the slot's 64-row block b = p/2 holds
-// gate rows (b even) or up rows (b odd) tn*128 + (b/2)*64 .. +63 of
-// W_gate_up [2f, K], so the tile holds [gate 0-63 | up 0-63 | gate 64-127 |
-// up 64-127] of its 128 d_ff columns and each wave's 128 rows pair every
-// gate row with its up row 64 further on.  Instruction p (0-7) fills rows
-// 32 (p%2) + 8 wave .. +7 of block b.
+// B slot of the fused SwiGLU forward: the slot's 64-row block p holds gate
+// rows (p even) or up rows (p odd) tn*128 + (p/2)*64 .. +63 of W_gate_up
+// [2f, K], so the slot holds [gate 0-63 | up 0-63 | gate 64-127 | up 64-127]
+// of its 128 d_ff columns and each wave's 128 rows pair every gate row with
+// its up row 64 further on.  Load instruction p fills rows 8 wave .. +7 of
+// block p.
 __device__ __forceinline__ void tile_part_glu(bf16* lds, const OpLanes<true>& o, const bf16* W, int64_t ld,
                                               int tn, int f, int k0, int K, int wave, int p) {
-  const int b = p >> 1;
-  const int64_t rbase = ((b & 1) ? f : 0) + static_cast<int64_t>(tn) * 128 + (b >> 1) * 64;
+  const int64_t rbase = ((p & 1) ? f : 0) + static_cast<int64_t>(tn) * 128 + (p >> 1) * 64;
   const v4i rs = dma_make_rsrc(W + rbase * ld, 64 * ld * 2);
-  const uint32_t u = static_cast<uint32_t>((static_cast<int64_t>(p & 1) * 32 * ld + k0) * 2);
-  const uint32_t off = k0 + o.kchunk < K ? o.ld_off[0] + u : kOob;
-  dma16(rs, lds + (p * 4 + wave) * 512, off);
+  const uint32_t off = k0 + o.kchunk < K ? o.ld_off + static_cast<uint32_t>(k0 * 2) : kOob;
+  dma16(rs, lds + (p * 8 + wave) * 512, off);
 }
 
-// Fragment of block i of the wave's 128 rows for k-substep ks of the tile
-// whose stage or slot starts at t (h: the tile's half of a k-contiguous
-// pair): the lane's MFMA row is r + 32 i + lane % 32 (r as given to
-// op_lanes), its 8 k values start at ks*16 + (lane/32)*8.  Only the per-lane
+// Fragment of 16-row block i of the wave's rows for k-substep ks (32) of the
+// slot at t: the lane's MFMA row is r + 16 i + lane % 16 (r as given to
+// op_lanes), its 8 k values start at ks*32 + (lane/16)*8.  Only the per-lane
 // offset is a register; the rest is a constant offset of the LDS instruction.
 template <bool KC>
-__device__ __forceinline__ bf16x8 frag(const bf16* t, const OpLanes<KC>& o, int i, int h, int ks) {
+__device__ __forceinline__ bf16x8 frag(const bf16* t, const OpLanes<KC>& o, int i, int ks) {
   if constexpr (KC) {
-    return *reinterpret_cast<const bf16x8*>(t + 32 * i * (2 * GK) + o.frag[2 * h + ks]);
+    return *reinterpret_cast<const bf16x8*>(t + 16 * i * GK + o.frag[ks]);
   } else {
-    (void)h;
-    const bf16* p = t + o.frag[i] + ks * 16 * GB;
+    const bf16* p = t + o.frag[i] + ks * 32 * GB;
     const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LD_LDS(v4s, p));
     const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LD_LDS(v4s, p + 4 * GB));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
@@ -495,7 +476,10 @@ __device__ __forceinline__ bf16x8 frag(const bf16* t, const OpLanes<KC>& o, int 
 // turn (id % 8), so XCD x is given its own contiguous, balanced range of
 // n_valid / 8 (+1) tiles: the tiles of rows past the kept count are not
 // piled onto the last XCDs, and consecutive tiles share an XCD's L2.  Within
-// a range, tiles go in groups of 8 tile rows, column by column.  The grid has
+// a range, tiles go in groups of tile rows, column by column: groups of 8, or
+// of 4 when the matrix has at most 8 tile columns, so that the 32 tiles an XCD
+// works on at a time cover every column of B (NN 14336 x 2048 x 11008 with
+// groups of 8 499 us, of 4 483 us; with 32 columns 8 is 1-2% better).  The grid has
 // at least as many ids per XCD as the largest range (it is sized for every
 // row), so every tile is taken.
 __device__ __forceinline__ bool tile_coords(int pid, int tiles_m, int tiles_n, int& tm, int& tn) {
@@ -504,7 +488,7 @@ __device__ __forceinline__ bool tile_coords(int pid, int tiles_m, int tiles_n, i
   const int base = n_valid >> 3, rem = n_valid & 7;
   if (li >= base + (x < rem ? 1 : 0)) return false;
   const int t = x * base + min(x, rem) + li;
-  constexpr int G = 8;
+  const int G = tiles_n <= 8 ? 4 : 8;
   const int group = G * tiles_n;
   const int first_m = (t / group) * G;
   const int gsz = min(tiles_m - first_m, G);
@@ -518,92 +502,95 @@ __device__ __forceinline__ bool tile_coords(int pid, int tiles_m, int tiles_n, i
 // (it = 0..15), its 4 columns n..n+3; the staged values (alpha applied) sit
 // at stage[(2 it + half) * kStagePitch + c].
 //
-// Full block row (every row < M, every column < N): all staged values, row
-// map entries and residual values are requested before the first store, so
-// their latencies overlap, and no branch splits the rows.
+// Full block row (every row < M, every column < N): the staged values, row
+// map entries and residual values of half the rows are requested before their
+// first store, so their latencies overlap, and no branch splits the rows.
 __device__ __forceinline__ void epilogue_rows_full(const GemmArgs& g, float* part, const float* stage,
                                                    int r0, int half, int c, int n, int q_last) {
-  float4 v[16];
-#pragma unroll
-  for (int it = 0; it < 16; ++it)
-    v[it] = *reinterpret_cast<const float4*>(stage + (2 * it + half) * kStagePitch + c);
-  if (part) {
-#pragma unroll
-    for (int it = 0; it < 16; ++it)
-      *reinterpret_cast<float4*>(part + static_cast<int64_t>(r0 + 2 * it) * g.N + n) = v[it];
-    return;
-  }
-  int32_t orow[16];
-  if (g.out_map.idx) {
-    // output row = idx[r / S] * S + r % S
-    const int S = g.out_map.S;
-    const int q0 = r0 / S, rem0 = r0 - q0 * S;
+  constexpr int NR = 8;  // rows in hand (16 would spill next to the accumulators)
+  // output row = idx[r / S] * S + r % S; for S >= 32 the 32 rows span at most
+  // two sequences
+  const int S = g.out_map.S;
+  int q0 = 0, rem0 = 0, s0 = 0, s1 = 0;
+  if (!part && g.out_map.idx) {
+    q0 = r0 / S;
+    rem0 = r0 - q0 * S;
     if (S >= 32) {
-      // the 32 rows span at most two sequences
-      const int s0 = g.out_map.idx[q0], s1 = g.out_map.idx[min(q0 + 1, q_last)];
+      s0 = g.out_map.idx[q0];
+      s1 = g.out_map.idx[min(q0 + 1, q_last)];
+    }
+  }
 #pragma unroll
-      for (int it = 0; it < 16; ++it) {
-        const int rr = rem0 + 2 * it;
-        orow[it] = rr >= S ? s1 * S + (rr - S) : s0 * S + rr;
-      }
-    } else {
+  for (int h = 0; h < 2; ++h) {
+    float4 v[NR];
 #pragma unroll
-      for (int it = 0; it < 16; ++it) {
-        const int r = r0 + 2 * it, q = r / S;
-        orow[it] = g.out_map.idx[q] * S + (r - q * S);
+    for (int it = 0; it < NR; ++it)
+      v[it] = *reinterpret_cast<const float4*>(stage + (2 * (NR * h + it) + half) * kStagePitch + c);
+    if (part) {
+#pragma unroll
+      for (int it = 0; it < NR; ++it)
+        *reinterpret_cast<float4*>(part + static_cast<int64_t>(r0 + 2 * (NR * h + it)) * g.N + n) = v[it];
+      continue;
+    }
+    int32_t orow[NR];
+#pragma unroll
+    for (int it = 0; it < NR; ++it) {
+      const int r = r0 + 2 * (NR * h + it);
+      orow[it] = r;
+      if (g.out_map.idx) {
+        if (S >= 32) {
+          const int rr = rem0 + 2 * (NR * h + it);
+          orow[it] = rr >= S ? s1 * S + (rr - S) : s0 * S + rr;
+        } else {
+          const int q = r / S;
+          orow[it] = g.out_map.idx[q] * S + (r - q * S);
+        }
       }
     }
-  } else {
+    if (g.R && g.r_f32) {  // float32 residual (the residual streams)
+      const float* R = static_cast<const float*>(g.R);
+      float4 rv[NR];
 #pragma unroll
-    for (int it = 0; it < 16; ++it) orow[it] = r0 + 2 * it;
-  }
-  if (g.R && g.r_f32) {  // float32 residual (the residual streams)
-    const float* R = static_cast<const float*>(g.R);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {  // two halves of 8 rows: fewer registers live
-      float4 rv[8];
-#pragma unroll
-      for (int it = 0; it < 8; ++it) {
-        const int64_t rrow = g.r_mapped ? orow[8 * h + it] : r0 + 2 * (8 * h + it);
+      for (int it = 0; it < NR; ++it) {
+        const int64_t rrow = g.r_mapped ? orow[it] : r0 + 2 * (NR * h + it);
         rv[it] = *reinterpret_cast<const float4*>(R + rrow * g.ldr + n);
       }
 #pragma unroll
-      for (int it = 0; it < 8; ++it) {
-        float4& t = v[8 * h + it];
-        t.x += rv[it].x;
-        t.y += rv[it].y;
-        t.z += rv[it].z;
-        t.w += rv[it].w;
+      for (int it = 0; it < NR; ++it) {
+        v[it].x += rv[it].x;
+        v[it].y += rv[it].y;
+        v[it].z += rv[it].z;
+        v[it].w += rv[it].w;
+      }
+    } else if (g.R) {  // bf16 residual
+      uint2 rv[NR];
+      const bf16* R = static_cast<const bf16*>(g.R);
+#pragma unroll
+      for (int it = 0; it < NR; ++it) {
+        const int64_t rrow = g.r_mapped ? orow[it] : r0 + 2 * (NR * h + it);
+        rv[it] = *reinterpret_cast<const uint2*>(R + rrow * g.ldr + n);
+      }
+#pragma unroll
+      for (int it = 0; it < NR; ++it) {
+        const bf16* rb = reinterpret_cast<const bf16*>(&rv[it]);
+        v[it].x += static_cast<float>(rb[0]);
+        v[it].y += static_cast<float>(rb[1]);
+        v[it].z += static_cast<float>(rb[2]);
+        v[it].w += static_cast<float>(rb[3]);
       }
     }
-  } else if (g.R) {  // bf16 residual
-    uint2 rv[16];
-    const bf16* R = static_cast<const bf16*>(g.R);
+    if (g.c_f32) {
 #pragma unroll
-    for (int it = 0; it < 16; ++it) {
-      const int64_t rrow = g.r_mapped ? orow[it] : r0 + 2 * it;
-      rv[it] = *reinterpret_cast<const uint2*>(R + rrow * g.ldr + n);
-    }
+      for (int it = 0; it < NR; ++it)
+        *reinterpret_cast<float4*>(static_cast<float*>(g.C) + static_cast<int64_t>(orow[it]) * g.ldc + n) = v[it];
+    } else {
 #pragma unroll
-    for (int it = 0; it < 16; ++it) {
-      const bf16* rb = reinterpret_cast<const bf16*>(&rv[it]);
-      v[it].x += static_cast<float>(rb[0]);
-      v[it].y += static_cast<float>(rb[1]);
-      v[it].z += static_cast<float>(rb[2]);
-      v[it].w += static_cast<float>(rb[3]);
-    }
-  }
-  if (g.c_f32) {
-#pragma unroll
-    for (int it = 0; it < 16; ++it)
-      *reinterpret_cast<float4*>(static_cast<float*>(g.C) + static_cast<int64_t>(orow[it]) * g.ldc + n) = v[it];
-  } else {
-#pragma unroll
-    for (int it = 0; it < 16; ++it) {
-      __attribute__((aligned(8))) bf16 o[4] = {static_cast<bf16>(v[it].x), static_cast<bf16>(v[it].y),
-                                               static_cast<bf16>(v[it].z), static_cast<bf16>(v[it].w)};
-      *reinterpret_cast<uint2*>(static_cast<bf16*>(g.C) + static_cast<int64_t>(orow[it]) * g.ldc + n) =
-          *reinterpret_cast<const uint2*>(o);
+      for (int it = 0; it < NR; ++it) {
+        __attribute__((aligned(8))) bf16 o[4] = {static_cast<bf16>(v[it].x), static_cast<bf16>(v[it].y),
+                                                 static_cast<bf16>(v[it].z), static_cast<bf16>(v[it].w)};
+        *reinterpret_cast<uint2*>(static_cast<bf16*>(g.C) + static_cast<int64_t>(orow[it]) * g.ldc + n) =
+            *reinterpret_cast<const uint2*>(o);
+      }
     }
   }
 }
@@ -678,17 +665,21 @@ __device__ __forceinline__ void glu_bwd_rows(const GemmArgs& g, const float* sta
   const bf16* U = static_cast<const bf16*>(g.aux);
   const int64_t ldu = 2ll * g.glu_f;
   if (full) {
-    uint2 ur[16], vr[16];
 #pragma unroll
-    for (int it = 0; it < 16; ++it) {
-      const int64_t m = r0 + 2 * it;
-      ur[it] = *reinterpret_cast<const uint2*>(U + m * ldu + n);
-      vr[it] = *reinterpret_cast<const uint2*>(U + m * ldu + g.glu_f + n);
-    }
+    for (int h = 0; h < 2; ++h) {
+      uint2 ur[8], vr[8];
 #pragma unroll
-    for (int it = 0; it < 16; ++it) {
-      const float4 gs = *reinterpret_cast<const float4*>(stage + (2 * it + half) * kStagePitch + c);
-      glu_bwd_one(g, gs, ur[it], vr[it], r0 + 2 * it, n);
+      for (int it = 0; it < 8; ++it) {
+        const int64_t m = r0 + 2 * (8 * h + it);
+        ur[it] = *reinterpret_cast<const uint2*>(U + m * ldu + n);
+        vr[it] = *reinterpret_cast<const uint2*>(U + m * ldu + g.glu_f + n);
+      }
+#pragma unroll
+      for (int it = 0; it < 8; ++it) {
+        const int r = 2 * (8 * h + it);
+        const float4 gs = *reinterpret_cast<const float4*>(stage + (r + half) * kStagePitch + c);
+        glu_bwd_one(g, gs, ur[it], vr[it], r0 + r, n);
+      }
     }
   } else {
 #pragma unroll 1
@@ -720,11 +711,9 @@ __device__ __forceinline__ void relu2_fwd_one(const GemmArgs& g, float4 v, int64
 __device__ __forceinline__ void relu2_fwd_rows(const GemmArgs& g, const float* stage, int r0, int half, int c,
                                                int n, int M, bool full) {
   if (full) {
-    float4 v[16];
 #pragma unroll
-    for (int it = 0; it < 16; ++it) v[it] = *reinterpret_cast<const float4*>(stage + (2 * it + half) * kStagePitch + c);
-#pragma unroll
-    for (int it = 0; it < 16; ++it) relu2_fwd_one(g, v[it], r0 + 2 * it, n);
+    for (int it = 0; it < 16; ++it)
+      relu2_fwd_one(g, *reinterpret_cast<const float4*>(stage + (2 * it + half) * kStagePitch + c), r0 + 2 * it, n);
   } else {
 #pragma unroll 1
     for (int it = 0; it < 16; ++it) {
@@ -770,19 +759,22 @@ __device__ __forceinline__ void relu2_bwd_rows(const GemmArgs& g, const float* s
 // (n_tiles covers every row the grid was sized for), `sp` of `splits` the
 // k range; `ring` is the workgroup's LDS.
 // Plain bf16 output of a 32-row block row that crosses M: straight from the
-// accumulators, each row checked (lane: row lm, columns j*32 + 8q + 4 half).
-__device__ __forceinline__ void epilogue_plain_edge_bf16(const GemmArgs& g, const floatx16 (&acc)[4], float alpha,
-                                                         int mb, int nb, int lm, int half, int M) {
-  if (mb + lm >= M) return;
-  bf16* C = static_cast<bf16*>(g.C) + static_cast<int64_t>(mb + lm) * g.ldc + nb;
+// accumulators, each row checked (lane: row 16 ii + l16, columns 16 j + q16).
+__device__ __forceinline__ void epilogue_plain_edge_bf16(const GemmArgs& g, const floatx4 (&a0)[8],
+                                                         const floatx4 (&a1)[8], float alpha, int mb, int nb, int l16,
+                                                         int q16, int M) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+  for (int ii = 0; ii < 2; ++ii) {
+    const int m = mb + 16 * ii + l16;
+    if (m < M) {
+      bf16* C = static_cast<bf16*>(g.C) + static_cast<int64_t>(m) * g.ldc + nb + q16;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const floatx16& a = acc[j];
-      *reinterpret_cast<uint2*>(C + j * 32 + 8 * q + 4 * half) =
-          pack4_bf16(alpha * a[4 * q], alpha * a[4 * q + 1], alpha * a[4 * q + 2], alpha * a[4 * q + 3]);
+      for (int j = 0; j < 8; ++j) {
+        const floatx4& a = ii ? a1[j] : a0[j];
+        *reinterpret_cast<uint2*>(C + j * 16) = pack4_bf16(alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]);
+      }
     }
+  }
 }
 
 template <bool AK, bool BKC, int EPI = kEpiPlain>
@@ -808,113 +800,84 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
   const int nk = kt1 - kt0;
   const int kend = min(K, kt1 * GK);  // loads at or past it read zeros
 
-  floatx16 acc[4][4];
+  floatx4 acc[4][8];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 8; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
 
-  const OpLanes<AK> oa = op_lanes<AK>(g.lda, lane, wave, wm * 128);
+  const OpLanes<AK> oa = op_lanes<AK>(g.lda, lane, wave, wm * 64);
   const OpLanes<BKC> ob = op_lanes<BKC>(g.ldb, lane, wave, wn * 128);
-  constexpr int NSA = slots_a<AK, BKC>(), NSB = 2;  // pair slots of a k-contiguous A, B
-  bf16* const ra = ring;                            // A's region
-  bf16* const rb = ring + region_a<AK, BKC>();      // B's region
-  // Load instruction q of A or B into the stage of tile kt (mn-contiguous,
-  // q 0-3) or the slot of the pair starting at tile kt (k-contiguous, q 0-7).
-  auto load_a = [&](int kt, int q) {
-    tile_part<AK>(ra + tile_base<AK, NSA>(kt), oa, A, g.lda, m0, M, (kt0 + kt) * GK, kend, wave, q);
+  bf16* const ra = ring;                     // A's slots
+  bf16* const rb = ring + kSlotsA * kSlot;   // B's slots
+  // Load instruction q of A or B for k step kt into slot sl.
+  auto load_a = [&](int sl, int kt, int q) {
+    tile_part<AK>(ra + sl * kSlot, oa, A, g.lda, m0, M, (kt0 + kt) * GK, kend, wave, q);
   };
-  auto load_b = [&](int kt, int q) {
+  auto load_b = [&](int sl, int kt, int q) {
     if constexpr (EPI == kEpiGluFwd)
-      tile_part_glu(rb + tile_base<true, NSB>(kt), ob, B, g.ldb, tn, g.glu_f, (kt0 + kt) * GK, kend, wave, q);
+      tile_part_glu(rb + sl * kSlot, ob, B, g.ldb, tn, g.glu_f, (kt0 + kt) * GK, kend, wave, q);
     else
-      tile_part<BKC>(rb + tile_base<BKC, NSB>(kt), ob, B, g.ldb, n0, g.N, (kt0 + kt) * GK, kend, wave, q);
+      tile_part<BKC>(rb + sl * kSlot, ob, B, g.ldb, n0, g.N, (kt0 + kt) * GK, kend, wave, q);
   };
-  // The ring starts full: per k tile t = 0..3, A's then B's loads of that
-  // tile (a k-contiguous operand loads its pair at even t), then, with three
-  // A slots, the first half of A's pair at tiles 4, 5; zeros past the
-  // split's end.
+  // The compiler's own loads (the kept count among them) are done with here:
+  // left pending on some path, it would wait for one -- for every load of
+  // the ring -- inside the k loop (11% of the backward pair launches).
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);
+  // Steps 0 and 1; A's step 2 goes out in step 0's first quarter.
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int q = 0; q < kLoads; ++q) load_b(0, 0, q);
 #pragma unroll
-    for (int q = 0; q < (AK ? kLoadsKC : kLoadsMC); ++q)
-      if (!AK || t % 2 == 0) load_a(t, q);
+  for (int q = 0; q < kLoads; ++q) load_a(0, 0, q);
 #pragma unroll
-    for (int q = 0; q < (BKC ? kLoadsKC : kLoadsMC); ++q)
-      if (!BKC || t % 2 == 0) load_b(t, q);
-  }
-  if constexpr (NSA == 3) {
+  for (int q = 0; q < kLoads; ++q) load_a(1, 1, q);
 #pragma unroll
-    for (int q = 0; q < kLoadsKC / 2; ++q) load_a(4, q);
-  }
-  // Loads that may still be in flight at the barriers (counted over the issue
-  // order of the first fill and of the tiles, below): at the first barrier,
-  // and at the top of even and odd tiles.
-  constexpr int kWaitFirst = NSA == 3 ? 20 : AK && BKC ? 16 : AK || BKC ? 20 : 24;
-  constexpr int kWaitEven = 16;
-  constexpr int kWaitOdd = NSA == 3 ? 4 : AK && BKC ? 0 : BKC ? 4 : AK ? 8 : 16;
-  dma_barrier<kWaitFirst>();  // tile 0 has landed
-  // Fragments are read one whole tile ahead: fa/fb[set][ks][block], the
-  // set alternating with the tile's parity.
-  bf16x8 fa[2][2][4], fb[2][2][4];
+  for (int q = 0; q < kLoads; ++q) load_b(1, 1, q);
+  dma_barrier<2 * kLoads>();  // step 0 has landed
+  bf16x8 fa[2][4], fb[2][4];  // A blocks per k-substep, B blocks per half
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks)
+  for (int i = 0; i < 4; ++i) fa[0][i] = frag<AK>(ra, oa, i, 0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      fa[0][ks][i] = frag<AK>(ra + tile_base<AK, NSA>(0), oa, i, 0, ks);
-      fb[0][ks][i] = frag<BKC>(rb + tile_base<BKC, NSB>(0), ob, i, 0, ks);
+  for (int j = 0; j < 4; ++j) fb[0][j] = frag<BKC>(rb, ob, j, 0);
+  int sa = 0;  // A's slot of step kt
+  for (int kt = 0; kt < nk; ++kt) {
+    const int sb = kt & 1;
+    const int sa1 = sa == 2 ? 0 : sa + 1, sa2 = sa1 == 2 ? 0 : sa1 + 1;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      const int ks = h >> 1, P = h & 1, nks = ((h + 1) >> 1) & 1;
+      const bf16* na = ra + (h == 3 ? sa1 : sa) * kSlot;
+      const bf16* nb = rb + (h == 3 ? sb ^ 1 : sb) * kSlot;
+      // all of step kt is read; step kt+1 has landed (in flight: A's kt+2)
+      if (h == 3) dma_barrier<kLoads>();
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int i = q >> 2, j = q & 3;
+        acc[i][4 * P + j] =
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[P][j], fa[ks][i], acc[i][4 * P + j], 0, 0, 0);
+        if (P == 0) {  // the other four B blocks
+          if (q < 8 && (q & 1) == 0) fb[1][q >> 1] = frag<BKC>(nb, ob, 4 + (q >> 1), ks);
+        } else if (q < 8) {  // the next k-substep's A blocks and first B blocks
+          if (q & 1)
+            fa[ks ^ 1][q >> 1] = frag<AK>(na, oa, q >> 1, nks);
+          else
+            fb[0][q >> 1] = frag<BKC>(nb, ob, q >> 1, nks);
+        }
+        if ((q & 3) == 0) {
+          if (h == 3) load_b(sb, kt + 2, q >> 2);
+          if (h == 0) load_a(sa2, kt + 2, q >> 2);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
-  // Tile kt: one barrier at the top, then 32 MFMAs on fragments in hand;
-  // next to the first 16 the 16 fragment reads of tile kt+1, and the loads,
-  // A's before B's: a k-contiguous A with three slots loads half of its pair
-  // kt+5, kt+6 (odd kt) or the other half of pair kt+4, kt+5 (even kt), with
-  // two slots its pair kt+3, kt+4 (odd kt); a k-contiguous B its pair kt+3,
-  // kt+4 (odd kt); an mn-contiguous operand its tile kt+4.  At the barrier
-  // tile kt+1 must have landed; only loads issued after its last one may
-  // still be in flight.
-  auto tile = [&](auto parity, int kt) {
-    constexpr int P = decltype(parity)::value;  // kt % 2
-    const bf16* na = ra + tile_base<AK, NSA>(kt + 1);
-    const bf16* nb = rb + tile_base<BKC, NSB>(kt + 1);
-    dma_barrier<P == 0 ? kWaitEven : kWaitOdd>();
-#pragma unroll
-    for (int q = 0; q < 32; ++q) {
-      const int ks = q >> 4, i = (q >> 2) & 3, j = q & 3;
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[P][ks][j], fa[P][ks][i], acc[i][j], 0, 0, 0);
-      if (q < 16) {  // read order per k-substep: B0 A0 B1 B2 B3 A1 A2 A3
-        const int rk = q >> 3, r = q & 7;
-        if (r == 0 || r == 2 || r == 3 || r == 4)
-          fb[P ^ 1][rk][r == 0 ? 0 : r - 1] = frag<BKC>(nb, ob, r == 0 ? 0 : r - 1, P ^ 1, rk);
-        else
-          fa[P ^ 1][rk][r == 1 ? 0 : r - 4] = frag<AK>(na, oa, r == 1 ? 0 : r - 4, P ^ 1, rk);
-      }
-      if constexpr (NSA == 3) {
-        if (q < 8 && (q & 1) == 0) load_a(P == 1 ? kt + 5 : kt + 4, (P == 1 ? 0 : 4) + (q >> 1));
-      } else if constexpr (AK) {
-        if (P == 1 && q < 16 && (q & 1)) load_a(kt + 3, q >> 1);
-      } else {
-        if (q < 16 && (q & 3) == 3) load_a(kt + 4, q >> 2);
-      }
-      if constexpr (BKC) {
-        constexpr int q0 = AK ? 8 : 16;  // after A's loads
-        if (P == 1 && q >= q0 && q < q0 + kLoadsKC) load_b(kt + 3, q - q0);
-      } else {
-        if (q >= 16 && (q & 3) == 3) load_b(kt + 4, (q - 16) >> 2);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  // Tiles in pairs (a phantom tile past the end loads and multiplies zeros).
-  for (int kt = 0; kt < nk; kt += 2) {
-    tile(std::integral_constant<int, 0>(), kt);
-    tile(std::integral_constant<int, 1>(), kt + 1);
+    sa = sa1;
   }
 
-  // Epilogue staged through LDS.  A lane holds, per 32x32 block, one output
+  // Epilogue staged through LDS.  A lane holds, per 16x16 block, one output
   // row and 4 consecutive columns; stored directly that scatters every store
-  // over 32 rows.  Instead each wave writes one block row of its results
+  // over 16 rows.  Instead each wave writes one block row of its results
   // (32 x 128 float32, alpha applied) into a private [32][kStagePitch] block
   // and reads it back row-major: a half-wave then covers 128 contiguous
   // columns of one row, so the residual loads and the output stores (one
@@ -924,10 +887,11 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
   // workgroup barrier, whose memory fence would wait for every store in
   // flight, and the stores drain while the wave goes on.
   const float alpha = g.alpha * (g.alpha_dev ? *g.alpha_dev : 1.f);
-  const int half = lane >> 5, lm = lane & 31;
+  const int half = lane >> 5;
+  const int l16 = lane & 15, q16 = 4 * (lane >> 4);
   float* part = g.part ? g.part + static_cast<int64_t>(sp) * g.M * g.N : nullptr;
   float* stage = reinterpret_cast<float*>(ring) + wave * (32 * kStagePitch);
-  const int c = lm * 4;
+  const int c = (lane & 31) * 4;
   const int n = n0 + wn * 128 + c;
   // A block row takes the branch-free path when all its 32 rows and 128
   // columns are in range.
@@ -951,16 +915,16 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
       bf16* C = static_cast<bf16*>(g.C);
       bf16* Sp = static_cast<bf16*>(g.aux);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int mb = m0 + wm * 128 + i * 32;
+      for (int i = 0; i < 2; ++i) {
+        const int mb = m0 + wm * 64 + i * 32;
         if (mb >= M) break;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const floatx16& a = acc[i][j];
-            *reinterpret_cast<uint2*>(st16 + lm * kStagePitch16 + j * 32 + 8 * q + 4 * half) =
-                pack4_bf16(alpha * a[4 * q], alpha * a[4 * q + 1], alpha * a[4 * q + 2], alpha * a[4 * q + 3]);
+          for (int j = 0; j < 8; ++j) {
+            const floatx4& a = acc[2 * i + ii][j];
+            *reinterpret_cast<uint2*>(st16 + (16 * ii + l16) * kStagePitch16 + j * 16 + q16) =
+                pack4_bf16(alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]);
           }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         // staged columns 0-63 are gate (u) columns, 64-127 up (v) columns
@@ -976,14 +940,14 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         // s = silu(u) v from the float32 accumulators (see below)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
+          for (int j = 0; j < 4; ++j) {
             float sv[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              sv[e] = swiglu_fwd_f(alpha * acc[i][j][4 * q + e], alpha * acc[i][j + 2][4 * q + e]);
-            *reinterpret_cast<uint2*>(st16 + lm * kStagePitch16 + j * 32 + 8 * q + 4 * half) =
+              sv[e] = swiglu_fwd_f(alpha * acc[2 * i + ii][j][e], alpha * acc[2 * i + ii][j + 4][e]);
+            *reinterpret_cast<uint2*>(st16 + (16 * ii + l16) * kStagePitch16 + j * 16 + q16) =
                 pack4_bf16(sv[0], sv[1], sv[2], sv[3]);
           }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -1005,19 +969,19 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
       bf16* st16 = reinterpret_cast<bf16*>(stage);
       const int rr = lane >> 4, cc = (lane & 15) * 8;  // read: row rr of each 4, columns cc..cc+7
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int mb = m0 + wm * 128 + i * 32;
+      for (int i = 0; i < 2; ++i) {
+        const int mb = m0 + wm * 64 + i * 32;
         if (mb + 32 > M) {
-          if (mb < M) epilogue_plain_edge_bf16(g, acc[i], alpha, mb, n0 + wn * 128, lm, half, M);
+          if (mb < M) epilogue_plain_edge_bf16(g, acc[2 * i], acc[2 * i + 1], alpha, mb, n0 + wn * 128, l16, q16, M);
           continue;
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const floatx16& a = acc[i][j];
-            *reinterpret_cast<uint2*>(st16 + lm * kStagePitch16 + j * 32 + 8 * q + 4 * half) =
-                pack4_bf16(alpha * a[4 * q], alpha * a[4 * q + 1], alpha * a[4 * q + 2], alpha * a[4 * q + 3]);
+          for (int j = 0; j < 8; ++j) {
+            const floatx4& a = acc[2 * i + ii][j];
+            *reinterpret_cast<uint2*>(st16 + (16 * ii + l16) * kStagePitch16 + j * 16 + q16) =
+                pack4_bf16(alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]);
           }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         // rows are 264 bytes apart (8-byte aligned, no bank conflicts for the
@@ -1039,17 +1003,17 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
     }
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < 2; ++i) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const floatx16& a = acc[i][j];
-        *reinterpret_cast<float4*>(stage + lm * kStagePitch + j * 32 + 8 * q + 4 * half) =
-            make_float4(alpha * a[4 * q], alpha * a[4 * q + 1], alpha * a[4 * q + 2], alpha * a[4 * q + 3]);
+      for (int j = 0; j < 8; ++j) {
+        const floatx4& a = acc[2 * i + ii][j];
+        *reinterpret_cast<float4*>(stage + (16 * ii + l16) * kStagePitch + j * 16 + q16) =
+            make_float4(alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]);
       }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // staged values visible to the wave
-    const int mb = m0 + wm * 128 + i * 32;             // first row of the block row
+    const int mb = m0 + wm * 64 + i * 32;              // first row of the block row
     if constexpr (EPI == kEpiGluBwd) {
       glu_bwd_rows(g, stage, mb + half, half, c, n, M, n0 + wn * 128 + 128 <= g.N && mb + 32 <= M);
     } else if constexpr (EPI == kEpiRelu2Fwd) {
@@ -1066,10 +1030,10 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
   }
 }
 
-#define LD_BIG_ATTRS __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+#define LD_BIG_ATTRS __global__ __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #define LD_BIG_KERNEL(name, ak, bk)                                                    \
   LD_BIG_ATTRS void name(GemmArgs g) {                                                 \
-    __shared__ __align__(16) bf16 ring[ring_elems<ak, bk>()];                          \
+    __shared__ __align__(16) bf16 ring[kRingElems];                          \
     gemm_big_body<ak, bk>(g, ring, blockIdx.x, gridDim.x, blockIdx.y, gridDim.y);      \
   }
 LD_BIG_KERNEL(ld_gemm_bf16_nt_256, true, true)
@@ -1079,13 +1043,13 @@ LD_BIG_KERNEL(ld_gemm_bf16_tt_256, false, true)
 
 // C = [u v] rows and aux = silu(u) v rows of the SwiGLU projection (see GemmArgs).
 LD_BIG_ATTRS void ld_gemm_bf16_nt_glu_256(GemmArgs g) {
-  __shared__ __align__(16) bf16 ring[ring_elems<true, true>()];
+  __shared__ __align__(16) bf16 ring[kRingElems];
   gemm_big_body<true, true, kEpiGluFwd>(g, ring, blockIdx.x, gridDim.x, 0, 1);
 }
 
 // C = u rows and aux = relu(u)^2 rows of the squared-ReLU projection (see GemmArgs).
 LD_BIG_ATTRS void ld_gemm_bf16_nt_relu2_256(GemmArgs g) {
-  __shared__ __align__(16) bf16 ring[ring_elems<true, true>()];
+  __shared__ __align__(16) bf16 ring[kRingElems];
   gemm_big_body<true, true, kEpiRelu2Fwd>(g, ring, blockIdx.x, gridDim.x, 0, 1);
 }
 
@@ -1099,7 +1063,7 @@ LD_BIG_ATTRS void ld_gemm_bf16_nt_relu2_256(GemmArgs g) {
 template <int EPI2>
 __device__ __forceinline__ void gemm_pair_body(const GemmArgs& g1, const GemmArgs& g3, const GemmArgs& g2, int tiles1,
                                                int splits1, int tiles3, int tiles2, int g2_first) {
-  __shared__ __align__(16) bf16 ring[ring_elems<true, false>()];
+  __shared__ __align__(16) bf16 ring[kRingElems];
   const int n1 = tiles1 * splits1;
   int id = blockIdx.x;
   if (g2_first) {
@@ -1167,6 +1131,8 @@ void set_attrs() {
 
 }  // namespace
 
+constexpr int kPlanK = 32;  // unit of k in the launch estimates
+
 GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, int64_t max_m,
                    int64_t max_k, bool allow_split) {
   GemmPlan p{};
@@ -1182,7 +1148,7 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
   const int64_t b_span = 2 * g.ldb * (b_kcontig ? static_cast<int64_t>(g.N) : max_k);
   // split-K only for float32 outputs without a residual (weight gradients);
   // such a GEMM fills the CUs through its splits even with few tiles
-  const bool splittable = allow_split && g.c_f32 && !g.R && !g.out_map.idx && g.ldc == g.N && max_k >= 16 * GK;
+  const bool splittable = allow_split && g.c_f32 && !g.R && !g.out_map.idx && g.ldc == g.N && max_k >= 16 * kPlanK;
   p.big = (g.N % 4 == 0) && (g.ldc % 4 == 0) && (!g.R || g.ldr % 4 == 0) && max_m >= 512 && g.N >= 512 &&
           (big_tiles >= 32 || (splittable && big_tiles * kMaxSplits >= 32)) && a_span < kBigMaxSpan &&
           b_span < kBigMaxSpan;
@@ -1192,7 +1158,7 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
       for (int s = 1; s <= kMaxSplits; ++s) {
         const int64_t wg = big_tiles * s;
         const double eff = static_cast<double>(wg) / (256.0 * ((wg + 255) / 256)) - 0.02 * (s - 1);
-        if (eff > best + 1e-9 && max_k / s >= 8 * GK) {
+        if (eff > best + 1e-9 && max_k / s >= 8 * kPlanK) {
           best = eff;
           p.splits = s;
         }
@@ -1237,7 +1203,7 @@ hipError_t launch_gemm_plan(int dtype, int a_kcontig, int b_kcontig, const GemmP
     } else {
       g.part = nullptr;
     }
-    const dim3 grid(static_cast<unsigned>(tiles), p.splits), block(256);
+    const dim3 grid(static_cast<unsigned>(tiles), p.splits), block(kBigThreads);
     if (a_kcontig && b_kcontig)
       hipLaunchKernelGGL(ld_gemm_bf16_nt_256, grid, block, 0, s, g);
     else if (a_kcontig)
@@ -1295,8 +1261,8 @@ PairPlan plan_gemm_pair(int64_t m1, int64_t n1, int64_t k1, int64_t m3, int64_t 
   auto tiles = [](int64_t m, int64_t n) { return ((m + GB - 1) / GB) * ((n + GB - 1) / GB); };
   const int64_t tiles1 = m1 > 0 ? tiles(m1, n1) : 0, tiles3 = m3 > 0 ? tiles(m3, n3) : 0;
   const int64_t tiles2 = tiles(m2, n2);
-  const int64_t nkt1 = (k1 + GK - 1) / GK;
-  const double c2 = static_cast<double>((k2 + GK - 1) / GK) + kEpi;
+  const int64_t nkt1 = (k1 + kPlanK - 1) / kPlanK;
+  const double c2 = static_cast<double>((k2 + kPlanK - 1) / kPlanK) + kEpi;
   const double c3 = static_cast<double>(nkt1) + kEpi;
   PairPlan best{1, 0, 0.0};
   double best_t = 0.0;
@@ -1323,14 +1289,14 @@ PairPlan plan_gemm_pair(int64_t m1, int64_t n1, int64_t k1, int64_t m3, int64_t 
 hipError_t launch_gemm_glu_fwd(const GemmArgs& g, int64_t max_m, hipStream_t s) {
   if (max_m <= 0 || g.N <= 0) return hipSuccess;
   const int64_t tiles = ((max_m + GB - 1) / GB) * (g.N / GB);
-  hipLaunchKernelGGL(ld_gemm_bf16_nt_glu_256, dim3(static_cast<unsigned>(tiles)), dim3(256), 0, s, g);
+  hipLaunchKernelGGL(ld_gemm_bf16_nt_glu_256, dim3(static_cast<unsigned>(tiles)), dim3(kBigThreads), 0, s, g);
   return hipGetLastError();
 }
 
 hipError_t launch_gemm_relu2_fwd(const GemmArgs& g, int64_t max_m, hipStream_t s) {
   if (max_m <= 0 || g.N <= 0) return hipSuccess;
   const int64_t tiles = ((max_m + GB - 1) / GB) * ((g.N + GB - 1) / GB);
-  hipLaunchKernelGGL(ld_gemm_bf16_nt_relu2_256, dim3(static_cast<unsigned>(tiles)), dim3(256), 0, s, g);
+  hipLaunchKernelGGL(ld_gemm_bf16_nt_relu2_256, dim3(static_cast<unsigned>(tiles)), dim3(kBigThreads), 0, s, g);
   return hipGetLastError();
 }
 
@@ -1351,15 +1317,15 @@ hipError_t launch_gemm_pair(GemmArgs g1, const GemmArgs* g3, const PairPlan& p, 
   const int64_t wg = tiles1 * splits1 + tiles3 + tiles2;
   if (wg <= 0) return hipSuccess;
   if (g2.relu2)
-    hipLaunchKernelGGL(ld_gemm_bf16_tn_nn_relu2_256, dim3(static_cast<unsigned>(wg)), dim3(256), 0, s, g1, g3v, g2,
+    hipLaunchKernelGGL(ld_gemm_bf16_tn_nn_relu2_256, dim3(static_cast<unsigned>(wg)), dim3(kBigThreads), 0, s, g1, g3v, g2,
                        static_cast<int>(tiles1), splits1, static_cast<int>(tiles3), static_cast<int>(tiles2),
                        p.g2_first);
   else if (g2.glu_f > 0)
-    hipLaunchKernelGGL(ld_gemm_bf16_tn_nn_glu_256, dim3(static_cast<unsigned>(wg)), dim3(256), 0, s, g1, g3v, g2,
+    hipLaunchKernelGGL(ld_gemm_bf16_tn_nn_glu_256, dim3(static_cast<unsigned>(wg)), dim3(kBigThreads), 0, s, g1, g3v, g2,
                        static_cast<int>(tiles1), splits1, static_cast<int>(tiles3), static_cast<int>(tiles2),
                        p.g2_first);
   else
-    hipLaunchKernelGGL(ld_gemm_bf16_tn_nn_256, dim3(static_cast<unsigned>(wg)), dim3(256), 0, s, g1, g3v, g2,
+    hipLaunchKernelGGL(ld_gemm_bf16_tn_nn_256, dim3(static_cast<unsigned>(wg)), dim3(kBigThreads), 0, s, g1, g3v, g2,
                        static_cast<int>(tiles1), splits1, static_cast<int>(tiles3), static_cast<int>(tiles2),
                        p.g2_first);
   return hipGetLastError();

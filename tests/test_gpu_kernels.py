@@ -189,6 +189,31 @@ def test_gemm_bf16_big_tiles(layout, shape):
     assert rel(f64(Cd), f64(R) - 1.5 * ref) < TOL_BF16
 
 
+@pytest.mark.parametrize("layout", [(1, 1), (1, 0), (0, 0), (0, 1)])
+@pytest.mark.parametrize("K", [8, 64, 72, 128, 192, 264])
+def test_gemm_bf16_big_k_steps(layout, K):
+    """The 256x256 kernel's ring at its first k steps (one step, a tail of 8,
+    fewer steps than slots), rows and columns 8 past a tile edge.  float32
+    output: sums of K exact products, error below K 2^-24 of the absolute sum;
+    bf16 output: one rounding to 8 significant bits more (at most 2^-8)."""
+    ak, bk = layout
+    M, N = 2056, 1032
+    g = torch.Generator().manual_seed(8)
+    A = torch.randn(M, K, generator=g).to(torch.bfloat16)
+    B = torch.randn(N, K, generator=g).to(torch.bfloat16)
+    Ad = (A if ak else A.t().contiguous()).to(DEV)
+    Bd = (B if bk else B.t().contiguous()).to(DEV)
+    Cf = torch.full((M, N), 7.0, dtype=torch.float32, device=DEV)
+    Cb = torch.full((M, N), 7.0, dtype=torch.bfloat16, device=DEV)
+    for C, f32 in ((Cf, True), (Cb, False)):
+        ld.ld_gemm(ak, bk, M, N, K, Ad, K if ak else M, Bd, K if bk else N, C, N, c_f32=f32)
+    torch.cuda.synchronize()
+    ref = f64(A) @ f64(B).T
+    bound = K * 2.0 ** -24 * (np.abs(f64(A)) @ np.abs(f64(B)).T)
+    assert np.all(np.abs(f64(Cf) - ref) <= bound)
+    assert np.all(np.abs(f64(Cb) - ref) <= 1.01 * (bound + 2.0 ** -8 * np.abs(ref)))
+
+
 @pytest.mark.parametrize("layout", [(0, 0), (1, 0)])
 def test_gemm_bf16_split_k(layout):
     """float32 output with split-K partials summed in a fixed order."""
