@@ -373,8 +373,8 @@ int ld_gemm_skinny(int32_t M, int32_t N, int32_t K, const void* A, int32_t lda, 
  *   act 2: squared ReLU, C = relu(bf16(alpha * A' W^T))^2 (R must be NULL).
  * A [M, K], W and C (bf16 [M, N], leading dimension ldc) are device
  * pointers; A, W (and g) 16-byte aligned, lda and ldw multiples of 8,
- * K % 8 == 0.  The rows of A are staged in LDS: K <= 4096 with g, K <= 9664
- * without; LD_E_UNSUPPORTED beyond.  No workspace; deterministic. */
+ * K % 8 == 0.  K <= 4096 with g, K <= 9664 without; LD_E_UNSUPPORTED beyond.
+ * No workspace; deterministic. */
 int ld_gemm_dec(int32_t M, int32_t N, int32_t K, const void* A, int32_t lda, const void* g, float eps,
                 const void* W, int32_t ldw, void* C, int32_t ldc, float alpha, const void* R, int32_t ldr,
                 int32_t act, void* stream);

@@ -1167,7 +1167,7 @@ int check_host_counts(const Dims& D, const LayerMasks& lm, const std::vector<int
 // Scratch of ld_stack_decode for n_new rows per sequence and caches of s_max
 // positions.
 struct DecLayout {
-  size_t h, rstd, qkv, att, z, uv, s, part_o, part_ml, skp, skp_bytes, total;
+  size_t h, rstd, qkv, att, z, uv, s, part_o, part_ml, total;
 };
 
 size_t skinny_part_bytes(int64_t M, int64_t N, int64_t K) {
@@ -1175,14 +1175,6 @@ size_t skinny_part_bytes(int64_t M, int64_t N, int64_t K) {
   const int ks = skinny_ksplit(M, N, K);
   return ks > 1 ? static_cast<size_t>(ks) * M * N * 4 : 0;
 }
-
-// Partials of a skinny GEMM whose reduction is fused with what follows it
-// (written even with one split).
-size_t skinny_fused_part_bytes(int64_t M, int64_t N, int64_t K) {
-  if (M > kSkinnyMaxM) return 0;
-  return static_cast<size_t>(skinny_ksplit(M, N, K)) * M * N * 4;
-}
-
 
 int64_t dec_chunks(int64_t keys) { return (keys + kDecKeys - 1) / kDecKeys; }
 
@@ -1205,9 +1197,6 @@ DecLayout dec_layout(const Dims& D, int64_t n_new, int64_t s_max) {
   const size_t pc = static_cast<size_t>(D.B) * D.H * dec_chunks(s_max) * kDecMaxRows;
   L.part_o = take(4 * pc * D.dh);
   L.part_ml = take(4 * pc * 2);
-  const int64_t shapes[4][2] = {{3 * D.d, D.d}, {D.d, D.d}, {D.fw, D.d}, {D.d, D.f}};
-  for (const auto& sh : shapes) L.skp_bytes = std::max(L.skp_bytes, skinny_fused_part_bytes(M, sh[0], sh[1]));
-  L.skp = take(L.skp_bytes);
   L.total = o;
   return L;
 }
@@ -1218,35 +1207,15 @@ struct KvOut {
   int32_t d, n, s_max, pos;
 };
 
-// C[M, N] = (R ? R : 0) + alpha * A W^T for the rows of a decoding step:
-// the skinny kernel for M <= kSkinnyMaxM, else the general GEMM.  kv: the
-// columns from kv.d on also go to that cache (skinny kernel), or the caller
-// stores them (general GEMM: returns with *kv_done = false).
+// C[M, N] = (R ? R : 0) + alpha * A W^T on the general GEMM kernels, for
+// decoding steps of more than kSkinnyMaxM rows.
 int dec_gemm(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, int64_t ldc,
-             const void* R, int64_t ldr, int64_t M, int64_t N, int64_t K, float alpha, float* part,
-             size_t part_bytes, hipStream_t s, const KvOut* kv = nullptr, bool* kv_done = nullptr) {
-  if (kv_done) *kv_done = false;
-  if (M > kSkinnyMaxM) {
-    GemmArgs g = gemm_args();
-    g.A = A;
-    g.lda = lda;
-    g.B = W;
-    g.ldb = ldw;
-    g.C = C;
-    g.ldc = ldc;
-    g.R = R;
-    g.ldr = ldr;
-    g.M = static_cast<int32_t>(M);
-    g.N = static_cast<int32_t>(N);
-    g.K = static_cast<int32_t>(K);
-    g.alpha = alpha;
-    return run_gemm(LD_BF16, 1, 1, g, M, M, K, s);
-  }
-  SkinnyArgs g{};
+             const void* R, int64_t ldr, int64_t M, int64_t N, int64_t K, float alpha, hipStream_t s) {
+  GemmArgs g = gemm_args();
   g.A = A;
   g.lda = lda;
-  g.W = W;
-  g.ldw = ldw;
+  g.B = W;
+  g.ldb = ldw;
   g.C = C;
   g.ldc = ldc;
   g.R = R;
@@ -1255,27 +1224,10 @@ int dec_gemm(const void* A, int64_t lda, const void* W, int64_t ldw, void* C, in
   g.N = static_cast<int32_t>(N);
   g.K = static_cast<int32_t>(K);
   g.alpha = alpha;
-  const int ks = skinny_ksplit(M, N, K);
-  if (ks > 1) {
-    if (static_cast<size_t>(ks) * M * N * 4 > part_bytes) return fail(LD_E_WORKSPACE, "skinny GEMM scratch too small");
-    g.part = part;
-  }
-  if (kv) {
-    g.kv = kv->kv;
-    g.kv_d = kv->d;
-    g.kv_n = kv->n;
-    g.kv_s_max = kv->s_max;
-    g.kv_pos = kv->pos;
-    if (kv_done) *kv_done = true;
-  }
-  ProfScope ps(M <= 32 ? "ld_gemm_bf16_skinny<1>" : "ld_gemm_bf16_skinny<2>", s);
-  hipError_t e = launch_gemm_skinny(g, ks, s);
-  if (e != hipSuccess) return fail(LD_E_HIP, "skinny GEMM: %s", hipGetErrorString(e));
-  ps.end(2.0 * M * N * K, 2.0 * (M * K + N * K + M * N) + (R ? 2.0 * M * N : 0.0));
-  return LD_OK;
+  return run_gemm(LD_BF16, 1, 1, g, M, M, K, s);
 }
 
-// Fused decode projection (at most 8 rows; see launch_gemm_dec): C = act(R +
+// Fused decode projection (see launch_gemm_dec): C = act(R +
 // alpha * A' W^T) with A' the RMSNorm of A's rows when g is set.
 int dec_proj(const void* A, int64_t lda, const void* g, float eps, const void* W, int64_t ldw, void* C,
              int64_t ldc, const void* R, int64_t ldr, int64_t M, int64_t N, int64_t K, float alpha, int act,
@@ -1308,30 +1260,6 @@ int dec_proj(const void* A, int64_t lda, const void* g, float eps, const void* W
   if (e != hipSuccess) return fail(LD_E_HIP, "decode projection: %s", hipGetErrorString(e));
   const double wrows = act == kDecActSwiglu ? 2.0 * N : static_cast<double>(N);
   ps.end(2.0 * M * wrows * K, 2.0 * (M * K + wrows * K + M * N) + (R ? 2.0 * M * N : 0.0));
-  return LD_OK;
-}
-
-// Skinny GEMM (at most 64 rows) writing only its split-K partials, for a
-// fused reduction launched next; g and ks describe them.
-int skinny_part(const void* A, int64_t lda, const void* W, int64_t ldw, int64_t M, int64_t N, int64_t K,
-                float alpha, float* part, size_t part_bytes, hipStream_t s, SkinnyArgs& g, int& ks) {
-  g = SkinnyArgs{};
-  g.A = A;
-  g.lda = lda;
-  g.W = W;
-  g.ldw = ldw;
-  g.M = static_cast<int32_t>(M);
-  g.N = static_cast<int32_t>(N);
-  g.K = static_cast<int32_t>(K);
-  g.alpha = alpha;
-  g.part = part;
-  g.part_only = 1;
-  ks = skinny_ksplit(M, N, K);
-  if (static_cast<size_t>(ks) * M * N * 4 > part_bytes) return fail(LD_E_WORKSPACE, "skinny GEMM scratch too small");
-  ProfScope ps(M <= 32 ? "ld_gemm_bf16_skinny<1>" : "ld_gemm_bf16_skinny<2>", s);
-  const hipError_t e = launch_gemm_skinny(g, ks, s);
-  if (e != hipSuccess) return fail(LD_E_HIP, "skinny GEMM: %s", hipGetErrorString(e));
-  ps.end(2.0 * M * N * K, 2.0 * (M * K + N * K) + 4.0 * ks * M * N);
   return LD_OK;
 }
 
@@ -1657,7 +1585,6 @@ int ld_stack_decode(const ld_config* cfg, int32_t n_layers, const ld_weights* w,
   hipStream_t s = as_stream(stream);
   char* base = static_cast<char*>(ws);
   auto P = [&](size_t off) { return static_cast<void*>(base + off); };
-  float* skp = L.skp_bytes ? reinterpret_cast<float*>(base + L.skp) : nullptr;
   const int64_t M = D.B * n_new, d = D.d;
   hipError_t e;
   auto norm = [&](const void* src, const void* gain) {
@@ -1675,15 +1602,10 @@ int ld_stack_decode(const ld_config* cfg, int32_t n_layers, const ld_weights* w,
     ps.end(0, 4.0 * M * d);
     return static_cast<int>(LD_OK);
   };
-  // At most 8 rows (one new row per sequence of a batch of 8): each
-  // projection is one fused launch that normalises its input rows and
-  // applies the FFN activation itself.
-  const bool fused = dec_gemm_ok(M, d, true) && dec_gemm_ok(M, D.f, false);
-  // 9 to 64 rows (verify steps): split-K skinny GEMMs whose partial sums are
-  // reduced together with what follows them: the residual and the next
-  // RMSNorm (output and down projections), or the FFN activation.
-  const bool part_fused = !fused && M <= kSkinnyMaxM;
-  bool h_ready = false;  // L.h holds RMSNorm(x) with this layer's gain
+  // At most 64 rows: each projection is one fused launch that applies the
+  // residual or the FFN activation, and normalises its input rows itself
+  // where they stay in registers (else a norm launch goes before it).
+  const bool fused = M <= kSkinnyMaxM, fused_norm = fused && dec_gemm_fuses_norm(M, d);
   const int act = D.kind == LD_BLOCK_SWIGLU ? kDecActSwiglu : kDecActRelu2;
   for (int32_t l = 0; l < n_layers; ++l) {
     if (active && !active[l]) continue;
@@ -1691,21 +1613,14 @@ int ld_stack_decode(const ld_config* cfg, int32_t n_layers, const ld_weights* w,
     const ld_weights& wl = w[l];
     // h = RMSNorm(x); qkv = h W_qkv^T; new keys/values into the cache
     const KvOut ko{kv[l], static_cast<int32_t>(d), n_new, s_max, pos};
-    bool kv_done = false;
+    if (!fused_norm)
+      if (int rc = norm(x, wl.g_attn)) return rc;
     if (fused) {
-      if (int rc = dec_proj(x, d, wl.g_attn, cfg->rms_eps, wl.w_qkv, d, P(L.qkv), 3 * d, nullptr, 0, M, 3 * d, d,
-                            1.f, kDecActNone, s, &ko))
+      if (int rc = dec_proj(fused_norm ? x : P(L.h), d, fused_norm ? wl.g_attn : nullptr, cfg->rms_eps, wl.w_qkv, d,
+                            P(L.qkv), 3 * d, nullptr, 0, M, 3 * d, d, 1.f, kDecActNone, s, &ko))
         return rc;
-      kv_done = true;
     } else {
-      if (!h_ready)
-        if (int rc = norm(x, wl.g_attn)) return rc;
-      h_ready = false;
-      if (int rc = dec_gemm(P(L.h), d, wl.w_qkv, d, P(L.qkv), 3 * d, nullptr, 0, M, 3 * d, d, 1.f, skp,
-                            L.skp_bytes, s, &ko, &kv_done))
-        return rc;
-    }
-    if (!kv_done) {
+      if (int rc = dec_gemm(P(L.h), d, wl.w_qkv, d, P(L.qkv), 3 * d, nullptr, 0, M, 3 * d, d, 1.f, s)) return rc;
       KvArgs k{};
       k.qkv = P(L.qkv);
       k.ld_qkv = 3 * d;
@@ -1746,8 +1661,10 @@ int ld_stack_decode(const ld_config* cfg, int32_t n_layers, const ld_weights* w,
     if (fused) {
       if (int rc = dec_proj(P(L.att), d, nullptr, 0.f, wl.w_o, d, P(L.z), d, x, d, M, d, d, r, kDecActNone, s))
         return rc;
-      if (int rc = dec_proj(P(L.z), d, wl.g_mlp, cfg->rms_eps, wl.w_gate_up, d, P(L.s), D.f, nullptr, 0, M, D.f,
-                            d, 1.f, act, s))
+      if (!fused_norm)
+        if (int rc = norm(P(L.z), wl.g_mlp)) return rc;
+      if (int rc = dec_proj(fused_norm ? P(L.z) : P(L.h), d, fused_norm ? wl.g_mlp : nullptr, cfg->rms_eps,
+                            wl.w_gate_up, d, P(L.s), D.f, nullptr, 0, M, D.f, d, 1.f, act, s))
         return rc;
       // x = z + r (s W_down^T)
       if (int rc = dec_proj(P(L.s), D.f, nullptr, 0.f, wl.w_down, D.f, x, d, P(L.z), d, M, d, D.f, r,
@@ -1755,41 +1672,9 @@ int ld_stack_decode(const ld_config* cfg, int32_t n_layers, const ld_weights* w,
         return rc;
       continue;
     }
-    if (part_fused) {
-      SkinnyArgs g{};
-      int ks = 1;
-      // z = x + r (att W_o^T) and h = RMSNorm(z)
-      if (int rc = skinny_part(P(L.att), d, wl.w_o, d, M, d, d, r, skp, L.skp_bytes, s, g, ks)) return rc;
-      g.C = P(L.z);
-      g.ldc = d;
-      g.R = x;
-      g.ldr = d;
-      if ((e = launch_skinny_reduce_norm(g, ks, wl.g_mlp, cfg->rms_eps, P(L.h), s)) != hipSuccess)
-        return fail(LD_E_HIP, "skinny reduce: %s", hipGetErrorString(e));
-      // s = act(h W_gate_up^T)
-      if (int rc = skinny_part(P(L.h), d, wl.w_gate_up, d, M, D.fw, d, 1.f, skp, L.skp_bytes, s, g, ks)) return rc;
-      if ((e = launch_skinny_reduce_act(g, ks, act, static_cast<int>(D.f), P(L.s), s)) != hipSuccess)
-        return fail(LD_E_HIP, "skinny reduce: %s", hipGetErrorString(e));
-      // x = z + r (s W_down^T), and the next active layer's h = RMSNorm(x)
-      if (int rc = skinny_part(P(L.s), D.f, wl.w_down, D.f, M, d, D.f, r, skp, L.skp_bytes, s, g, ks)) return rc;
-      g.C = x;
-      g.ldc = d;
-      g.R = P(L.z);
-      g.ldr = d;
-      int32_t next = l + 1;
-      while (next < n_layers && active && !active[next]) ++next;
-      const void* gain = next < n_layers ? w[next].g_attn : nullptr;
-      if ((e = launch_skinny_reduce_norm(g, ks, gain, cfg->rms_eps, P(L.h), s)) != hipSuccess)
-        return fail(LD_E_HIP, "skinny reduce: %s", hipGetErrorString(e));
-      h_ready = gain != nullptr;
-      continue;
-    }
-    if (int rc = dec_gemm(P(L.att), d, wl.w_o, d, P(L.z), d, x, d, M, d, d, r, skp, L.skp_bytes, s))
-      return rc;
+    if (int rc = dec_gemm(P(L.att), d, wl.w_o, d, P(L.z), d, x, d, M, d, d, r, s)) return rc;
     if (int rc = norm(P(L.z), wl.g_mlp)) return rc;
-    if (int rc = dec_gemm(P(L.h), d, wl.w_gate_up, d, P(L.uv), D.fw, nullptr, 0, M, D.fw, d, 1.f, skp,
-                          L.skp_bytes, s))
-      return rc;
+    if (int rc = dec_gemm(P(L.h), d, wl.w_gate_up, d, P(L.uv), D.fw, nullptr, 0, M, D.fw, d, 1.f, s)) return rc;
     EltArgs a{};
     a.a = P(L.uv);
     a.out = P(L.s);
@@ -1798,8 +1683,7 @@ int ld_stack_decode(const ld_config* cfg, int32_t n_layers, const ld_weights* w,
     e = D.kind == LD_BLOCK_SWIGLU ? launch_swiglu_fwd(LD_BF16, a, s) : launch_relu2_fwd(LD_BF16, a, s);
     if (e != hipSuccess) return fail(LD_E_HIP, "activation: %s", hipGetErrorString(e));
     // x = z + r (s W_down^T)
-    if (int rc = dec_gemm(P(L.s), D.f, wl.w_down, D.f, x, d, P(L.z), d, M, d, D.f, r, skp, L.skp_bytes, s))
-      return rc;
+    if (int rc = dec_gemm(P(L.s), D.f, wl.w_down, D.f, x, d, P(L.z), d, M, d, D.f, r, s)) return rc;
   }
   return LD_OK;
 }
@@ -1948,19 +1832,38 @@ int ld_gemm_skinny(int32_t M, int32_t N, int32_t K, const void* A, int32_t lda, 
   if (!std::isfinite(alpha)) return fail(LD_E_INVALID, "alpha not finite");
   const size_t need = ld_gemm_skinny_ws_bytes(M, N, K);
   if (need && (!ws || ws_bytes < need)) return fail(LD_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
-  return dec_gemm(A, lda, W, ldw, C, ldc, R, ldr, M, N, K, alpha, static_cast<float*>(ws), ws ? ws_bytes : 0,
-                  as_stream(stream));
+  SkinnyArgs g{};
+  g.A = A;
+  g.lda = lda;
+  g.W = W;
+  g.ldw = ldw;
+  g.C = C;
+  g.ldc = ldc;
+  g.R = R;
+  g.ldr = ldr;
+  g.M = M;
+  g.N = N;
+  g.K = K;
+  g.alpha = alpha;
+  g.part = static_cast<float*>(ws);
+  hipStream_t s = as_stream(stream);
+  ProfScope ps(M <= 32 ? "ld_gemm_bf16_skinny<1>" : "ld_gemm_bf16_skinny<2>", s);
+  const hipError_t e = launch_gemm_skinny(g, skinny_ksplit(M, N, K), s);
+  if (e != hipSuccess) return fail(LD_E_HIP, "skinny GEMM: %s", hipGetErrorString(e));
+  ps.end(2.0 * M * N * K, 2.0 * (1.0 * M * K + 1.0 * N * K + 1.0 * M * N) + (R ? 2.0 * M * N : 0.0));
+  return LD_OK;
 }
 
 int ld_gemm_dec(int32_t M, int32_t N, int32_t K, const void* A, int32_t lda, const void* g, float eps,
                 const void* W, int32_t ldw, void* C, int32_t ldc, float alpha, const void* R, int32_t ldr,
                 int32_t act, void* stream) {
   t_err.clear();
-  if (M < 1 || M > kDecGemmMaxM) return fail(LD_E_SHAPE, "M outside [1, %d]", kDecGemmMaxM);
+  constexpr int32_t kMaxM = 8, kMaxKNorm = 4096, kMaxK = 9664;  // the documented limits of this entry point
+  if (M < 1 || M > kMaxM) return fail(LD_E_SHAPE, "M outside [1, %d]", kMaxM);
   if (N < 1 || K < 8 || K % 8) return fail(LD_E_SHAPE, "need N >= 1, K >= 8, K %% 8 == 0");
   if (act != kDecActNone && act != kDecActSwiglu && act != kDecActRelu2) return fail(LD_E_INVALID, "unknown act");
   if (act != kDecActNone && R) return fail(LD_E_INVALID, "a residual only without activation");
-  if (!dec_gemm_ok(M, K, g != nullptr)) return fail(LD_E_UNSUPPORTED, "K = %d does not fit the staged rows", K);
+  if (K > (g ? kMaxKNorm : kMaxK)) return fail(LD_E_UNSUPPORTED, "K = %d does not fit the staged rows", K);
   if (lda < K || ldw < K || ldc < N || (R && ldr < N)) return fail(LD_E_SHAPE, "leading dimension too small");
   if (lda % 8 || ldw % 8) return fail(LD_E_SHAPE, "lda, ldw must be multiples of 8");
   if (!A || !W || !C) return fail(LD_E_INVALID, "NULL pointer");

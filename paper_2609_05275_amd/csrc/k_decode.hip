@@ -1,9 +1,9 @@
 // Kernels of incremental (KV-cached) decoding: a few new rows per sequence
 // go through a layer whose keys and values of earlier positions are cached.
-// Both hot kernels are bound by HBM reads: the skinny GEMM reads each weight
-// matrix once, the decode attention reads each cached key/value row once.
+// Both hot kernels are bound by HBM reads: the fused projection (below) reads
+// each weight matrix once, the decode attention each cached key/value row.
 //
-// Skinny GEMM (M <= 64 rows, bf16, v_mfma_f32_32x32x16_bf16): one wave owns
+// Skinny GEMM (the standalone entry point; M <= 64 rows, bf16, v_mfma_f32_32x32x16_bf16): one wave owns
 // 32 output columns; the four waves of a workgroup (and, with ksplit > 1,
 // several workgroups) take interleaved 64-wide k chunks of the same columns.
 // Within a chunk the k index of the four MFMAs is permuted so that each lane
@@ -31,8 +31,8 @@ namespace ld {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kSkWaves = 4;
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256) void ld_gemm_bf16_skinny(SkinnyArgs g) {
     const int m = mb * 32 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
     const int n = n0 + (l & 31);
     if (m < g.M && n < g.N) {
-      if (gridDim.y > 1 || g.part_only)
+      if (gridDim.y > 1)
         g.part[(static_cast<int64_t>(blockIdx.y) * g.M + m) * g.N + n] = sum;
       else
         skinny_store(g, m, n, sum);
@@ -141,279 +141,336 @@ __global__ __launch_bounds__(256) void ld_skinny_reduce_k(SkinnyArgs g, int kspl
 
 __device__ __forceinline__ float bf16r(float x) { return static_cast<float>(static_cast<bf16>(x)); }
 
-// Split-K sums (split order) of one row of a skinny GEMM with alpha and the
-// residual, stored as C, then (when a gain is given) the RMSNorm of the
-// stored row (sum of squares over the workgroup in a fixed order):
-// h = bf16(C rstd gain).  One workgroup of 1024 threads per row.
-__global__ __launch_bounds__(1024) void ld_skinny_reduce_norm_k(SkinnyArgs g, int ksplit, const bf16* gain,
-                                                                 float eps, bf16* h) {
-  constexpr int kPer = 4;  // columns per thread and pass: one pass up to 4096 columns
-  __shared__ float wsum[16];
-  const int m = blockIdx.x, tid = threadIdx.x;
-  const int64_t mn = static_cast<int64_t>(g.M) * g.N;
-  const float* prow = g.part + static_cast<int64_t>(m) * g.N;
-  bf16* C = static_cast<bf16*>(g.C) + static_cast<int64_t>(m) * g.ldc;
-  const bf16* R = g.R ? static_cast<const bf16*>(g.R) + static_cast<int64_t>(m) * g.ldr : nullptr;
-  float ss = 0.f;
-  for (int n0 = 0; n0 < g.N; n0 += 1024 * kPer) {
-    float sum[kPer];
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) sum[i] = 0.f;
-    // the splits in order; every column's loads of a split are independent
-#pragma unroll 2
-    for (int sp = 0; sp < ksplit; ++sp)
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        const int n = n0 + i * 1024 + tid;
-        if (n < g.N) sum[i] += prow[sp * mn + n];
-      }
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int n = n0 + i * 1024 + tid;
-      if (n < g.N) {
-        const bf16 o = static_cast<bf16>(g.alpha * sum[i] + (R ? static_cast<float>(R[n]) : 0.f));
-        C[n] = o;
-        const float of = static_cast<float>(o);
-        ss = __builtin_fmaf(of, of, ss);
-      }
-    }
-  }
-  if (!gain) return;  // no norm follows (workgroup-uniform)
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
-  if ((tid & 63) == 0) wsum[tid >> 6] = ss;
-  __syncthreads();
-  float tot = 0.f;
-#pragma unroll
-  for (int w = 0; w < 16; ++w) tot += wsum[w];
-  const float rstd = rsqrtf(tot / static_cast<float>(g.N) + eps);
-  bf16* hr = h + static_cast<int64_t>(m) * g.N;
-  for (int n = tid; n < g.N; n += 1024)  // this thread's own stores, read back
-    hr[n] = static_cast<bf16>(static_cast<float>(C[n]) * rstd * static_cast<float>(gain[n]));
-}
-
-// The FFN activation from a skinny GEMM's partials: u (and v = column f + n
-// for SwiGLU) rounded to bf16 as stored outputs would be, s = act(u, v).
-__global__ __launch_bounds__(256) void ld_skinny_reduce_act_k(SkinnyArgs g, int ksplit, int act, int f, bf16* so) {
-  const int64_t mn = static_cast<int64_t>(g.M) * g.N, total = static_cast<int64_t>(g.M) * f;
-  for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < total; i += gridDim.x * 256ll) {
-    const int64_t m = i / f, n = i % f, iu = m * g.N + n;
-    float su = g.part[iu];
-#pragma unroll 4
-    for (int sp = 1; sp < ksplit; ++sp) su += g.part[sp * mn + iu];
-    const float u = bf16r(g.alpha * su);
-    float out;
-    if (act == kDecActSwiglu) {
-      float sv = g.part[iu + f];
-#pragma unroll 4
-      for (int sp = 1; sp < ksplit; ++sp) sv += g.part[sp * mn + iu + f];
-      out = swiglu_fwd_f(u, bf16r(g.alpha * sv));
-    } else {
-      const float z = fmaxf(u, 0.f);
-      out = z * z;
-    }
-    so[m * f + n] = static_cast<bf16>(out);
-  }
-}
-
 // ------------------------------------------------ fused decode projection
-// At most 8 rows, so the product is a few dot products per weight: vector
-// ALU work (v_dot2 on bf16 pairs), not MFMA tiles, and the layout is chosen
-// for the weight stream.  A tile is 8 output columns (8 rows of W; with
+// At most 64 rows.  Bound by the weight stream: W is read once, and the
+// rest is kept out of its way.  A tile is 8 output columns (8 rows of W; with
 // SwiGLU the 8 gate rows and the 8 up rows of those columns) over the whole
-// k range, so every column is finished in one workgroup (no split-K
-// partials) and N = 2048 still spreads over 256 workgroups.  Lane 8r + t
-// reads 16 bytes at k = 64c + 8t of row r: each load instruction takes 8
-// whole 128-byte lines.  The NW waves take interleaved chunks c, four per
-// pass, the next pass's loads in flight while one is summed (a workgroup
-// may also walk several tiles in turn; the launch gives each one tile, as
-// timing favoured more resident waves over fewer rounds).  The rows of A are
-// staged in LDS once per workgroup (zero rows past M), normalised on the way
-// when a gain is given:
-// one wave per row, sum of squares in lane order, rstd = 1/sqrt(mean + eps),
-// A' = bf16(A rstd g), as the row-wise RMSNorm kernel computes it.  Partial
-// sums are reduced over the 8 lanes of a row, then over the waves in wave
-// order through LDS; the epilogue applies alpha and the residual (and copies
-// key/value columns to the cache) or the activation, rounding u and v to
-// bf16 first as the unfused path stores them.
+// k range, so every column is finished in one workgroup (no split-K partials,
+// no reduction launch) and N = 2048 still spreads over 256 workgroups.
+//
+// Lane l reads 16 bytes of row l % 8 at k = 64c + 32 ((l / 8) % 2) + 8 (l / 16),
+// of W and of the activations alike, so a load instruction takes 8 whole
+// 128-byte lines.  As operands of v_mfma_f32_16x16x32_bf16 the lanes hold 8
+// rows of W (A) and 8 rows of activations (B), each twice: rows 0-7 with the
+// first 32 k of the chunk, rows 8-15 with the last 32.  One product then gives
+// both halves on its diagonal 8x8 blocks, which are added; the off-diagonal
+// blocks mix the halves and are dropped.  (Dot products on the vector ALU,
+// which this replaces, read every row of A from LDS once per 8 columns: at 8
+// rows the LDS, at one row the padding to 8 rows, cost more than the weights.
+// 1B shape at 8 rows, before -> now: QKV 14.8 -> 9.4 us, gate/up 18.5 -> 11.8,
+// output 6.6 -> 5.1, down 11.6 -> 10.4, 25, 45, 8 and 23 MB of weights.  At 48
+// rows, against split-K GEMMs and their reductions: the four projections with
+// their norms and activation 95 -> 75 us; there every CU reading all the
+// activations is what bounds it, at about 15 bytes a clock.)
+//
+// The waves take interleaved chunks.  ld_gemm_bf16_dec keeps its waves'
+// activations in registers (K <= 2048 at up to 48 rows, 4096 at up to 16):
+// loaded straight from memory in operand layout, normalised there when a gain
+// is given (partial sums of squares per wave, one exchange through LDS), and
+// used for every tile the workgroup takes in turn, so a CU reads A once; the
+// first two tiles' weights are requested before anything waits where the
+// registers allow.  ld_gemm_bf16_dec_long streams the activations beside the
+// weights.
+//
+// Partial sums go over the waves in wave order through LDS; the epilogue
+// applies alpha and the residual (and copies key/value columns to the cache)
+// or the activation, rounding u and v to bf16 first as stored outputs would be.
 
-constexpr int kDecCols = 8;   // output columns per workgroup
-constexpr int kDecU = 4;      // chunks per pass
+constexpr int kDecCols = 8;   // output columns per tile
 constexpr int kDecCus = 256;  // compute units
 
-__host__ __device__ inline int dec_pitch(int64_t K) { return static_cast<int>((K + 63) & ~63ll); }
+typedef int int4v __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float dot8(const bf16x8& w, const bf16x8& a, float c) {
+// Sums of the waves' products of one tile: red[wave][j][m][8 columns], MB
+// blocks of 8 rows.
+template <int MB, int NR>
+constexpr int dec_red_floats() { return NR * MB * 8 * kDecCols; }
+
+// Lane l of a product holds D rows 4 (l / 16) + e of column l % 16: the first
+// 32 k's block in the lanes with bits 3 and 5 clear, the last 32 k's in those
+// with both set.  Their sum goes to the wave's block of `red`.
+template <int MB, int NR>
+__device__ __forceinline__ void dec_put(float* red, const floatx4 (&acc)[NR][MB], int lane) {
 #pragma unroll
-  for (int e = 0; e < 8; e += 2)
-    c = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{w[e], w[e + 1]}, bf16x2{a[e], a[e + 1]}, c, false);
-  return c;
+  for (int j = 0; j < NR; ++j)
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      floatx4 v = acc[j][mb];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += __shfl_xor(v[e], 40, 64);
+      if ((lane & 40) == 0)
+        *reinterpret_cast<floatx4*>(red + ((j * MB + mb) * 8 + (lane & 7)) * kDecCols + 4 * (lane >> 4)) = v;
+    }
 }
 
-template <int NW, int ACT, bool NORM>
+// Element (row em, column en) of the output from the waves' sums.
+template <int MB, int ACT, int NW>
+__device__ __forceinline__ void dec_finish(const SkinnyArgs& g, const float* red, int em, int c, int en, uint16_t resid) {
+  constexpr int NR = ACT == kDecActSwiglu ? 2 : 1;
+  constexpr int kWave = dec_red_floats<MB, NR>();
+  const int at = em * kDecCols + c;
+  float s0 = red[at], s1 = 0.f;
+#pragma unroll
+  for (int w = 1; w < NW; ++w) s0 += red[w * kWave + at];
+  if constexpr (NR == 2) {
+    s1 = red[kWave / 2 + at];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s1 += red[w * kWave + kWave / 2 + at];
+  }
+  bf16* C = static_cast<bf16*>(g.C) + static_cast<int64_t>(em) * g.ldc + en;
+  if constexpr (ACT == kDecActSwiglu) {
+    *C = static_cast<bf16>(swiglu_fwd_f(bf16r(g.alpha * s0), bf16r(g.alpha * s1)));
+  } else if constexpr (ACT == kDecActRelu2) {
+    const float z = fmaxf(bf16r(g.alpha * s0), 0.f);
+    *C = static_cast<bf16>(z * z);
+  } else {
+    const bf16 o = static_cast<bf16>(g.alpha * s0 + (g.R ? static_cast<float>(__builtin_bit_cast(bf16, resid)) : 0.f));
+    *C = o;
+    if (g.kv && en >= g.kv_d) {
+      const int64_t b = em / g.kv_n, jj = em % g.kv_n;
+      static_cast<bf16*>(g.kv)[(b * g.kv_s_max + g.kv_pos + jj) * 2 * g.kv_d + (en - g.kv_d)] = o;
+    }
+  }
+}
+
+// The residual of an output element as stored, converted where it is used
+// and loaded without a branch, so that nothing waits for it (and for the loads
+// before it) earlier.  Without a residual: any readable element.
+__device__ __forceinline__ uint16_t dec_resid(const SkinnyArgs& g, int em, int en) {
+  const uint16_t* p = static_cast<const uint16_t*>(g.R ? g.R : g.A);
+  return p[g.R ? static_cast<int64_t>(min(em, g.M - 1)) * g.ldr + min(en, g.N - 1) : 0];
+}
+
+// Zeroes what was loaded from a clamped address: the lane's 8 values at k >= K.
+__device__ __forceinline__ void dec_mask(bf16x8& v, bool keep) {
+  int4v t = __builtin_bit_cast(int4v, v);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) t[i] = keep ? t[i] : 0;
+  v = __builtin_bit_cast(bf16x8, t);
+}
+
+// K <= 64 NW CPW; MB blocks of 8 rows; one thread per output element of a tile
+// (NW * 64 >= 64 MB).
+template <int MB, int ACT, bool NORM, int NW, int CPW>
 __global__ __launch_bounds__(NW * 64) void ld_gemm_bf16_dec(SkinnyArgs g) {
   constexpr int NR = ACT == kDecActSwiglu ? 2 : 1;  // W rows per lane
-  extern __shared__ __align__(16) unsigned char dsm[];
+  constexpr int kRed = NW * dec_red_floats<MB, NR>();
+  static_assert(NW * 64 >= MB * 8 * kDecCols, "a thread per output element");
+  __shared__ __align__(16) float red[2][kRed];
+  __shared__ float ssq[NORM ? NW : 1][MB * 8];
+  __shared__ __align__(16) bf16 gs[NORM ? NW * CPW * 64 : 8];  // the gain
+  static_assert(!NORM || NW * CPW * 64 <= NW * 64 * 8, "one gain chunk per thread");
+  // the second tile's weights go out before the normalisation if the registers allow
+  constexpr bool kTwo = CPW * NR <= 8;  // two tiles' weights in hand, else one
+  constexpr bool kBoth = kTwo && (!NORM || MB <= 2 || NR == 1);
   const int M = g.M, N = g.N, K = g.K;
-  const int pitch = dec_pitch(K);
-  bf16* as = reinterpret_cast<bf16*>(dsm);
-  float* red = reinterpret_cast<float*>(dsm + static_cast<size_t>(kDecGemmMaxM) * pitch * 2);
-  float* fin = red + NW * NR * kDecCols * kDecGemmMaxM;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r = lane >> 3, t = lane & 7;
-  const int nchunks = (K + 63) >> 6;
-  const bf16* A = static_cast<const bf16*>(g.A);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tiles = (N + kDecCols - 1) / kDecCols;
+  const int lk = 32 * ((lane >> 3) & 1) + 8 * (lane >> 4);  // the lane's k of a chunk
   const bf16* W = static_cast<const bf16*>(g.W);
 
-  // This workgroup's tile: columns col of its lanes' rows; the k range in
-  // npass passes of kDecU chunks per wave.
-  const int col = blockIdx.x * kDecCols + r;
-  const bool nvalid = col < N;
-  const int npass = (nchunks + kDecU * NW - 1) / (kDecU * NW);
-  const bf16* wrow[NR];
+  typedef bf16x8 WBuf[CPW][NR];
+  auto load_w = [&](WBuf& wb, int tile) {
+    // no branch around a load (the compiler would wait at each): columns past
+    // N repeat the last, k past K the row's start
+    const int col = min(tile * kDecCols + (lane & 7), N - 1);
 #pragma unroll
-  for (int j = 0; j < NR; ++j) wrow[j] = W + static_cast<int64_t>(nvalid ? col + j * N : 0) * g.ldw + 8 * t;
-
-  typedef bf16x8 WBuf[kDecU][NR];
-  auto load_w = [&](WBuf& wb, int p) {
+    for (int j = 0; j < NR; ++j) {
+      const bf16* wrow = W + static_cast<int64_t>(col + j * N) * g.ldw;
 #pragma unroll
-    for (int u = 0; u < kDecU; ++u) {
-      const int kc = (wave + NW * (kDecU * p + u)) * 64;
-#pragma unroll
-      for (int j = 0; j < NR; ++j) wb[u][j] = (nvalid && kc + 8 * t < K) ? load8(wrow[j] + kc) : zero8();
+      for (int u = 0; u < CPW; ++u) {
+        const int k = (wave + NW * u) * 64 + lk;
+        wb[u][j] = load8(wrow + (k < K ? k : 0));
+      }
     }
   };
-  // the first two passes' loads and the epilogue's residual go out before
-  // the staging below waits on its own loads
   WBuf w0, w1;
-  load_w(w0, 0);
-  if (npass > 1) load_w(w1, 1);
-  const int em = tid / kDecCols, en = blockIdx.x * kDecCols + tid % kDecCols;  // epilogue element
-  const bool eval = tid < M * kDecCols && en < N;
-  float resid = 0.f;
-  if (ACT == kDecActNone && g.R && eval)
-    resid = static_cast<float>(static_cast<const bf16*>(g.R)[static_cast<int64_t>(em) * g.ldr + en]);
+  load_w(w0, blockIdx.x);
+  if (kBoth) load_w(w1, blockIdx.x + gridDim.x);
+  const int em = tid / kDecCols, c = tid % kDecCols;  // the thread's output element of a tile
+  const bool erow = em < M;
+  uint16_t r0 = 0, r1 = 0;  // its residual, of the two tiles in hand
+  if (ACT == kDecActNone) {
+    r0 = dec_resid(g, em, blockIdx.x * kDecCols + c);
+    r1 = dec_resid(g, em, (blockIdx.x + gridDim.x) * kDecCols + c);
+  }
 
-  // stage the rows of A (normalised when a gain is given), zero rows past M
-  const int k8n = K >> 3, p8 = pitch >> 3;
-  for (int m = wave; m < kDecGemmMaxM; m += NW) {
-    bf16* dst = as + m * pitch;
-    if (m >= M) {
-      for (int k8 = lane; k8 < p8; k8 += 64) *reinterpret_cast<bf16x8*>(dst + 8 * k8) = zero8();
-      continue;
+  // this wave's activations in operand layout (rows past M repeat the last)
+  bf16x8 x[CPW][MB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const bf16* xr = static_cast<const bf16*>(g.A) + static_cast<int64_t>(min(mb * 8 + (lane & 7), M - 1)) * g.lda;
+#pragma unroll
+    for (int u = 0; u < CPW; ++u) {
+      const int k = (wave + NW * u) * 64 + lk;
+      x[u][mb] = load8(xr + (k < K ? k : 0));
     }
-    const bf16* x = A + static_cast<int64_t>(m) * g.lda;
-    if constexpr (NORM) {
-      constexpr int NCH = kDecGemmMaxKNorm / 512;
-      bf16x8 xv[NCH];
+  }
+#pragma unroll
+  for (int u = 0; u < CPW; ++u)
+    if ((wave + NW * u) * 64 + 64 > K) {  // wave-uniform
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) dec_mask(x[u][mb], (wave + NW * u) * 64 + lk < K);
+    }
+  if constexpr (NORM) {
+    if (8 * tid < NW * CPW * 64)
+      *reinterpret_cast<bf16x8*>(gs + 8 * tid) =
+          8 * tid < K ? load8(static_cast<const bf16*>(g.g) + 8 * tid) : zero8();
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
       float ss = 0.f;
 #pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const int k8 = c * 64 + lane;
-        if (k8 < k8n) {
-          xv[c] = load8(x + 8 * k8);
+      for (int u = 0; u < CPW; ++u)
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float f = static_cast<float>(xv[c][e]);
-            ss = __builtin_fmaf(f, f, ss);
-          }
+        for (int i = 0; i < 8; ++i) {
+          const float f = static_cast<float>(x[u][mb][i]);
+          ss = __builtin_fmaf(f, f, ss);
         }
-      }
 #pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
-      const float rstd = rsqrtf(ss / static_cast<float>(K) + g.eps);
-      const bf16* gain = static_cast<const bf16*>(g.g);
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const int k8 = c * 64 + lane;
-        if (k8 < k8n) {
-          const bf16x8 gv = load8(gain + 8 * k8);
-          bf16x8 o;
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            o[e] = static_cast<bf16>(static_cast<float>(xv[c][e]) * rstd * static_cast<float>(gv[e]));
-          *reinterpret_cast<bf16x8*>(dst + 8 * k8) = o;
-        }
-      }
-    } else {
-      for (int k8 = lane; k8 < k8n; k8 += 64) *reinterpret_cast<bf16x8*>(dst + 8 * k8) = load8(x + 8 * k8);
+      for (int o = 8; o < 64; o <<= 1) ss += __shfl_xor(ss, o, 64);
+      if (lane < 8) ssq[wave][mb * 8 + lane] = ss;
     }
-    for (int k8 = k8n + lane; k8 < p8; k8 += 64) *reinterpret_cast<bf16x8*>(dst + 8 * k8) = zero8();
-  }
-  __syncthreads();
-
-  float acc[NR][kDecGemmMaxM];
+    __syncthreads();
+    float rstd[MB];
 #pragma unroll
-  for (int j = 0; j < NR; ++j)
+    for (int mb = 0; mb < MB; ++mb) {
+      float tot = 0.f;
 #pragma unroll
-    for (int m = 0; m < kDecGemmMaxM; ++m) acc[j][m] = 0.f;
-  auto dots = [&](const WBuf& wb, int p) {
-#pragma unroll
-    for (int u = 0; u < kDecU; ++u) {
-      const int c = wave + NW * (kDecU * p + u);
-      if (c < nchunks) {  // wave-uniform
-        const bf16* ak = as + c * 64 + 8 * t;
-#pragma unroll
-        for (int m = 0; m < kDecGemmMaxM; ++m) {
-          const bf16x8 a = *reinterpret_cast<const bf16x8*>(ak + m * pitch);
-#pragma unroll
-          for (int j = 0; j < NR; ++j) acc[j][m] = dot8(wb[u][j], a, acc[j][m]);
-        }
-      }
+      for (int w = 0; w < NW; ++w) tot += ssq[w][mb * 8 + (lane & 7)];
+      rstd[mb] = rsqrtf(tot / static_cast<float>(K) + g.eps);
     }
-  };
-  for (int p = 0; p < npass; p += 2) {
-    dots(w0, p);
-    if (p + 2 < npass) load_w(w0, p + 2);
-    if (p + 1 < npass) {
-      dots(w1, p + 1);
-      if (p + 3 < npass) load_w(w1, p + 3);
+#pragma unroll
+    for (int u = 0; u < CPW; ++u) {
+      const bf16x8 gv = load8(gs + (wave + NW * u) * 64 + lk);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        // opaque here, or the float32 values squared above are kept for this
+        int4v xi = __builtin_bit_cast(int4v, x[u][mb]);
+        asm volatile("" : "+v"(xi));
+        const bf16x8 xv = __builtin_bit_cast(bf16x8, xi);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          x[u][mb][i] = static_cast<bf16>(static_cast<float>(xv[i]) * rstd[mb] * static_cast<float>(gv[i]));
+      }
+      __builtin_amdgcn_sched_barrier(0);  // a chunk at a time: all chunks' gains at once would spill
     }
   }
+  if (kTwo && !kBoth) load_w(w1, blockIdx.x + gridDim.x);
 
-  // sums over the 8 lanes of a row, then over the waves in wave order
-#pragma unroll
-  for (int j = 0; j < NR; ++j)
-#pragma unroll
-    for (int m = 0; m < kDecGemmMaxM; ++m) {
-      float v = acc[j][m];
-      v += __shfl_xor(v, 1, 8);
-      v += __shfl_xor(v, 2, 8);
-      v += __shfl_xor(v, 4, 8);
-      acc[j][m] = v;
-    }
-  if (t == 0)
+  // one tile: products, the request of the buffer's next tile, the waves' sums
+  // into red[buf], and after the barrier the outputs (the other buffer's
+  // readers are past the barrier before it is written again)
+  auto do_tile = [&](WBuf& wb, int tile, int next, int buf, uint16_t& resid) {
+    floatx4 acc[NR][MB];
 #pragma unroll
     for (int j = 0; j < NR; ++j)
 #pragma unroll
-      for (int m = 0; m < kDecGemmMaxM; ++m) red[((wave * NR + j) * kDecCols + r) * kDecGemmMaxM + m] = acc[j][m];
-  __syncthreads();
-  constexpr int kVals = NR * kDecCols * kDecGemmMaxM;
-  if (tid < kVals) {
-    float sum = 0.f;
-    for (int w = 0; w < NW; ++w) sum += red[w * kVals + tid];
-    fin[tid] = sum;  // [j][column][row]
-  }
-  __syncthreads();
-  if (eval) {
-    const int c = tid % kDecCols;
-    bf16* C = static_cast<bf16*>(g.C) + static_cast<int64_t>(em) * g.ldc + en;
-    const float s0 = fin[c * kDecGemmMaxM + em];
-    if constexpr (ACT == kDecActSwiglu) {
-      const float u = bf16r(g.alpha * s0), v = bf16r(g.alpha * fin[(kDecCols + c) * kDecGemmMaxM + em]);
-      *C = static_cast<bf16>(swiglu_fwd_f(u, v));
-    } else if constexpr (ACT == kDecActRelu2) {
-      const float z = fmaxf(bf16r(g.alpha * s0), 0.f);
-      *C = static_cast<bf16>(z * z);
-    } else {
-      const bf16 o = static_cast<bf16>(g.alpha * s0 + resid);
-      *C = o;
-      if (g.kv && en >= g.kv_d) {
-        const int64_t b = em / g.kv_n, jj = em % g.kv_n;
-        static_cast<bf16*>(g.kv)[(b * g.kv_s_max + g.kv_pos + jj) * 2 * g.kv_d + (en - g.kv_d)] = o;
+      for (int mb = 0; mb < MB; ++mb) acc[j][mb] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < CPW; ++u) {
+      if ((wave + NW * u) * 64 + 64 > K) {  // wave-uniform: x is zero there, and W must not be inf or NaN
+#pragma unroll
+        for (int j = 0; j < NR; ++j) dec_mask(wb[u][j], (wave + NW * u) * 64 + lk < K);
       }
+#pragma unroll
+      for (int j = 0; j < NR; ++j)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+          acc[j][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb[u][j], x[u][mb], acc[j][mb], 0, 0, 0);
     }
+    const uint16_t r = resid;
+    if (next < tiles) {
+      load_w(wb, next);
+      if (ACT == kDecActNone) resid = dec_resid(g, em, next * kDecCols + c);
+    }
+    dec_put<MB, NR>(red[buf] + wave * dec_red_floats<MB, NR>(), acc, lane);
+    __syncthreads();
+    const int en = tile * kDecCols + c;
+    if (erow && en < N) dec_finish<MB, ACT, NW>(g, red[buf], em, c, en, r);
+  };
+  const int step = gridDim.x;
+  if constexpr (kTwo) {
+    for (int tile = blockIdx.x; tile < tiles; tile += 2 * step) {
+      do_tile(w0, tile, tile + 2 * step, 0, r0);
+      if (tile + step < tiles) do_tile(w1, tile + step, tile + 3 * step, 1, r1);
+    }
+  } else {
+    int buf = 0;
+    for (int tile = blockIdx.x; tile < tiles; tile += step, buf ^= 1) do_tile(w0, tile, tile + step, buf, r0);
   }
+}
+
+// Any K: weights and activations streamed in passes of U chunks per wave, the
+// next pass's loads in flight while one is used.  One tile per workgroup.
+template <int MB, int ACT, int NW, int U>
+__global__ __launch_bounds__(NW * 64) void ld_gemm_bf16_dec_long(SkinnyArgs g) {
+  constexpr int NR = ACT == kDecActSwiglu ? 2 : 1;
+  static_assert(NW * 64 >= MB * 8 * kDecCols, "a thread per output element");
+  __shared__ __align__(16) float red[NW * dec_red_floats<MB, NR>()];
+  const int M = g.M, N = g.N, K = g.K;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lk = 32 * ((lane >> 3) & 1) + 8 * (lane >> 4);
+  const int col = min(blockIdx.x * kDecCols + (lane & 7), N - 1);  // columns past N repeat the last
+  const bf16 *wrow[NR], *xrow[MB];
+#pragma unroll
+  for (int j = 0; j < NR; ++j) wrow[j] = static_cast<const bf16*>(g.W) + static_cast<int64_t>(col + j * N) * g.ldw;
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+    xrow[mb] = static_cast<const bf16*>(g.A) + static_cast<int64_t>(min(mb * 8 + (lane & 7), M - 1)) * g.lda;
+  struct Pass {
+    bf16x8 w[U][NR], x[U][MB];
+  };
+  // Chunks c0, c0 + NW, ...; k past K reads the row's start (no branch around
+  // a load, where the compiler would wait), and `use` drops it.
+  auto load = [&](Pass& p, int c0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int kc = (c0 + NW * u) * 64, k = kc + lk < K ? kc + lk : 0;
+#pragma unroll
+      for (int j = 0; j < NR; ++j) p.w[u][j] = load8(wrow[j] + k);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) p.x[u][mb] = load8(xrow[mb] + k);
+    }
+  };
+  floatx4 acc[NR][MB];
+#pragma unroll
+  for (int j = 0; j < NR; ++j)
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) acc[j][mb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto use = [&](Pass& p, int c0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int kc = (c0 + NW * u) * 64;
+      if (kc + 64 > K) {  // wave-uniform
+#pragma unroll
+        for (int j = 0; j < NR; ++j) dec_mask(p.w[u][j], kc + lk < K);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) dec_mask(p.x[u][mb], kc + lk < K);
+      }
+#pragma unroll
+      for (int j = 0; j < NR; ++j)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+          acc[j][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p.w[u][j], p.x[u][mb], acc[j][mb], 0, 0, 0);
+    }
+  };
+  const int nchunks = (K + 63) >> 6;
+  Pass p0, p1;
+  load(p0, wave);
+  load(p1, wave + U * NW);
+  const int em = tid / kDecCols, c = tid % kDecCols, en = blockIdx.x * kDecCols + c;
+  const bool eval = em < M && en < N;
+  uint16_t resid = 0;
+  if (ACT == kDecActNone) resid = dec_resid(g, em, en);
+  for (int c0 = wave; c0 < nchunks; c0 += 2 * U * NW) {
+    use(p0, c0);
+    if (c0 + 2 * U * NW < nchunks) load(p0, c0 + 2 * U * NW);
+    use(p1, c0 + U * NW);
+    if (c0 + 3 * U * NW < nchunks) load(p1, c0 + 3 * U * NW);
+  }
+  dec_put<MB, NR>(red + wave * dec_red_floats<MB, NR>(), acc, lane);
+  __syncthreads();
+  if (eval) dec_finish<MB, ACT, NW>(g, red, em, c, en, resid);
 }
 
 // ------------------------------------------------------------ KV store
@@ -653,60 +710,67 @@ hipError_t launch_gemm_skinny(const SkinnyArgs& g, int ksplit, hipStream_t s) {
   else
     hipLaunchKernelGGL(ld_gemm_bf16_skinny<2>, grid, dim3(256), 0, s, g);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || ksplit == 1 || g.part_only) return e;
+  if (e != hipSuccess || ksplit == 1) return e;
   hipLaunchKernelGGL(ld_skinny_reduce_k, dim3(grid_for(static_cast<int64_t>(g.M) * g.N)), dim3(256), 0,
                      s, g, ksplit);
   return hipGetLastError();
 }
 
-size_t dec_gemm_lds_bytes(int64_t K, int nw) {
-  return static_cast<size_t>(kDecGemmMaxM) * dec_pitch(K) * 2 +
-         static_cast<size_t>(nw + 1) * 2 * kDecCols * kDecGemmMaxM * 4;
+bool dec_gemm_fuses_norm(int64_t M, int64_t K) {
+  return M >= 1 && ((M <= 48 && K <= 2048) || (M <= 16 && K <= 4096));
 }
 
-bool dec_gemm_ok(int64_t M, int64_t K, bool norm) {
-  return M >= 1 && M <= kDecGemmMaxM && K >= 8 && K % 8 == 0 && (!norm || K <= kDecGemmMaxKNorm) &&
-         dec_gemm_lds_bytes(K, 16) <= 160 * 1024;
-}
-
-template <int NW, int ACT>
-hipError_t gemm_dec_t(const SkinnyArgs& g, int tiles, hipStream_t s) {
-  const size_t lds = dec_gemm_lds_bytes(g.K, NW);
-  if (g.g)
-    hipLaunchKernelGGL((ld_gemm_bf16_dec<NW, ACT, true>), dim3(tiles), dim3(NW * 64), lds, s, g);
-  else
-    hipLaunchKernelGGL((ld_gemm_bf16_dec<NW, ACT, false>), dim3(tiles), dim3(NW * 64), lds, s, g);
+// Rows of the tiles' weights in flight per CU, and the activations' registers,
+// set the variant: eight waves with the activations of K <= 2048 (4 chunks
+// each) for up to 48 rows, of K <= 4096 (8 chunks) for up to 16, beyond which
+// they would spill, one workgroup per CU, each CU taking the same number of
+// tiles; else streamed activations, 16 waves while their registers allow.
+template <int MB, int ACT>
+hipError_t gemm_dec_t(const SkinnyArgs& g, hipStream_t s) {
+  const int tiles = (g.N + kDecCols - 1) / kDecCols;
+  if (dec_gemm_fuses_norm(g.M, g.K)) {
+    const int rounds = (tiles + kDecCus - 1) / kDecCus, grid = (tiles + rounds - 1) / rounds;
+    const dim3 block(512);
+    if (g.K <= 2048) {
+      if constexpr (MB <= 6) {
+        if (g.g)
+          hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, true, 8, 4>), dim3(grid), block, 0, s, g);
+        else
+          hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, false, 8, 4>), dim3(grid), block, 0, s, g);
+      }
+    } else {
+      if constexpr (MB <= 2) {
+        if (g.g)
+          hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, true, 8, 8>), dim3(grid), block, 0, s, g);
+        else
+          hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, false, 8, 8>), dim3(grid), block, 0, s, g);
+      }
+    }
+  } else {
+    if (g.g) return hipErrorInvalidValue;
+    constexpr int NW = MB <= 3 ? 16 : 8, U = MB <= 2 && ACT != kDecActSwiglu ? 4 : 2;
+    hipLaunchKernelGGL((ld_gemm_bf16_dec_long<MB, ACT, NW, U>), dim3(tiles), dim3(NW * 64), 0, s, g);
+  }
   return hipGetLastError();
+}
+
+template <int MB>
+hipError_t gemm_dec_act(const SkinnyArgs& g, hipStream_t s) {
+  if (g.act == kDecActSwiglu) return gemm_dec_t<MB, kDecActSwiglu>(g, s);
+  if (g.act == kDecActRelu2) return gemm_dec_t<MB, kDecActRelu2>(g, s);
+  return gemm_dec_t<MB, kDecActNone>(g, s);
 }
 
 hipError_t launch_gemm_dec(const SkinnyArgs& g, hipStream_t s) {
   if (g.N <= 0) return hipSuccess;
-  if (!dec_gemm_ok(g.M, g.K, g.g != nullptr)) return hipErrorInvalidValue;
-  const int tiles = (g.N + kDecCols - 1) / kDecCols;
-  // One workgroup per tile, all resident at once: while the tiles fit one
-  // per CU, 16 waves (8 with SwiGLU, whose two rows per lane need more than
-  // the 128 registers of 16 waves), else 4 (up to four workgroups per CU);
-  // either way every wave's loads are issued up front.
-  if (g.act == kDecActSwiglu)
-    return tiles <= kDecCus ? gemm_dec_t<8, kDecActSwiglu>(g, tiles, s) : gemm_dec_t<4, kDecActSwiglu>(g, tiles, s);
-  if (g.act == kDecActRelu2)
-    return tiles <= kDecCus ? gemm_dec_t<16, kDecActRelu2>(g, tiles, s) : gemm_dec_t<4, kDecActRelu2>(g, tiles, s);
-  return tiles <= kDecCus ? gemm_dec_t<16, kDecActNone>(g, tiles, s) : gemm_dec_t<4, kDecActNone>(g, tiles, s);
-}
-
-hipError_t launch_skinny_reduce_norm(const SkinnyArgs& g, int ksplit, const void* gain, float eps, void* h,
-                                     hipStream_t s) {
-  if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  hipLaunchKernelGGL(ld_skinny_reduce_norm_k, dim3(g.M), dim3(1024), 0, s, g, ksplit, static_cast<const bf16*>(gain),
-                     eps, static_cast<bf16*>(h));
-  return hipGetLastError();
-}
-
-hipError_t launch_skinny_reduce_act(const SkinnyArgs& g, int ksplit, int act, int f, void* s_out, hipStream_t s) {
-  if (g.M <= 0 || f <= 0) return hipSuccess;
-  hipLaunchKernelGGL(ld_skinny_reduce_act_k, dim3(grid_for(static_cast<int64_t>(g.M) * f)), dim3(256), 0, s, g,
-                     ksplit, act, f, static_cast<bf16*>(s_out));
-  return hipGetLastError();
+  if (g.M < 1 || g.M > kSkinnyMaxM || g.K < 8 || g.K % 8) return hipErrorInvalidValue;
+  const int mb = (g.M + 7) / 8;  // blocks of 8 rows
+  return mb <= 1   ? gemm_dec_act<1>(g, s)
+         : mb <= 2 ? gemm_dec_act<2>(g, s)
+         : mb <= 3 ? gemm_dec_act<3>(g, s)
+         : mb <= 4 ? gemm_dec_act<4>(g, s)
+         : mb <= 6 ? gemm_dec_act<6>(g, s)
+                   : gemm_dec_act<8>(g, s);
 }
 
 hipError_t launch_kv_store(const KvArgs& a, hipStream_t s) {

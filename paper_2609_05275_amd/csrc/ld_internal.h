@@ -290,8 +290,7 @@ struct SkinnyArgs {
   int64_t lda, ldw, ldc, ldr;
   int32_t M, N, K;
   float alpha;
-  float* part;        // float32 [ksplit][M][N] when ksplit > 1 or part_only
-  int32_t part_only;  // write the partials even with ksplit == 1 (a fused reduction follows)
+  float* part;        // float32 [ksplit][M][N] when ksplit > 1
   // optional: columns kv_d.. of row m also go to the cache kv [*, s_max, 2 kv_d]
   // at position kv_pos + m % kv_n of sequence m / kv_n (the keys/values of a
   // qkv projection)
@@ -306,16 +305,13 @@ struct SkinnyArgs {
 };
 constexpr int kSkinnyMaxM = 64;
 
-// Fused decode projection (at most 8 rows): one workgroup per 8 output
-// columns and the whole k range, A rows staged in LDS (normalised on the
-// way when g is set); no split-K partials and no separate norm or
-// activation launch.
-constexpr int kDecGemmMaxM = 8;
-constexpr int kDecGemmMaxKNorm = 4096;
+// Fused decode projection (at most kSkinnyMaxM rows): one workgroup per tile
+// of 8 output columns and the whole k range, so no split-K partials and no
+// separate activation launch; nor a norm launch where dec_gemm_fuses_norm.
 constexpr int kDecActNone = 0, kDecActSwiglu = 1, kDecActRelu2 = 2;
-// LDS bytes the fused projection needs for K (0 when it does not fit).
-size_t dec_gemm_lds_bytes(int64_t K, int nw);
-bool dec_gemm_ok(int64_t M, int64_t K, bool norm);
+// Whether launch_gemm_dec applies the RMSNorm gain g itself for these sizes
+// (it must be null otherwise).
+bool dec_gemm_fuses_norm(int64_t M, int64_t K);
 hipError_t launch_gemm_dec(const SkinnyArgs& g, hipStream_t s);
 
 // Copy of the key/value columns of qkv rows into a cache [n_seq, s_max, 2d]
@@ -366,13 +362,6 @@ hipError_t launch_masks(const MaskArgs& a, hipStream_t s);
 hipError_t launch_zero_f32(const ZeroArgs& a, hipStream_t s);
 int skinny_ksplit(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemm_skinny(const SkinnyArgs& g, int ksplit, hipStream_t s);
-// Fused reductions of a skinny GEMM's partials (g.part_only launches):
-// C = bf16(alpha sum + R) and h = RMSNorm(C rows) with gain `gain`; or the
-// FFN activation s = act(bf16(alpha sum)) of f columns (SwiGLU pairs
-// columns n and f + n).
-hipError_t launch_skinny_reduce_norm(const SkinnyArgs& g, int ksplit, const void* gain, float eps, void* h,
-                                     hipStream_t s);
-hipError_t launch_skinny_reduce_act(const SkinnyArgs& g, int ksplit, int act, int f, void* s_out, hipStream_t s);
 hipError_t launch_kv_store(const KvArgs& a, hipStream_t s);
 hipError_t launch_attn_decode(const DecAttnArgs& a, hipStream_t s);
 hipError_t launch_gather(int dtype, const RowsArgs& a, hipStream_t s);

@@ -291,6 +291,19 @@ def test_decode_across_key_chunks(sh):
     _decode_case(sh, steps, s_max=64 + 8 * 26)
 
 
+@pytest.mark.parametrize("d,H,f,batch,n", [
+    (256, 2, 2120, 2, 8), (256, 2, 2120, 3, 7), (256, 2, 2120, 5, 6), (256, 2, 2120, 6, 8), (256, 2, 2120, 7, 7),
+    (256, 2, 2120, 8, 8), (2304, 18, 264, 2, 8), (2304, 18, 264, 3, 6), (2304, 18, 264, 8, 8)])
+@pytest.mark.parametrize("kind", [0, 1])
+def test_decode_projection_variants(d, H, f, batch, n, kind):
+    """Every row-block variant of the fused projections (16 to 64 rows): the
+    activations kept in registers (K <= 2048, or 4096 up to 16 rows) or
+    streamed (a d_ff of 2120 ends in a chunk of 8), the RMSNorm fused or
+    before them (d = 2304 beyond 16 rows, any d beyond 48)."""
+    sh = inp.Shape(1, d, H, f, 64, batch, "bf16", kind)
+    _decode_case(sh, [(n, None)], s_max=64 + n)
+
+
 def test_decode_more_rows_than_the_skinny_kernel():
     """batch 9 x 8 rows = 72 > 64: the projections take the general GEMM."""
     _decode_case(SMALL_BF16, [(8, None), (1, None)], s_max=128, batch=9)
