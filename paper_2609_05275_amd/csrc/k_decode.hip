@@ -20,7 +20,7 @@
 // wave per 64 keys.  Scores in base 2 with the causal cut (key <= query
 // position) and the ALiBi bias: for one query row, dh/8 lanes per key, each
 // with 8 of the head's dimensions, summed by lane exchanges; for several
-// rows, S^T = K Q^T on the matrix cores (the rows padded to 32 columns).
+// rows, S^T = K Q^T on the matrix cores (the rows padded to 16 columns).
 // Softmax statistics per query row over the chunk, then P V with dh/8 lanes
 // per key (16-byte coalesced value reads), summed over the wave's keys by
 // lane exchanges and over the four waves in LDS.  A combine kernel merges
@@ -539,45 +539,51 @@ __global__ __launch_bounds__(256) void ld_attn_decode_bf16(DecAttnArgs a) {
       if (sl == 0) sc[0][kl] = (kk < nk && kk <= a.pos) ? s - al2 * static_cast<float>(a.pos - kk) : -INFINITY;
     }
   } else {
-    // several query rows: S^T = K Q^T on the matrix cores, the wave's 64 keys
-    // in two 32-key blocks (A operand: lane l holds key l % 32, dimensions
-    // 16 ks + 8 (l / 32) .. +7), the query rows as the 32 columns (B operand;
-    // rows past n_new are zero).  Lane l, register v of block kb then holds
-    // key 32 kb + 8 (v / 4) + 4 (l / 32) + v % 4 of query row l % 32.
-    const int ql = lane & 31, hf = lane >> 5;
-    bf16x8 qf[DH / 16], kf[2][DH / 16];
+    // several query rows: S^T = K Q^T on the matrix cores (16x16x32), 8 keys a
+    // time.  Lane l loads 16 bytes of key l % 8 at dimension 64 s + 32 ((l / 8)
+    // % 2) + 8 (l / 16), so an instruction takes 8 whole 128-byte lines (32
+    // keys of 32 bytes each took four times as long to issue: the load cost
+    // goes by the lines touched).  As A operand its lanes hold the keys twice,
+    // rows 0-7 with dimensions 0-31 of the 64 and rows 8-15 with 32-63, so
+    // each load feeds two products, against the query rows' (B operand, row
+    // l % 16, zero past n_new) first and last 32 dimensions; the two rows of a
+    // key are added.
+    const int qm = lane & 15, qg = lane >> 4;
+    bf16x8 qf[DH / 64][2], kf[8][DH / 64];
 #pragma unroll
-    for (int ks = 0; ks < DH / 16; ++ks)
-      qf[ks] = ql < a.n_new ? load8(qkv + (static_cast<int64_t>(b) * a.n_new + ql) * a.ld_qkv + h * DH + 16 * ks + 8 * hf)
-                            : zero8();
+    for (int s = 0; s < DH / 64; ++s)
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      const int kk = k0 + kb * 32 + ql;
-      const bf16* kp = cache + static_cast<int64_t>(kk < nk ? kk : 0) * row2 + h * DH + 8 * hf;
+      for (int e = 0; e < 2; ++e)
+        qf[s][e] = qm < a.n_new ? load8(qkv + (static_cast<int64_t>(b) * a.n_new + qm) * a.ld_qkv + h * DH + 64 * s +
+                                        32 * e + 8 * qg)
+                                : zero8();
 #pragma unroll
-      for (int ks = 0; ks < DH / 16; ++ks) kf[kb][ks] = load8(kp + 16 * ks);
+    for (int kb = 0; kb < 8; ++kb) {
+      const int kk = k0 + kb * 8 + (lane & 7);
+      const bf16* kp = cache + static_cast<int64_t>(kk < nk ? kk : 0) * row2 + h * DH + 32 * ((lane >> 3) & 1) + 8 * qg;
+#pragma unroll
+      for (int s = 0; s < DH / 64; ++s) kf[kb][s] = load8(kp + 64 * s);
     }
-    floatx16 acc[2];
+    const int qpos = a.pos + qm;
+    const float sl2 = a.scale * kLog2e;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    for (int kb = 0; kb < 8; ++kb) {
+      floatx4 s0{0.f, 0.f, 0.f, 0.f}, s1{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[kb][v] = 0.f;
+      for (int s = 0; s < DH / 64; ++s) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][s], qf[s][0], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][s], qf[s][1], s1, 0, 0, 0);
+      }
 #pragma unroll
-      for (int ks = 0; ks < DH / 16; ++ks)
-        acc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb][ks], qf[ks], acc[kb], 0, 0, 0);
-    }
-    if (ql < a.n_new) {
-      const int qpos = a.pos + ql;
-      const float sl2 = a.scale * kLog2e;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int kl = 32 * kb + 8 * (v >> 2) + 4 * hf + (v & 3);
-          const int kk = k0 + kl;
-          sc[ql][wave * 64 + kl] =
-              (kk < nk && kk <= qpos) ? acc[kb][v] * sl2 - al2 * static_cast<float>(qpos - kk) : -INFINITY;
-        }
+      for (int v = 0; v < 4; ++v) {  // lane groups 0, 1: keys 4 qg + v of s0; 2, 3: of s1
+        const float lo = s0[v], hi = s1[v];
+        float t = qg < 2 ? lo : hi;
+        t += __shfl_xor(t, 32, 64);
+        const int kl = kb * 8 + 4 * qg + v, kk = k0 + kl;
+        if (qg < 2 && qm < a.n_new)
+          sc[qm][wave * 64 + kl] =
+              (kk < nk && kk <= qpos) ? t * sl2 - al2 * static_cast<float>(qpos - kk) : -INFINITY;
+      }
     }
   }
   // values of the same positions, in flight during the softmax
