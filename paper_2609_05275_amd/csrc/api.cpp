@@ -350,7 +350,7 @@ GemmArgs gemm_args() {
 int run_gemm(int dtype, int a_k, int b_k, GemmArgs g, int64_t max_m, int64_t host_m,
              int64_t host_k, hipStream_t s, float* part = nullptr, size_t part_bytes = 0,
              int64_t max_k = 0) {
-  const GemmPlan plan = plan_gemm(dtype, a_k, b_k, g, max_m, max_k, part != nullptr);
+  const GemmPlan plan = plan_gemm(dtype, a_k, b_k, g, max_m, max_k, part != nullptr, host_m);
   if (plan.splits > 1) {
     if (gemm_part_bytes(plan, g.M, g.N) > part_bytes) return fail(LD_E_WORKSPACE, "split-K scratch too small");
     g.part = part;
@@ -615,9 +615,11 @@ int ffn_forward_part(const ld_config* cfg, const Dims& D, const ld_weights& w, c
     if (D.kind == LD_BLOCK_SWIGLU && dt == LD_BF16 && D.f % 128 == 0 && plan_gemm(dt, 1, 1, g, T, 0, false).big) {
       g.aux = act.at(act.L.s);
       g.glu_f = static_cast<int32_t>(D.f);
-      ProfScope ps("ld_gemm_bf16_nt_glu_256", s);
-      if ((e = launch_gemm_glu_fwd(g, T, s)) != hipSuccess)
-        return fail(LD_E_HIP, "ld_gemm_bf16_nt_glu_256 launch: %s", hipGetErrorString(e));
+      const int bm = plan_rows(hm > 0 ? hm : T, g.N);
+      const char* name = bm == 128 ? "ld_gemm_bf16_nt_glu_128" : "ld_gemm_bf16_nt_glu_256";
+      ProfScope ps(name, s);
+      if ((e = launch_gemm_glu_fwd(g, T, bm, s)) != hipSuccess)
+        return fail(LD_E_HIP, "%s launch: %s", name, hipGetErrorString(e));
       ps.end(2.0 * hm * D.fw * D.d, D.es * (hm * D.d + D.fw * D.d + hm * D.fw + hm * D.f));
       goto down_projection;
     }
@@ -626,9 +628,11 @@ int ffn_forward_part(const ld_config* cfg, const Dims& D, const ld_weights& w, c
       g.aux = act.at(act.L.s);
       g.glu_f = static_cast<int32_t>(D.f);
       g.relu2 = 1;
-      ProfScope ps("ld_gemm_bf16_nt_relu2_256", s);
-      if ((e = launch_gemm_relu2_fwd(g, T, s)) != hipSuccess)
-        return fail(LD_E_HIP, "ld_gemm_bf16_nt_relu2_256 launch: %s", hipGetErrorString(e));
+      const int bm = plan_rows(hm > 0 ? hm : T, g.N);
+      const char* name = bm == 128 ? "ld_gemm_bf16_nt_relu2_128" : "ld_gemm_bf16_nt_relu2_256";
+      ProfScope ps(name, s);
+      if ((e = launch_gemm_relu2_fwd(g, T, bm, s)) != hipSuccess)
+        return fail(LD_E_HIP, "%s launch: %s", name, hipGetErrorString(e));
       ps.end(2.0 * hm * D.fw * D.d, D.es * (hm * D.d + D.fw * D.d + 2.0 * hm * D.f));
       goto down_projection;
     }

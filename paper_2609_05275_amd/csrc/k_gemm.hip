@@ -347,17 +347,30 @@ constexpr size_t kGemmLds = 4 * kTileElems * sizeof(bf16);
 
 constexpr int GB = 256, GK = 64;
 constexpr int kBigThreads = 512;        // eight waves
-constexpr int kSlot = GB * GK;          // elements of one operand's k step
-constexpr int kLoads = 4;               // load instructions per wave per slot
-constexpr int kSlotsA = 3, kSlotsB = 2;
+constexpr int kSlot = GB * GK;          // elements of a k step of 256 rows or columns
+constexpr int kLoads = 4;               // load instructions per wave per 256-row slot
 constexpr int kWaitVm0 = 0x0F70;        // s_waitcnt vmcnt(0), the other counters untouched
-constexpr int kRingElems = (kSlotsA + kSlotsB) * kSlot;
-constexpr int kStagePitch = 132;        // floats per staged epilogue row (128 + 4 pad)
-constexpr int kStagePitch16 = 132;      // bf16 per staged row of a bf16 epilogue (264 bytes)
+constexpr int kRingElems = 5 * kSlot;   // 160 KB
 constexpr uint32_t kOob = kDmaOob;
 constexpr int64_t kBigMaxSpan = kDmaMaxSpan;
 static_assert(kRingElems * 2 <= 160 * 1024, "the ring fits the LDS");
-static_assert(kRingElems * 2 >= 8 * 32 * kStagePitch * 4, "epilogue staging fits the ring");
+
+// The tile of BM rows (256 or 128) x 256 columns and its waves' parts: eight
+// waves in a (BM / 64) x NWN grid, each 64 rows x WC columns.  Three slots of A
+// and NSB of B fit the ring.
+template <int BM>
+struct BigShape {
+  static constexpr int NWN = BM == 256 ? 2 : 4, WC = 256 / NWN;
+  static constexpr int NJ = WC / 16;               // 16-column blocks per wave
+  static constexpr int SlotA = BM * GK, LoadsA = kLoads * BM / 256;
+  static constexpr int NSA = 3, NSB = BM == 256 ? 2 : 3;
+  static constexpr int Elems = NSA * SlotA + NSB * kSlot;
+  // epilogue staging: WC + 4 elements per row; RPI rows per load or store of
+  // 4 floats per lane
+  static constexpr int Pitch = WC + 4, RPI = 256 / WC, NIT = 32 / RPI;
+};
+static_assert(BigShape<256>::Elems <= kRingElems && BigShape<128>::Elems <= kRingElems, "the slots fit the ring");
+static_assert(kRingElems * 2 >= 8 * 32 * BigShape<256>::Pitch * 4, "epilogue staging fits the ring");
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef dma_rsrc v4i;
@@ -440,15 +453,18 @@ __device__ __forceinline__ void tile_part(bf16* lds, const OpLanes<KC>& o, const
   (void)R;
 }
 
-// B slot of the fused SwiGLU forward: the slot's 64-row block p holds gate
-// rows (p even) or up rows (p odd) tn*128 + (p/2)*64 .. +63 of W_gate_up
-// [2f, K], so the slot holds [gate 0-63 | up 0-63 | gate 64-127 | up 64-127]
-// of its 128 d_ff columns and each wave's 128 rows pair every gate row with
-// its up row 64 further on.  Load instruction p fills rows 8 wave .. +7 of
-// block p.
+// B slot of the fused SwiGLU forward: each wave's WC columns pair WC / 2 gate
+// rows of W_gate_up [2f, K] with their up rows.  For WC = 128 the slot's 64-row
+// block p holds gate rows (p even) or up rows (p odd) tn*128 + (p/2)*64 .. +63;
+// for WC = 64 gate rows tn*128 + 32p .. +31, then the up rows.  Load
+// instruction p fills rows 8 wave .. +7 of block p.
+template <int WC>
 __device__ __forceinline__ void tile_part_glu(bf16* lds, const OpLanes<true>& o, const bf16* W, int64_t ld,
                                               int tn, int f, int k0, int K, int wave, int p) {
-  const int64_t rbase = ((p & 1) ? f : 0) + static_cast<int64_t>(tn) * 128 + (p >> 1) * 64;
+  // W row of the block's row 0 (the lane's offset adds 8 wave + lane / 8)
+  const int64_t rbase = WC == 128
+                            ? ((p & 1) ? f : 0) + static_cast<int64_t>(tn) * 128 + (p >> 1) * 64
+                            : (wave >= 4 ? f - 32 : 0) + static_cast<int64_t>(tn) * 128 + p * 32;
   const v4i rs = dma_make_rsrc(W + rbase * ld, 64 * ld * 2);
   const uint32_t off = k0 + o.kchunk < K ? o.ld_off + static_cast<uint32_t>(k0 * 2) : kOob;
   dma16(rs, lds + (p * 8 + wave) * 512, off);
@@ -498,16 +514,17 @@ __device__ __forceinline__ bool tile_coords(int pid, int tiles_m, int tiles_n, i
   return true;
 }
 
-// Epilogue of one staged 32-row block row: the lane's rows are r0 + 2 it
-// (it = 0..15), its 4 columns n..n+3; the staged values (alpha applied) sit
-// at stage[(2 it + half) * kStagePitch + c].
+// Epilogue of one staged 32-row block row: the lane's rows are r0 + RPI it
+// (it < NIT), its 4 columns n..n+3; the staged values (alpha applied) sit at
+// stage[(RPI it + sub) * Pitch + c], sub the lane's row of each RPI.
 //
 // Full block row (every row < M, every column < N): the staged values, row
 // map entries and residual values of half the rows are requested before their
 // first store, so their latencies overlap, and no branch splits the rows.
+template <class SH>
 __device__ __forceinline__ void epilogue_rows_full(const GemmArgs& g, float* part, const float* stage,
-                                                   int r0, int half, int c, int n, int q_last) {
-  constexpr int NR = 8;  // rows in hand (16 would spill next to the accumulators)
+                                                   int r0, int sub, int c, int n, int q_last) {
+  constexpr int NR = 8, RPI = SH::RPI;  // rows in hand (16 would spill next to the accumulators)
   // output row = idx[r / S] * S + r % S; for S >= 32 the 32 rows span at most
   // two sequences
   const int S = g.out_map.S;
@@ -521,25 +538,25 @@ __device__ __forceinline__ void epilogue_rows_full(const GemmArgs& g, float* par
     }
   }
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
+  for (int h = 0; h < SH::NIT / NR; ++h) {
     float4 v[NR];
 #pragma unroll
     for (int it = 0; it < NR; ++it)
-      v[it] = *reinterpret_cast<const float4*>(stage + (2 * (NR * h + it) + half) * kStagePitch + c);
+      v[it] = *reinterpret_cast<const float4*>(stage + (RPI * (NR * h + it) + sub) * SH::Pitch + c);
     if (part) {
 #pragma unroll
       for (int it = 0; it < NR; ++it)
-        *reinterpret_cast<float4*>(part + static_cast<int64_t>(r0 + 2 * (NR * h + it)) * g.N + n) = v[it];
+        *reinterpret_cast<float4*>(part + static_cast<int64_t>(r0 + RPI * (NR * h + it)) * g.N + n) = v[it];
       continue;
     }
     int32_t orow[NR];
 #pragma unroll
     for (int it = 0; it < NR; ++it) {
-      const int r = r0 + 2 * (NR * h + it);
+      const int r = r0 + RPI * (NR * h + it);
       orow[it] = r;
       if (g.out_map.idx) {
         if (S >= 32) {
-          const int rr = rem0 + 2 * (NR * h + it);
+          const int rr = rem0 + RPI * (NR * h + it);
           orow[it] = rr >= S ? s1 * S + (rr - S) : s0 * S + rr;
         } else {
           const int q = r / S;
@@ -552,7 +569,7 @@ __device__ __forceinline__ void epilogue_rows_full(const GemmArgs& g, float* par
       float4 rv[NR];
 #pragma unroll
       for (int it = 0; it < NR; ++it) {
-        const int64_t rrow = g.r_mapped ? orow[it] : r0 + 2 * (NR * h + it);
+        const int64_t rrow = g.r_mapped ? orow[it] : r0 + RPI * (NR * h + it);
         rv[it] = *reinterpret_cast<const float4*>(R + rrow * g.ldr + n);
       }
 #pragma unroll
@@ -567,7 +584,7 @@ __device__ __forceinline__ void epilogue_rows_full(const GemmArgs& g, float* par
       const bf16* R = static_cast<const bf16*>(g.R);
 #pragma unroll
       for (int it = 0; it < NR; ++it) {
-        const int64_t rrow = g.r_mapped ? orow[it] : r0 + 2 * (NR * h + it);
+        const int64_t rrow = g.r_mapped ? orow[it] : r0 + RPI * (NR * h + it);
         rv[it] = *reinterpret_cast<const uint2*>(R + rrow * g.ldr + n);
       }
 #pragma unroll
@@ -597,13 +614,14 @@ __device__ __forceinline__ void epilogue_rows_full(const GemmArgs& g, float* par
 
 // Block row with rows past M or columns past N: one row at a time, each
 // checked.
+template <class SH>
 __device__ __forceinline__ void epilogue_rows_edge(const GemmArgs& g, float* part, const float* stage,
-                                                   int r0, int half, int c, int n, int M) {
+                                                   int r0, int sub, int c, int n, int M) {
 #pragma unroll 1
-  for (int it = 0; it < 16; ++it) {
-    const int m = r0 + 2 * it;
+  for (int it = 0; it < SH::NIT; ++it) {
+    const int m = r0 + SH::RPI * it;
     if (m >= M || n >= g.N) continue;
-    float4 v = *reinterpret_cast<const float4*>(stage + (2 * it + half) * kStagePitch + c);
+    float4 v = *reinterpret_cast<const float4*>(stage + (SH::RPI * it + sub) * SH::Pitch + c);
     if (part) {
       *reinterpret_cast<float4*>(part + static_cast<int64_t>(m) * g.N + n) = v;
       continue;
@@ -660,33 +678,34 @@ __device__ __forceinline__ void glu_bwd_one(const GemmArgs& g, float4 gs, uint2 
   *reinterpret_cast<uint2*>(C + g.glu_f + n) = pack4_bf16(gv[0], gv[1], gv[2], gv[3]);
 }
 
-__device__ __forceinline__ void glu_bwd_rows(const GemmArgs& g, const float* stage, int r0, int half, int c, int n,
+template <class SH>
+__device__ __forceinline__ void glu_bwd_rows(const GemmArgs& g, const float* stage, int r0, int sub, int c, int n,
                                              int M, bool full) {
   const bf16* U = static_cast<const bf16*>(g.aux);
   const int64_t ldu = 2ll * g.glu_f;
   if (full) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < SH::NIT / 8; ++h) {
       uint2 ur[8], vr[8];
 #pragma unroll
       for (int it = 0; it < 8; ++it) {
-        const int64_t m = r0 + 2 * (8 * h + it);
+        const int64_t m = r0 + SH::RPI * (8 * h + it);
         ur[it] = *reinterpret_cast<const uint2*>(U + m * ldu + n);
         vr[it] = *reinterpret_cast<const uint2*>(U + m * ldu + g.glu_f + n);
       }
 #pragma unroll
       for (int it = 0; it < 8; ++it) {
-        const int r = 2 * (8 * h + it);
-        const float4 gs = *reinterpret_cast<const float4*>(stage + (r + half) * kStagePitch + c);
+        const int r = SH::RPI * (8 * h + it);
+        const float4 gs = *reinterpret_cast<const float4*>(stage + (r + sub) * SH::Pitch + c);
         glu_bwd_one(g, gs, ur[it], vr[it], r0 + r, n);
       }
     }
   } else {
 #pragma unroll 1
-    for (int it = 0; it < 16; ++it) {
-      const int64_t m = r0 + 2 * it;
+    for (int it = 0; it < SH::NIT; ++it) {
+      const int64_t m = r0 + SH::RPI * it;
       if (m >= M || n >= g.N) continue;
-      const float4 gs = *reinterpret_cast<const float4*>(stage + (2 * it + half) * kStagePitch + c);
+      const float4 gs = *reinterpret_cast<const float4*>(stage + (SH::RPI * it + sub) * SH::Pitch + c);
       glu_bwd_one(g, gs, *reinterpret_cast<const uint2*>(U + m * ldu + n),
                   *reinterpret_cast<const uint2*>(U + m * ldu + g.glu_f + n), m, n);
     }
@@ -708,18 +727,19 @@ __device__ __forceinline__ void relu2_fwd_one(const GemmArgs& g, float4 v, int64
   *reinterpret_cast<uint2*>(static_cast<bf16*>(g.aux) + m * g.glu_f + n) = pack4_bf16(q[0], q[1], q[2], q[3]);
 }
 
-__device__ __forceinline__ void relu2_fwd_rows(const GemmArgs& g, const float* stage, int r0, int half, int c,
+template <class SH>
+__device__ __forceinline__ void relu2_fwd_rows(const GemmArgs& g, const float* stage, int r0, int sub, int c,
                                                int n, int M, bool full) {
   if (full) {
 #pragma unroll
-    for (int it = 0; it < 16; ++it)
-      relu2_fwd_one(g, *reinterpret_cast<const float4*>(stage + (2 * it + half) * kStagePitch + c), r0 + 2 * it, n);
+    for (int it = 0; it < SH::NIT; ++it)
+      relu2_fwd_one(g, *reinterpret_cast<const float4*>(stage + (SH::RPI * it + sub) * SH::Pitch + c), r0 + SH::RPI * it, n);
   } else {
 #pragma unroll 1
-    for (int it = 0; it < 16; ++it) {
-      const int64_t m = r0 + 2 * it;
+    for (int it = 0; it < SH::NIT; ++it) {
+      const int64_t m = r0 + SH::RPI * it;
       if (m >= M || n >= g.N) continue;
-      relu2_fwd_one(g, *reinterpret_cast<const float4*>(stage + (2 * it + half) * kStagePitch + c), m, n);
+      relu2_fwd_one(g, *reinterpret_cast<const float4*>(stage + (SH::RPI * it + sub) * SH::Pitch + c), m, n);
     }
   }
 }
@@ -733,23 +753,24 @@ __device__ __forceinline__ void relu2_bwd_one(const GemmArgs& g, float4 gs, uint
                  gs.w * 2.f * fmaxf(u.w, 0.f));
 }
 
-__device__ __forceinline__ void relu2_bwd_rows(const GemmArgs& g, const float* stage, int r0, int half, int c,
+template <class SH>
+__device__ __forceinline__ void relu2_bwd_rows(const GemmArgs& g, const float* stage, int r0, int sub, int c,
                                                int n, int M, bool full) {
   const bf16* U = static_cast<const bf16*>(g.aux);
   if (full) {
-    uint2 ur[16];
+    uint2 ur[SH::NIT];
 #pragma unroll
-    for (int it = 0; it < 16; ++it) ur[it] = *reinterpret_cast<const uint2*>(U + static_cast<int64_t>(r0 + 2 * it) * g.glu_f + n);
+    for (int it = 0; it < SH::NIT; ++it) ur[it] = *reinterpret_cast<const uint2*>(U + static_cast<int64_t>(r0 + SH::RPI * it) * g.glu_f + n);
 #pragma unroll
-    for (int it = 0; it < 16; ++it)
-      relu2_bwd_one(g, *reinterpret_cast<const float4*>(stage + (2 * it + half) * kStagePitch + c), ur[it],
-                    r0 + 2 * it, n);
+    for (int it = 0; it < SH::NIT; ++it)
+      relu2_bwd_one(g, *reinterpret_cast<const float4*>(stage + (SH::RPI * it + sub) * SH::Pitch + c), ur[it],
+                    r0 + SH::RPI * it, n);
   } else {
 #pragma unroll 1
-    for (int it = 0; it < 16; ++it) {
-      const int64_t m = r0 + 2 * it;
+    for (int it = 0; it < SH::NIT; ++it) {
+      const int64_t m = r0 + SH::RPI * it;
       if (m >= M || n >= g.N) continue;
-      relu2_bwd_one(g, *reinterpret_cast<const float4*>(stage + (2 * it + half) * kStagePitch + c),
+      relu2_bwd_one(g, *reinterpret_cast<const float4*>(stage + (SH::RPI * it + sub) * SH::Pitch + c),
                     *reinterpret_cast<const uint2*>(U + m * g.glu_f + n), m, n);
     }
   }
@@ -760,16 +781,17 @@ __device__ __forceinline__ void relu2_bwd_rows(const GemmArgs& g, const float* s
 // k range; `ring` is the workgroup's LDS.
 // Plain bf16 output of a 32-row block row that crosses M: straight from the
 // accumulators, each row checked (lane: row 16 ii + l16, columns 16 j + q16).
-__device__ __forceinline__ void epilogue_plain_edge_bf16(const GemmArgs& g, const floatx4 (&a0)[8],
-                                                         const floatx4 (&a1)[8], float alpha, int mb, int nb, int l16,
-                                                         int q16, int M) {
+template <int NJ>
+__device__ __forceinline__ void epilogue_plain_edge_bf16(const GemmArgs& g, const floatx4 (&a0)[NJ],
+                                                         const floatx4 (&a1)[NJ], float alpha, int mb, int nb,
+                                                         int l16, int q16, int M) {
 #pragma unroll
   for (int ii = 0; ii < 2; ++ii) {
     const int m = mb + 16 * ii + l16;
     if (m < M) {
       bf16* C = static_cast<bf16*>(g.C) + static_cast<int64_t>(m) * g.ldc + nb + q16;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
+      for (int j = 0; j < NJ; ++j) {
         const floatx4& a = ii ? a1[j] : a0[j];
         *reinterpret_cast<uint2*>(C + j * 16) = pack4_bf16(alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]);
       }
@@ -777,19 +799,21 @@ __device__ __forceinline__ void epilogue_plain_edge_bf16(const GemmArgs& g, cons
   }
 }
 
-template <bool AK, bool BKC, int EPI = kEpiPlain>
+template <bool AK, bool BKC, int EPI = kEpiPlain, int BM = 256>
 __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int pid, int n_tiles, int sp,
                                               int splits) {
+  using SH = BigShape<BM>;
+  constexpr int NJ = SH::NJ, WC = SH::WC;
   int M, K;
   resolve_counts(g, M, K);
   const int tiles_n = (g.N + GB - 1) / GB;
-  const int tiles_m = min(n_tiles / tiles_n, (M + GB - 1) / GB);
+  const int tiles_m = min(n_tiles / tiles_n, (M + BM - 1) / BM);
   int tm, tn;
   if (!tile_coords(pid, tiles_m, tiles_n, tm, tn)) return;
-  const int m0 = tm * GB, n0 = tn * GB;
+  const int m0 = tm * BM, n0 = tn * GB;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
+  const int wm = wave / SH::NWN, wn = wave % SH::NWN;
   const bf16* A = static_cast<const bf16*>(g.A);
   const bf16* B = static_cast<const bf16*>(g.B);
 
@@ -800,25 +824,25 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
   const int nk = kt1 - kt0;
   const int kend = min(K, kt1 * GK);  // loads at or past it read zeros
 
-  floatx4 acc[4][8];
+  floatx4 acc[4][NJ];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
 
   const OpLanes<AK> oa = op_lanes<AK>(g.lda, lane, wave, wm * 64);
-  const OpLanes<BKC> ob = op_lanes<BKC>(g.ldb, lane, wave, wn * 128);
+  const OpLanes<BKC> ob = op_lanes<BKC>(g.ldb, lane, wave, wn * WC);
   bf16* const ra = ring;                     // A's slots
-  bf16* const rb = ring + kSlotsA * kSlot;   // B's slots
+  bf16* const rb = ring + SH::NSA * SH::SlotA;  // B's slots
   // Load instruction q of A or B for k step kt into slot sl.
   auto load_a = [&](int sl, int kt, int q) {
-    tile_part<AK>(ra + sl * kSlot, oa, A, g.lda, m0, M, (kt0 + kt) * GK, kend, wave, q);
+    tile_part<AK>(ra + sl * SH::SlotA, oa, A, g.lda, m0, M, (kt0 + kt) * GK, kend, wave, q);
   };
   auto load_b = [&](int sl, int kt, int q) {
     if constexpr (EPI == kEpiGluFwd)
-      tile_part_glu(rb + sl * kSlot, ob, B, g.ldb, tn, g.glu_f, (kt0 + kt) * GK, kend, wave, q);
+      tile_part_glu<WC>(rb + sl * kSlot, ob, B, g.ldb, tn, g.glu_f, (kt0 + kt) * GK, kend, wave, q);
     else
       tile_part<BKC>(rb + sl * kSlot, ob, B, g.ldb, n0, g.N, (kt0 + kt) * GK, kend, wave, q);
   };
@@ -826,60 +850,109 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
   // left pending on some path, it would wait for one -- for every load of
   // the ring -- inside the k loop (11% of the backward pair launches).
   __builtin_amdgcn_s_waitcnt(kWaitVm0);
-  // Steps 0 and 1; A's step 2 goes out in step 0's first quarter.
+  if constexpr (BM == 256) {
+    // Steps 0 and 1; A's step 2 goes out in step 0's first quarter.
 #pragma unroll
-  for (int q = 0; q < kLoads; ++q) load_b(0, 0, q);
+    for (int q = 0; q < kLoads; ++q) load_b(0, 0, q);
 #pragma unroll
-  for (int q = 0; q < kLoads; ++q) load_a(0, 0, q);
+    for (int q = 0; q < kLoads; ++q) load_a(0, 0, q);
 #pragma unroll
-  for (int q = 0; q < kLoads; ++q) load_a(1, 1, q);
+    for (int q = 0; q < kLoads; ++q) load_a(1, 1, q);
 #pragma unroll
-  for (int q = 0; q < kLoads; ++q) load_b(1, 1, q);
-  dma_barrier<2 * kLoads>();  // step 0 has landed
-  bf16x8 fa[2][4], fb[2][4];  // A blocks per k-substep, B blocks per half
+    for (int q = 0; q < kLoads; ++q) load_b(1, 1, q);
+    dma_barrier<2 * kLoads>();  // step 0 has landed
+    bf16x8 fa[2][4], fb[2][4];  // A blocks per k-substep, B blocks per half
 #pragma unroll
-  for (int i = 0; i < 4; ++i) fa[0][i] = frag<AK>(ra, oa, i, 0);
+    for (int i = 0; i < 4; ++i) fa[0][i] = frag<AK>(ra, oa, i, 0);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) fb[0][j] = frag<BKC>(rb, ob, j, 0);
-  int sa = 0;  // A's slot of step kt
-  for (int kt = 0; kt < nk; ++kt) {
-    const int sb = kt & 1;
-    const int sa1 = sa == 2 ? 0 : sa + 1, sa2 = sa1 == 2 ? 0 : sa1 + 1;
+    for (int j = 0; j < 4; ++j) fb[0][j] = frag<BKC>(rb, ob, j, 0);
+    int sa = 0;  // A's slot of step kt
+    for (int kt = 0; kt < nk; ++kt) {
+      const int sb = kt & 1;
+      const int sa1 = sa == 2 ? 0 : sa + 1, sa2 = sa1 == 2 ? 0 : sa1 + 1;
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      const int ks = h >> 1, P = h & 1, nks = ((h + 1) >> 1) & 1;
-      const bf16* na = ra + (h == 3 ? sa1 : sa) * kSlot;
-      const bf16* nb = rb + (h == 3 ? sb ^ 1 : sb) * kSlot;
-      // all of step kt is read; step kt+1 has landed (in flight: A's kt+2)
-      if (h == 3) dma_barrier<kLoads>();
+      for (int h = 0; h < 4; ++h) {
+        const int ks = h >> 1, P = h & 1, nks = ((h + 1) >> 1) & 1;
+        const bf16* na = ra + (h == 3 ? sa1 : sa) * kSlot;
+        const bf16* nb = rb + (h == 3 ? sb ^ 1 : sb) * kSlot;
+        // all of step kt is read; step kt+1 has landed (in flight: A's kt+2)
+        if (h == 3) dma_barrier<kLoads>();
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int i = q >> 2, j = q & 3;
-        acc[i][4 * P + j] =
-            __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[P][j], fa[ks][i], acc[i][4 * P + j], 0, 0, 0);
-        if (P == 0) {  // the other four B blocks
-          if (q < 8 && (q & 1) == 0) fb[1][q >> 1] = frag<BKC>(nb, ob, 4 + (q >> 1), ks);
-        } else if (q < 8) {  // the next k-substep's A blocks and first B blocks
-          if (q & 1)
-            fa[ks ^ 1][q >> 1] = frag<AK>(na, oa, q >> 1, nks);
-          else
-            fb[0][q >> 1] = frag<BKC>(nb, ob, q >> 1, nks);
+        for (int q = 0; q < 16; ++q) {
+          const int i = q >> 2, j = q & 3;
+          acc[i][4 * P + j] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[P][j], fa[ks][i], acc[i][4 * P + j], 0, 0, 0);
+          if (P == 0) {  // the other four B blocks
+            if (q < 8 && (q & 1) == 0) fb[1][q >> 1] = frag<BKC>(nb, ob, 4 + (q >> 1), ks);
+          } else if (q < 8) {  // the next k-substep's A blocks and first B blocks
+            if (q & 1)
+              fa[ks ^ 1][q >> 1] = frag<AK>(na, oa, q >> 1, nks);
+            else
+              fb[0][q >> 1] = frag<BKC>(nb, ob, q >> 1, nks);
+          }
+          if ((q & 3) == 0) {
+            if (h == 3) load_b(sb, kt + 2, q >> 2);
+            if (h == 0) load_a(sa2, kt + 2, q >> 2);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
-        if ((q & 3) == 0) {
-          if (h == 3) load_b(sb, kt + 2, q >> 2);
-          if (h == 0) load_a(sa2, kt + 2, q >> 2);
-        }
-        __builtin_amdgcn_sched_barrier(0);
       }
+      sa = sa1;
     }
-    sa = sa1;
+  } else {
+    // Half the rows: two halves of 16 MFMAs per k step, one per k-substep, the
+    // barrier before the second.  Three slots of each operand, so step kt+3
+    // follows into step kt's slots: B's loads after the barrier, A's in the
+    // next step's first half (the first fill leaves step 2's to step 0).
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+      for (int q = 0; q < kLoads; ++q) load_b(t, t, q);
+#pragma unroll
+      for (int q = 0; q < SH::LoadsA; ++q) load_a(t, t, q);
+    }
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) load_b(2, 2, q);
+    dma_barrier<2 * kLoads + SH::LoadsA>();  // step 0 has landed
+    bf16x8 fa[2][4], fb[2][4];               // per k-substep
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      fa[0][i] = frag<AK>(ra, oa, i, 0);
+      fb[0][i] = frag<BKC>(rb, ob, i, 0);
+    }
+    int sl = 0;  // slots of step kt
+    for (int kt = 0; kt < nk; ++kt) {
+      const int sl1 = sl == 2 ? 0 : sl + 1, sl2 = sl1 == 2 ? 0 : sl1 + 1;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const bf16* na = ra + (h == 1 ? sl1 : sl) * SH::SlotA;
+        const bf16* nb = rb + (h == 1 ? sl1 : sl) * kSlot;
+        // all of step kt is read; step kt+1 has landed (in flight: step kt+2)
+        if (h == 1) dma_barrier<kLoads + SH::LoadsA>();
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          const int i = q >> 2, j = q & 3;
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[h][j], fa[h][i], acc[i][j], 0, 0, 0);
+          if (q < 8) {
+            if (q & 1)
+              fa[h ^ 1][q >> 1] = frag<AK>(na, oa, q >> 1, h ^ 1);
+            else
+              fb[h ^ 1][q >> 1] = frag<BKC>(nb, ob, q >> 1, h ^ 1);
+          }
+          if (h == 1 && (q & 3) == 0) load_b(sl, kt + 3, q >> 2);
+          if (h == 0 && (q & 7) == 0) load_a(sl2, kt + 2, q >> 3);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      sl = sl1;
+    }
   }
 
   // Epilogue staged through LDS.  A lane holds, per 16x16 block, one output
   // row and 4 consecutive columns; stored directly that scatters every store
   // over 16 rows.  Instead each wave writes one block row of its results
-  // (32 x 128 float32, alpha applied) into a private [32][kStagePitch] block
-  // and reads it back row-major: a half-wave then covers 128 contiguous
+  // (32 x WC float32, alpha applied) into a private [32][Pitch] block
+  // and reads it back row-major: WC / 4 lanes then cover WC contiguous
   // columns of one row, so the residual loads and the output stores (one
   // rounding, after the residual) are fully coalesced.  The blocks are
   // private to the wave, so after one barrier (the ring's last loads have
@@ -887,15 +960,15 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
   // workgroup barrier, whose memory fence would wait for every store in
   // flight, and the stores drain while the wave goes on.
   const float alpha = g.alpha * (g.alpha_dev ? *g.alpha_dev : 1.f);
-  const int half = lane >> 5;
+  const int sub = lane / (WC / 4);
   const int l16 = lane & 15, q16 = 4 * (lane >> 4);
   float* part = g.part ? g.part + static_cast<int64_t>(sp) * g.M * g.N : nullptr;
-  float* stage = reinterpret_cast<float*>(ring) + wave * (32 * kStagePitch);
-  const int c = (lane & 31) * 4;
-  const int n = n0 + wn * 128 + c;
-  // A block row takes the branch-free path when all its 32 rows and 128
+  float* stage = reinterpret_cast<float*>(ring) + wave * (32 * SH::Pitch);
+  const int c = (lane % (WC / 4)) * 4;
+  const int n = n0 + wn * WC + c;
+  // A block row takes the branch-free path when all its 32 rows and WC
   // columns are in range.
-  const bool full_cols = n0 + wn * 128 + 128 <= g.N;
+  const bool full_cols = n0 + wn * WC + WC <= g.N;
   // Largest kept sequence index, for the row map (rows < M only).
   const int q_last = g.out_map.idx && M > 0 ? (M - 1) / g.out_map.S : 0;
   dma_barrier<0>();  // the loop's last loads (zeros) land before the ring is reused
@@ -909,9 +982,11 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
     // past M are not stored
     {
       bf16* st16 = reinterpret_cast<bf16*>(stage);
-      const int rr = lane >> 4, cc = (lane & 15) * 8;  // [u v]: row rr of each 4, columns cc..cc+7
-      const int rs = lane >> 3, cs = (lane & 7) * 8;   // s: row rs of each 8, columns cs..cs+7
-      const int f0 = tn * 128 + wn * 64;               // the wave's first d_ff column
+      constexpr int GW = WC / 2;                                  // the wave's d_ff columns
+      constexpr int LU = WC / 8, LS = GW / 8;                     // lanes per row of [u v], of s
+      const int rr = lane / LU, cc = (lane % LU) * 8;             // [u v]: the lane's row and columns cc..cc+7
+      const int rs = lane / LS, cs = (lane % LS) * 8;             // s
+      const int f0 = tn * 128 + wn * GW;                          // the wave's first d_ff column
       bf16* C = static_cast<bf16*>(g.C);
       bf16* Sp = static_cast<bf16*>(g.aux);
 #pragma unroll
@@ -921,20 +996,21 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
 #pragma unroll
         for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
+          for (int j = 0; j < NJ; ++j) {
             const floatx4& a = acc[2 * i + ii][j];
-            *reinterpret_cast<uint2*>(st16 + (16 * ii + l16) * kStagePitch16 + j * 16 + q16) =
+            *reinterpret_cast<uint2*>(st16 + (16 * ii + l16) * SH::Pitch + j * 16 + q16) =
                 pack4_bf16(alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]);
           }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        // staged columns 0-63 are gate (u) columns, 64-127 up (v) columns
-        const int gcol = cc < 64 ? f0 + cc : g.glu_f + f0 + cc - 64;
+        // staged columns below GW are gate (u) columns, the others up (v) columns
+        const int gcol = cc < GW ? f0 + cc : g.glu_f + f0 + cc - GW;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const bf16* src = st16 + (4 * k + rr) * kStagePitch16 + cc;
+        for (int k = 0; k < LU / 2; ++k) {
+          const int row = 64 / LU * k + rr;
+          const bf16* src = st16 + row * SH::Pitch + cc;
           const uint2 lo = *reinterpret_cast<const uint2*>(src), hi = *reinterpret_cast<const uint2*>(src + 4);
-          if (mb + 4 * k + rr < M)
-            *reinterpret_cast<uint4*>(C + static_cast<int64_t>(mb + 4 * k + rr) * g.ldc + gcol) =
+          if (mb + row < M)
+            *reinterpret_cast<uint4*>(C + static_cast<int64_t>(mb + row) * g.ldc + gcol) =
                 make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -942,21 +1018,22 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
 #pragma unroll
         for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
+          for (int j = 0; j < NJ / 2; ++j) {
             float sv[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              sv[e] = swiglu_fwd_f(alpha * acc[2 * i + ii][j][e], alpha * acc[2 * i + ii][j + 4][e]);
-            *reinterpret_cast<uint2*>(st16 + (16 * ii + l16) * kStagePitch16 + j * 16 + q16) =
+              sv[e] = swiglu_fwd_f(alpha * acc[2 * i + ii][j][e], alpha * acc[2 * i + ii][j + NJ / 2][e]);
+            *reinterpret_cast<uint2*>(st16 + (16 * ii + l16) * SH::Pitch + j * 16 + q16) =
                 pack4_bf16(sv[0], sv[1], sv[2], sv[3]);
           }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const bf16* src = st16 + (8 * k + rs) * kStagePitch16 + cs;
+        for (int k = 0; k < LS / 2; ++k) {
+          const int row = 64 / LS * k + rs;
+          const bf16* src = st16 + row * SH::Pitch + cs;
           const uint2 lo = *reinterpret_cast<const uint2*>(src), hi = *reinterpret_cast<const uint2*>(src + 4);
-          if (mb + 8 * k + rs < M)
-            *reinterpret_cast<uint4*>(Sp + static_cast<int64_t>(mb + 8 * k + rs) * g.glu_f + f0 + cs) =
+          if (mb + row < M)
+            *reinterpret_cast<uint4*>(Sp + static_cast<int64_t>(mb + row) * g.glu_f + f0 + cs) =
                 make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // reads done before the block is rewritten
@@ -967,36 +1044,37 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
   if constexpr (EPI == kEpiPlain) {
     if (!part && !g.R && !g.c_f32 && !g.out_map.idx && full_cols) {
       bf16* st16 = reinterpret_cast<bf16*>(stage);
-      const int rr = lane >> 4, cc = (lane & 15) * 8;  // read: row rr of each 4, columns cc..cc+7
+      constexpr int LU = WC / 8;                       // lanes per row
+      const int rr = lane / LU, cc = (lane % LU) * 8;  // read: the lane's row and columns cc..cc+7
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const int mb = m0 + wm * 64 + i * 32;
         if (mb + 32 > M) {
-          if (mb < M) epilogue_plain_edge_bf16(g, acc[2 * i], acc[2 * i + 1], alpha, mb, n0 + wn * 128, l16, q16, M);
+          if (mb < M) epilogue_plain_edge_bf16(g, acc[2 * i], acc[2 * i + 1], alpha, mb, n0 + wn * WC, l16, q16, M);
           continue;
         }
 #pragma unroll
         for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
+          for (int j = 0; j < NJ; ++j) {
             const floatx4& a = acc[2 * i + ii][j];
-            *reinterpret_cast<uint2*>(st16 + (16 * ii + l16) * kStagePitch16 + j * 16 + q16) =
+            *reinterpret_cast<uint2*>(st16 + (16 * ii + l16) * SH::Pitch + j * 16 + q16) =
                 pack4_bf16(alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]);
           }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        // rows are 264 bytes apart (8-byte aligned, no bank conflicts for the
+        // rows are 2 WC + 8 bytes apart (8-byte aligned, no bank conflicts for the
         // 8-byte stage writes), so each 16 bytes are read as two 8-byte halves
-        uint4 v[8];
+        uint4 v[LU / 2];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const bf16* src = st16 + (4 * k + rr) * kStagePitch16 + cc;
+        for (int k = 0; k < LU / 2; ++k) {
+          const bf16* src = st16 + (64 / LU * k + rr) * SH::Pitch + cc;
           const uint2 lo = *reinterpret_cast<const uint2*>(src), hi = *reinterpret_cast<const uint2*>(src + 4);
           v[k] = make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
         bf16* C = static_cast<bf16*>(g.C);
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-          *reinterpret_cast<uint4*>(C + static_cast<int64_t>(mb + 4 * k + rr) * g.ldc + n0 + wn * 128 + cc) = v[k];
+        for (int k = 0; k < LU / 2; ++k)
+          *reinterpret_cast<uint4*>(C + static_cast<int64_t>(mb + 64 / LU * k + rr) * g.ldc + n0 + wn * WC + cc) = v[k];
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // reads done before the block is rewritten
       }
       return;
@@ -1007,24 +1085,24 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
 #pragma unroll
     for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
+      for (int j = 0; j < NJ; ++j) {
         const floatx4& a = acc[2 * i + ii][j];
-        *reinterpret_cast<float4*>(stage + (16 * ii + l16) * kStagePitch + j * 16 + q16) =
+        *reinterpret_cast<float4*>(stage + (16 * ii + l16) * SH::Pitch + j * 16 + q16) =
             make_float4(alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]);
       }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // staged values visible to the wave
     const int mb = m0 + wm * 64 + i * 32;              // first row of the block row
     if constexpr (EPI == kEpiGluBwd) {
-      glu_bwd_rows(g, stage, mb + half, half, c, n, M, n0 + wn * 128 + 128 <= g.N && mb + 32 <= M);
+      glu_bwd_rows<SH>(g, stage, mb + sub, sub, c, n, M, n0 + wn * WC + WC <= g.N && mb + 32 <= M);
     } else if constexpr (EPI == kEpiRelu2Fwd) {
-      relu2_fwd_rows(g, stage, mb + half, half, c, n, M, n0 + wn * 128 + 128 <= g.N && mb + 32 <= M);
+      relu2_fwd_rows<SH>(g, stage, mb + sub, sub, c, n, M, n0 + wn * WC + WC <= g.N && mb + 32 <= M);
     } else if constexpr (EPI == kEpiRelu2Bwd) {
-      relu2_bwd_rows(g, stage, mb + half, half, c, n, M, n0 + wn * 128 + 128 <= g.N && mb + 32 <= M);
+      relu2_bwd_rows<SH>(g, stage, mb + sub, sub, c, n, M, n0 + wn * WC + WC <= g.N && mb + 32 <= M);
     } else {
       if (full_cols && mb + 32 <= M)
-        epilogue_rows_full(g, part, stage, mb + half, half, c, n, q_last);
+        epilogue_rows_full<SH>(g, part, stage, mb + sub, sub, c, n, q_last);
       else
-        epilogue_rows_edge(g, part, stage, mb + half, half, c, n, M);
+        epilogue_rows_edge<SH>(g, part, stage, mb + sub, sub, c, n, M);
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // reads done before the block is rewritten
   }
@@ -1051,6 +1129,20 @@ LD_BIG_ATTRS void ld_gemm_bf16_nt_glu_256(GemmArgs g) {
 LD_BIG_ATTRS void ld_gemm_bf16_nt_relu2_256(GemmArgs g) {
   __shared__ __align__(16) bf16 ring[kRingElems];
   gemm_big_body<true, true, kEpiRelu2Fwd>(g, ring, blockIdx.x, gridDim.x, 0, 1);
+}
+
+// The forward projections on 128-row tiles (see plan_rows).
+LD_BIG_ATTRS void ld_gemm_bf16_nt_128(GemmArgs g) {
+  __shared__ __align__(16) bf16 ring[kRingElems];
+  gemm_big_body<true, true, kEpiPlain, 128>(g, ring, blockIdx.x, gridDim.x, 0, 1);
+}
+LD_BIG_ATTRS void ld_gemm_bf16_nt_glu_128(GemmArgs g) {
+  __shared__ __align__(16) bf16 ring[kRingElems];
+  gemm_big_body<true, true, kEpiGluFwd, 128>(g, ring, blockIdx.x, gridDim.x, 0, 1);
+}
+LD_BIG_ATTRS void ld_gemm_bf16_nt_relu2_128(GemmArgs g) {
+  __shared__ __align__(16) bf16 ring[kRingElems];
+  gemm_big_body<true, true, kEpiRelu2Fwd, 128>(g, ring, blockIdx.x, gridDim.x, 0, 1);
 }
 
 // Up to three GEMMs in one launch: weight-gradient GEMMs g1 (tiles1 tiles,
@@ -1133,10 +1225,27 @@ void set_attrs() {
 
 constexpr int kPlanK = 32;  // unit of k in the launch estimates
 
+static int64_t big_tiles_of(int64_t M, int64_t N, int bm) { return ((M + bm - 1) / bm) * ((N + GB - 1) / GB); }
+
+// A last round of tiles that leaves most of the 256 CUs idle costs as much as a
+// full one; 128-row tiles halve what a round costs, at 0.56-0.6 of a 256-row
+// tile's time each (8192 x 8192 x 8192 1.15 times as long, a third more
+// operand traffic per product).  So they are taken where the rounds, weighted
+// with that, are fewer: 3264 x 2048 x 5504 (104 or 208 tiles) 95 -> 66 us,
+// 3264 x 6144 x 2048 (312 or 624) 88 -> 82, 8192 x 768 x 2048 (96 or 192) 41 -> 27;
+// 8192 x 4096 x 768 (512 or 1024) stays at 50 (59).
+constexpr double kHalfTile = 0.59;
+
+int plan_rows(int64_t m, int64_t n) {
+  auto rounds = [&](int bm) { return static_cast<double>((big_tiles_of(m, n, bm) + 255) / 256); };
+  return kHalfTile * rounds(128) < rounds(256) ? 128 : 256;
+}
+
 GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, int64_t max_m,
-                   int64_t max_k, bool allow_split) {
+                   int64_t max_k, bool allow_split, int64_t host_m) {
   GemmPlan p{};
   p.splits = 1;
+  p.bm = GB;
   if (dtype != LD_BF16) {
     p.name = "ld_gemm_f32_k";
     return p;
@@ -1149,8 +1258,12 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
   // split-K only for float32 outputs without a residual (weight gradients);
   // such a GEMM fills the CUs through its splits even with few tiles
   const bool splittable = allow_split && g.c_f32 && !g.R && !g.out_map.idx && g.ldc == g.N && max_k >= 16 * kPlanK;
-  p.big = (g.N % 4 == 0) && (g.ldc % 4 == 0) && (!g.R || g.ldr % 4 == 0) && max_m >= 512 && g.N >= 512 &&
-          (big_tiles >= 32 || (splittable && big_tiles * kMaxSplits >= 32)) && a_span < kBigMaxSpan &&
+  // The big kernel takes every size (at 64 rows of 2048 columns and K = 2048,
+  // a few tiles, the 128x128 one takes 33 us and it 23; NN 60 and 41): the
+  // 128x128 kernel is for what its loads and stores of 8 and 16 bytes do not.
+  auto aligned = [](const void* q, int bytes) { return reinterpret_cast<uintptr_t>(q) % bytes == 0; };
+  p.big = g.N % 4 == 0 && g.ldc % 4 == 0 && (!g.R || g.ldr % 4 == 0) && aligned(g.A, 16) && aligned(g.B, 16) &&
+          aligned(g.C, g.c_f32 ? 16 : 8) && aligned(g.R, g.r_f32 || g.c_f32 ? 16 : 8) && a_span < kBigMaxSpan &&
           b_span < kBigMaxSpan;
   if (p.big) {
     if (splittable) {
@@ -1164,7 +1277,8 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
         }
       }
     }
-    p.name = a_kcontig && b_kcontig ? "ld_gemm_bf16_nt_256"
+    if (a_kcontig && b_kcontig && p.splits == 1) p.bm = plan_rows(host_m > 0 ? host_m : max_m, g.N);
+    p.name = a_kcontig && b_kcontig ? (p.bm == 128 ? "ld_gemm_bf16_nt_128" : "ld_gemm_bf16_nt_256")
              : a_kcontig            ? "ld_gemm_bf16_nn_256"
              : b_kcontig            ? "ld_gemm_bf16_tt_256"
                                     : "ld_gemm_bf16_tn_256";
@@ -1196,7 +1310,7 @@ hipError_t launch_gemm_plan(int dtype, int a_kcontig, int b_kcontig, const GemmP
   if (max_m <= 0 || g.N <= 0) return hipSuccess;
   if (dtype == LD_BF16 && p.big) {
     set_attrs();
-    const int64_t tiles = ((max_m + GB - 1) / GB) * ((g.N + GB - 1) / GB);
+    const int64_t tiles = big_tiles_of(max_m, g.N, p.bm);
     float* C = static_cast<float*>(g.C);
     if (p.splits > 1) {
       if (!g.part) return hipErrorInvalidValue;
@@ -1204,7 +1318,9 @@ hipError_t launch_gemm_plan(int dtype, int a_kcontig, int b_kcontig, const GemmP
       g.part = nullptr;
     }
     const dim3 grid(static_cast<unsigned>(tiles), p.splits), block(kBigThreads);
-    if (a_kcontig && b_kcontig)
+    if (a_kcontig && b_kcontig && p.bm == 128)
+      hipLaunchKernelGGL(ld_gemm_bf16_nt_128, grid, block, 0, s, g);
+    else if (a_kcontig && b_kcontig)
       hipLaunchKernelGGL(ld_gemm_bf16_nt_256, grid, block, 0, s, g);
     else if (a_kcontig)
       hipLaunchKernelGGL(ld_gemm_bf16_nn_256, grid, block, 0, s, g);
@@ -1286,17 +1402,23 @@ PairPlan plan_gemm_pair(int64_t m1, int64_t n1, int64_t k1, int64_t m3, int64_t 
   return best;
 }
 
-hipError_t launch_gemm_glu_fwd(const GemmArgs& g, int64_t max_m, hipStream_t s) {
+hipError_t launch_gemm_glu_fwd(const GemmArgs& g, int64_t max_m, int bm, hipStream_t s) {
   if (max_m <= 0 || g.N <= 0) return hipSuccess;
-  const int64_t tiles = ((max_m + GB - 1) / GB) * (g.N / GB);
-  hipLaunchKernelGGL(ld_gemm_bf16_nt_glu_256, dim3(static_cast<unsigned>(tiles)), dim3(kBigThreads), 0, s, g);
+  const dim3 grid(static_cast<unsigned>(big_tiles_of(max_m, g.N, bm))), block(kBigThreads);
+  if (bm == 128)
+    hipLaunchKernelGGL(ld_gemm_bf16_nt_glu_128, grid, block, 0, s, g);
+  else
+    hipLaunchKernelGGL(ld_gemm_bf16_nt_glu_256, grid, block, 0, s, g);
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_relu2_fwd(const GemmArgs& g, int64_t max_m, hipStream_t s) {
+hipError_t launch_gemm_relu2_fwd(const GemmArgs& g, int64_t max_m, int bm, hipStream_t s) {
   if (max_m <= 0 || g.N <= 0) return hipSuccess;
-  const int64_t tiles = ((max_m + GB - 1) / GB) * ((g.N + GB - 1) / GB);
-  hipLaunchKernelGGL(ld_gemm_bf16_nt_relu2_256, dim3(static_cast<unsigned>(tiles)), dim3(kBigThreads), 0, s, g);
+  const dim3 grid(static_cast<unsigned>(big_tiles_of(max_m, g.N, bm))), block(kBigThreads);
+  if (bm == 128)
+    hipLaunchKernelGGL(ld_gemm_bf16_nt_relu2_128, grid, block, 0, s, g);
+  else
+    hipLaunchKernelGGL(ld_gemm_bf16_nt_relu2_256, grid, block, 0, s, g);
   return hipGetLastError();
 }
 

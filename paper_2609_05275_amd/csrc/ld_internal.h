@@ -264,6 +264,7 @@ struct GemmPlan {
   const char* name;
   int big;
   int splits;
+  int bm;  // rows of the big kernel's tile (256, or 128 for k-contiguous operands)
 };
 
 struct AttnArgs {
@@ -383,7 +384,10 @@ const char* gemm_kernel_name(int dtype, int a_kcontig, int b_kcontig);
 // allow_split: split-K may be chosen (the caller then provides g.part of
 // gemm_part_bytes bytes).
 GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, int64_t max_m,
-                   int64_t max_k, bool allow_split);
+                   int64_t max_k, bool allow_split, int64_t host_m = -1);
+// Rows of the tiles (256 or 128) of a forward projection of m rows (the kept
+// rows where the host knows them) and n columns.
+int plan_rows(int64_t m, int64_t n);
 size_t gemm_part_bytes(const GemmPlan& p, int64_t M, int64_t N);
 // Weight-gradient GEMMs g1 and g3 (both operands mn-contiguous, float32
 // out; g3 optional and never split, g1 absent when g1.M = 0) and an
@@ -406,11 +410,11 @@ hipError_t launch_gemm_pair(GemmArgs g1, const GemmArgs* g3, const PairPlan& p, 
 // C[i] = sum over splits of part[s * mn + i] (float32, split order).
 hipError_t launch_splitk_reduce(const float* part, int splits, int64_t mn, float* C, hipStream_t s);
 // The SwiGLU projection with its activation fused (GemmArgs glu_f, aux):
-// ld_gemm_bf16_nt_glu_256 over max_m rows, for bf16 with glu_f % 128 == 0
+// ld_gemm_bf16_nt_glu_256 or _128 (bm, plan_rows) over max_m rows, for bf16 with glu_f % 128 == 0
 // and N = 2 glu_f, both operands k-contiguous.
-hipError_t launch_gemm_glu_fwd(const GemmArgs& g, int64_t max_m, hipStream_t s);
-// ld_gemm_bf16_nt_relu2_256 over max_m rows (see GemmArgs.relu2)
-hipError_t launch_gemm_relu2_fwd(const GemmArgs& g, int64_t max_m, hipStream_t s);
+hipError_t launch_gemm_glu_fwd(const GemmArgs& g, int64_t max_m, int bm, hipStream_t s);
+// ld_gemm_bf16_nt_relu2_256 or _128 over max_m rows (see GemmArgs.relu2)
+hipError_t launch_gemm_relu2_fwd(const GemmArgs& g, int64_t max_m, int bm, hipStream_t s);
 hipError_t launch_gemm_plan(int dtype, int a_kcontig, int b_kcontig, const GemmPlan& p, GemmArgs g,
                             int64_t max_m, hipStream_t s);
 // Fixed scratch of the no-allocation attention backward (the delta rows,

@@ -214,6 +214,35 @@ def test_gemm_bf16_big_k_steps(layout, K):
     assert np.all(np.abs(f64(Cb) - ref) <= 1.01 * (bound + 2.0 ** -8 * np.abs(ref)))
 
 
+@pytest.mark.parametrize("layout", [(1, 1), (1, 0), (0, 0), (0, 1)])
+@pytest.mark.parametrize("M,N,K", [(1, 4, 8), (8, 264, 64), (64, 512, 136), (136, 256, 328), (264, 520, 192),
+                                   (3264, 264, 72)])
+@pytest.mark.parametrize("off,pad", [(0, 0), (1, 0), (0, 1)], ids=["aligned", "offset", "odd_ldc"])
+def test_gemm_bf16_few_tiles(layout, M, N, K, off, pad):
+    """One to a few tiles (128-row ones among them), rows and columns short of
+    and past a tile edge; with C off 8 bytes' alignment or an odd leading
+    dimension the 128x128 kernel.  bf16 output and residual: one rounding to 8
+    significant bits (2^-8) of sums of K exact products."""
+    ak, bk = layout
+    if (not ak and M % 8) or (not bk and N % 8):
+        pytest.skip("mn-contiguous operands come in eights")
+    g = torch.Generator().manual_seed(9)
+    A = torch.randn(M, K, generator=g).to(torch.bfloat16)
+    B = torch.randn(N, K, generator=g).to(torch.bfloat16)
+    R = torch.randn(M, N, generator=g).to(torch.bfloat16)
+    Ad = (A if ak else A.t().contiguous()).to(DEV)
+    Bd = (B if bk else B.t().contiguous()).to(DEV)
+    ldc = N + pad
+    buf = torch.full((off + M * ldc + 8,), 7.0, dtype=torch.bfloat16, device=DEV)
+    ld.ld_gemm(ak, bk, M, N, K, Ad, K if ak else M, Bd, K if bk else N, buf[off:], ldc, R=R.to(DEV), ldr=N)
+    torch.cuda.synchronize()
+    C = f64(buf)[off:off + M * ldc].reshape(M, ldc)
+    ref = f64(R) + f64(A) @ f64(B).T
+    bound = (K + 1) * 2.0 ** -24 * (np.abs(f64(R)) + np.abs(f64(A)) @ np.abs(f64(B)).T) + 2.0 ** -8 * np.abs(ref)
+    assert np.all(np.abs(C[:, :N] - ref) <= 1.01 * bound)
+    assert (C[:, N:] == 7.0).all() and (f64(buf)[:off] == 7.0).all() and (f64(buf)[off + M * ldc:] == 7.0).all()
+
+
 @pytest.mark.parametrize("layout", [(0, 0), (1, 0)])
 def test_gemm_bf16_split_k(layout):
     """float32 output with split-K partials summed in a fixed order."""
