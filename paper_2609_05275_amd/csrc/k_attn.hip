@@ -1005,19 +1005,24 @@ __global__ __launch_bounds__(64) void ld_attn_fwd_f32(AttnArgs a) {
   const int q0 = blockIdx.x * ST, q = q0 + threadIdx.x;
   const int64_t ldq = 3ll * H * DH;
   const float* base = static_cast<const float*>(a.qkv) + static_cast<int64_t>(seq) * S * ldq;
+  // rows past S repeat the last (nothing of theirs is used): a load in a
+  // branch of its own would be waited for on its own
+  const int qc = min(q, S - 1);
   float qv[DH], o[DH];
+#pragma unroll
   for (int i = 0; i < DH; ++i) {
-    qv[i] = q < S ? base[static_cast<int64_t>(q) * ldq + head * DH + i] : 0.f;
+    qv[i] = base[static_cast<int64_t>(qc) * ldq + head * DH + i];
     o[i] = 0.f;
   }
   float m = -INFINITY, l = 0.f;
   const int kv_end = min(S, q0 + ST);
   for (int k0 = 0; k0 < kv_end; k0 += ST) {
-    for (int e = threadIdx.x; e < ST * DH; e += ST) {
-      const int r = e / DH, c = e % DH;
-      const bool ok = k0 + r < S;
-      Ks[r][c] = ok ? base[static_cast<int64_t>(k0 + r) * ldq + H * DH + head * DH + c] : 0.f;
-      Vs[r][c] = ok ? base[static_cast<int64_t>(k0 + r) * ldq + 2 * H * DH + head * DH + c] : 0.f;
+#pragma unroll 8
+    for (int t = 0; t < DH; ++t) {
+      const int e = t * ST + threadIdx.x, r = e / DH, c = e % DH;
+      const float* row = base + static_cast<int64_t>(min(k0 + r, S - 1)) * ldq + head * DH + c;
+      Ks[r][c] = row[H * DH];
+      Vs[r][c] = row[2 * H * DH];
     }
     __syncthreads();
     for (int j = 0; j < ST; ++j) {
@@ -1053,20 +1058,23 @@ __global__ __launch_bounds__(64) void ld_attn_bwd_dq_f32(AttnArgs a) {
   const float* base = static_cast<const float*>(a.qkv) + static_cast<int64_t>(seq) * S * ldq;
   const float* go = static_cast<const float*>(a.go) + static_cast<int64_t>(seq) * S * ldo;
   float qv[DH], dov[DH], dq[DH];
+  const int qc = min(q, S - 1);  // rows past S repeat the last
+#pragma unroll
   for (int i = 0; i < DH; ++i) {
-    qv[i] = q < S ? base[static_cast<int64_t>(q) * ldq + head * DH + i] : 0.f;
-    dov[i] = q < S ? go[static_cast<int64_t>(q) * ldo + head * DH + i] : 0.f;
+    qv[i] = base[static_cast<int64_t>(qc) * ldq + head * DH + i];
+    dov[i] = go[static_cast<int64_t>(qc) * ldo + head * DH + i];
     dq[i] = 0.f;
   }
   const int64_t srow = (static_cast<int64_t>(seq) * H + head) * S + (q < S ? q : 0);
   const float lse = a.lse[srow], dl = a.delta[srow];
   const int kv_end = min(S, q0 + ST);
   for (int k0 = 0; k0 < kv_end; k0 += ST) {
-    for (int e = threadIdx.x; e < ST * DH; e += ST) {
-      const int r = e / DH, c = e % DH;
-      const bool ok = k0 + r < S;
-      Ks[r][c] = ok ? base[static_cast<int64_t>(k0 + r) * ldq + H * DH + head * DH + c] : 0.f;
-      Vs[r][c] = ok ? base[static_cast<int64_t>(k0 + r) * ldq + 2 * H * DH + head * DH + c] : 0.f;
+#pragma unroll 8
+    for (int t = 0; t < DH; ++t) {
+      const int e = t * ST + threadIdx.x, r = e / DH, c = e % DH;
+      const float* row = base + static_cast<int64_t>(min(k0 + r, S - 1)) * ldq + head * DH + c;
+      Ks[r][c] = row[H * DH];
+      Vs[r][c] = row[2 * H * DH];
     }
     __syncthreads();
     for (int j = 0; j < ST; ++j) {
@@ -1103,23 +1111,23 @@ __global__ __launch_bounds__(64) void ld_attn_bwd_dkdv_f32(AttnArgs a) {
   const float* lse = a.lse + (static_cast<int64_t>(seq) * H + head) * S;
   const float* del = a.delta + (static_cast<int64_t>(seq) * H + head) * S;
   float kv[DH], vv[DH], dk[DH], dv[DH];
+  const int kc = min(key, S - 1);  // rows past S repeat the last
+#pragma unroll
   for (int i = 0; i < DH; ++i) {
-    kv[i] = key < S ? base[static_cast<int64_t>(key) * ldq + H * DH + head * DH + i] : 0.f;
-    vv[i] = key < S ? base[static_cast<int64_t>(key) * ldq + 2 * H * DH + head * DH + i] : 0.f;
+    kv[i] = base[static_cast<int64_t>(kc) * ldq + H * DH + head * DH + i];
+    vv[i] = base[static_cast<int64_t>(kc) * ldq + 2 * H * DH + head * DH + i];
     dk[i] = dv[i] = 0.f;
   }
   for (int qb = k0; qb < S; qb += ST) {
-    for (int e = threadIdx.x; e < ST * DH; e += ST) {
-      const int r = e / DH, c = e % DH;
-      const bool ok = qb + r < S;
-      Qs[r][c] = ok ? base[static_cast<int64_t>(qb + r) * ldq + head * DH + c] : 0.f;
-      Os[r][c] = ok ? go[static_cast<int64_t>(qb + r) * ldo + head * DH + c] : 0.f;
+#pragma unroll 8
+    for (int t = 0; t < DH; ++t) {
+      const int e = t * ST + threadIdx.x, r = e / DH, c = e % DH;
+      const int64_t row = min(qb + r, S - 1);
+      Qs[r][c] = base[row * ldq + head * DH + c];
+      Os[r][c] = go[row * ldo + head * DH + c];
     }
-    if (threadIdx.x < ST) {
-      const bool ok = qb + threadIdx.x < S;
-      ls[threadIdx.x] = ok ? lse[qb + threadIdx.x] : 0.f;
-      dls[threadIdx.x] = ok ? del[qb + threadIdx.x] : 0.f;
-    }
+    ls[threadIdx.x] = lse[min(qb + static_cast<int>(threadIdx.x), S - 1)];
+    dls[threadIdx.x] = del[min(qb + static_cast<int>(threadIdx.x), S - 1)];
     __syncthreads();
     if (key < S) {
       for (int j = 0; j < ST; ++j) {

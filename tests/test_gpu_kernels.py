@@ -104,6 +104,28 @@ def test_rmsnorm_fwd_bwd(dt, d):
     assert rel(f64(dg), edg) < tol
 
 
+@pytest.mark.parametrize("dt,d", [("bf16", 8), ("bf16", 512), ("bf16", 520), ("bf16", 1024), ("bf16", 1032),
+                                  ("f32", 4), ("f32", 256), ("f32", 260), ("f32", 512), ("f32", 516)])
+@pytest.mark.parametrize("rows", [1, 16, 37])
+def test_rmsnorm_bwd_widths(dt, d, rows):
+    """Widths at the edges of one and two chunks per lane (a wave per row) and
+    of the four-wave strip kernel; one row, one strip, a short last strip."""
+    g = torch.Generator().manual_seed(10)
+    x, gy, gres = (torch.randn(rows, d, generator=g).to(TD[dt]) for _ in range(3))
+    gam = (1 + 0.1 * torch.randn(d, generator=g)).to(TD[dt])
+    _, er = block.rmsnorm(f64(x), f64(gam), 1e-5)
+    gx = torch.full((rows, d), 7.0, dtype=TD[dt], device=DEV)
+    dg = torch.full((d,), 7.0, device=DEV)
+    ws = torch.empty(ld.ld_rmsnorm_bwd_ws_bytes(rows, d), dtype=torch.uint8, device=DEV)
+    rstd = torch.from_numpy(np.asarray(er)).reshape(rows).float().to(DEV)
+    ld.ld_rmsnorm_bwd(x.to(DEV), gam.to(DEV), rstd, gy.to(DEV), gres.to(DEV), gx, dg, ws)
+    torch.cuda.synchronize()
+    egx, edg = block.rmsnorm_bwd(f64(x), f64(gam), er, f64(gy))
+    tol = TOL_BF16 if dt == "bf16" else TOL_F32
+    assert rel(f64(gx), egx + f64(gres)) < tol
+    assert rel(f64(dg), edg) < TOL_F32
+
+
 @pytest.mark.parametrize("dt,f", [("bf16", 16384), ("bf16", 2048), ("f32", 172)])
 def test_relu2_fwd_bwd(dt, f):
     rows = 257
@@ -265,6 +287,25 @@ def test_gemm_bf16_split_k(layout):
         outs.append(Cd.cpu())
     assert torch.equal(outs[0], outs[1])
     assert rel(outs[0].double().numpy(), 0.25 * (f64(A) @ f64(B).T)) < 1e-5
+
+
+@pytest.mark.parametrize("layout", [(1, 1), (1, 0), (0, 0), (0, 1)])
+@pytest.mark.parametrize("M,N,K", [(4, 4, 4), (32, 36, 32), (36, 64, 100), (100, 172, 64), (1100, 1028, 36),
+                                   (6, 10, 7)])
+def test_gemm_f32_tiles(layout, M, N, K):
+    """Edges of the 32 and 64 tiles and of the k tiles, and sizes the 16-byte
+    loads do not take; each output one chain of K fused multiply-adds."""
+    ak, bk = layout
+    g = torch.Generator().manual_seed(12)
+    A, B, R = (torch.randn(*s, generator=g) for s in ((M, K), (N, K), (M, N)))
+    Ad = (A if ak else A.t().contiguous()).to(DEV)
+    Bd = (B if bk else B.t().contiguous()).to(DEV)
+    Cd = torch.full((M, N), 7.0, device=DEV)
+    ld.ld_gemm(ak, bk, M, N, K, Ad, K if ak else M, Bd, K if bk else N, Cd, N, R=R.to(DEV), ldr=N)
+    torch.cuda.synchronize()
+    ref = f64(R) + f64(A) @ f64(B).T
+    bound = (K + 2) * 2.0 ** -24 * (np.abs(f64(R)) + np.abs(f64(A)) @ np.abs(f64(B)).T)
+    assert np.all(np.abs(f64(Cd) - ref) <= bound)
 
 
 @pytest.mark.parametrize("layout", [(1, 1), (1, 0), (0, 0)])
