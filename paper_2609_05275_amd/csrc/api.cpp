@@ -1652,7 +1652,6 @@ int ld_stack_decode(const ld_config* cfg, int32_t n_layers, const ld_weights* w,
     at.dh = static_cast<int32_t>(D.dh);
     at.n_new = n_new;
     at.pos = pos;
-    at.n_chunks = static_cast<int32_t>(dec_chunks(static_cast<int64_t>(pos) + n_new));
     at.scale = static_cast<float>(1.0 / std::sqrt(static_cast<double>(D.dh)));
     at.alibi = D.kind == LD_BLOCK_ALIBI_RELU2;
     {
@@ -1934,7 +1933,6 @@ int ld_attn_decode(int32_t n_seq, int32_t n_heads, int32_t d_head, int32_t alibi
   at.dh = d_head;
   at.n_new = n_new;
   at.pos = pos;
-  at.n_chunks = static_cast<int32_t>(dec_chunks(static_cast<int64_t>(pos) + n_new));
   at.scale = static_cast<float>(1.0 / std::sqrt(static_cast<double>(d_head)));
   at.alibi = alibi;
   hipError_t e = launch_attn_decode(at, as_stream(stream));

@@ -16,15 +16,10 @@
 // write back and invalidate the per-XCD L2 and cost far more than the
 // second launch.)
 //
-// Decode attention: one workgroup per (256-key chunk, head, sequence), a
-// wave per 64 keys.  Scores in base 2 with the causal cut (key <= query
-// position) and the ALiBi bias: for one query row, dh/8 lanes per key, each
-// with 8 of the head's dimensions, summed by lane exchanges; for several
-// rows, S^T = K Q^T on the matrix cores (the rows padded to 16 columns).
-// Softmax statistics per query row over the chunk, then P V with dh/8 lanes
-// per key (16-byte coalesced value reads), summed over the wave's keys by
-// lane exchanges and over the four waves in LDS.  A combine kernel merges
-// the chunks with the usual max/sum rescaling and writes bf16.
+// Decode attention: one workgroup per (chunk of keys, head, sequence), scores
+// in base 2 with the causal cut (key <= query position) and the ALiBi bias.  A
+// combine kernel merges the chunks with the usual max/sum rescaling and writes
+// bf16; a single chunk writes its result itself.
 #include "ld_internal.h"
 
 namespace ld {
@@ -490,199 +485,220 @@ __global__ __launch_bounds__(256) void ld_kv_store_k(KvArgs a) {
 
 // ------------------------------------------------------ decode attention
 
-// NQ >= n_new query rows per sequence (1, 2, 4 or 8).  A wave covers 64 keys
-// of the chunk: DH/8 lanes per key row, 8 dimensions (16 bytes) each, so a
-// pass covers 64/(DH/8) keys and all passes' loads are issued before any
-// arithmetic.
-template <int DH, int NQ>
-__global__ __launch_bounds__(256) void ld_attn_decode_bf16(DecAttnArgs a) {
-  constexpr int LPK = DH / 8;    // lanes per key row
-  constexpr int KPP = 64 / LPK;  // keys per pass
-  constexpr int NP = 64 / KPP;   // passes per wave
-  __shared__ float sc[NQ][kDecKeys + 1];  // + 1: the MFMA path's rows in different banks
-  __shared__ float red[4][NQ][DH];
+// A workgroup takes a chunk of 64 KB keys of one head and sequence, each of
+// its eight waves 8 KB of them from load to weighted sum on its own; the
+// waves meet once, to add up.  Bound by the cache stream: all loads of a
+// wave, keys and values, go out before anything waits, so what it holds in
+// registers is what it has in flight (32 keys at most: two workgroups fit a
+// CU).
+//
+// Scores S^T = K Q^T on the matrix cores (16x16x32), 8 keys a time.  Lane l
+// loads 16 bytes of key l % 8 at dimension 64 s + 32 ((l / 8) % 2) + 8 (l / 16),
+// so an instruction takes 8 whole 128-byte lines (the load cost goes by the
+// lines touched).  As A operand its lanes hold the keys twice, rows 0-7 with
+// dimensions 0-31 of the 64 and rows 8-15 with 32-63, so each load feeds two
+// products, against the query rows' (B operand, row l % 16, rows past n_new
+// repeating the last) first and last 32 dimensions.  Of a product's 4 keys per
+// lane, lanes l and l ^ 32 add up two each: lane group g = l / 16 ends with
+// keys 4 (g % 2) + 2 (g / 2) + t, t < 2, of the 8.
+//
+// The values are loaded to match: group g's lanes hold those keys' rows, DH/16
+// dimensions each.  Several query rows: P is then the A operand and V the B
+// operand of v_mfma_f32_16x16x4_f32 (float32 in, nothing rounded) as they
+// stand, column n of product e being dimension n DH/16 + e.  One query row:
+// every lane has its key's probability, and multiplies it in itself.
+//
+// The split of the cache into chunks is dec_attn_blocks's.  Measured per layer
+// of 16 heads of 128, before -> now: one row over 778 keys 9.2 -> 4.3 us; six
+// rows of 8 sequences over 1506 keys 34.2 -> 27.5 us (3.6 TB/s of cache); one
+// row of 8 sequences over 2048 keys 27.4 -> 28.4 us (4.7 TB/s, what a large copy
+// reaches), its combine 5.5 -> 4.6.  Before, waves of
+// 64 keys loaded the values after the scores, the probabilities went through
+// LDS, and the sum over keys through lane exchanges.
+template <int DH, int NQ, int KB>
+__global__ __launch_bounds__(512) void ld_attn_decode_bf16(DecAttnArgs a) {
+  constexpr int EPL = DH / 16;  // dimensions per lane of a value row
+  typedef __bf16 VRow __attribute__((ext_vector_type(EPL)));
+  __shared__ float ml[8][NQ][2];
+  __shared__ __align__(16) float red[8][NQ][DH];
   const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int kg = lane / LPK, sl = lane % LPK;
-  const int d = a.H * DH;
-  const int64_t row2 = 2ll * d;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, g = lane >> 4;
+  const int64_t d = static_cast<int64_t>(a.H) * DH, row2 = 2 * d;
   const int nk = a.pos + a.n_new;
-  const int k0 = c * kDecKeys + wave * 64;
-  const float al2 = a.alibi ? alibi_slope(h, a.H) * kLog2e : 0.f;
-  const bf16* qkv = static_cast<const bf16*>(a.qkv);
-  const bf16* cache = static_cast<const bf16*>(a.cache) + static_cast<int64_t>(b) * a.s_max * row2;
+  const int k0 = (c * 8 + wave) * 8 * KB;
+  const int kv0 = k0 + 4 * (g & 1) + 2 * (g >> 1);  // the lane's keys: kv0 + 8 kb + t
+  const float al2 = a.alibi ? alibi_slope(h, a.H) * kLog2e : 0.f, sl2 = a.scale * kLog2e;
+  const bf16* q = static_cast<const bf16*>(a.qkv) + h * DH +
+                  (static_cast<int64_t>(b) * a.n_new + min(n, a.n_new - 1)) * a.ld_qkv;
+  const bf16* cache = static_cast<const bf16*>(a.cache) + static_cast<int64_t>(b) * a.s_max * row2 + h * DH;
+
+  // keys past the last position read row 0
+  bf16x8 qf[DH / 64][2], kf[KB][DH / 64];
+  VRow vr[KB][2];
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb) {
+    const int kk = k0 + kb * 8 + (lane & 7);
+    const bf16* kp = cache + static_cast<int64_t>(kk < nk ? kk : 0) * row2 + 32 * ((lane >> 3) & 1) + 8 * g;
+#pragma unroll
+    for (int s = 0; s < DH / 64; ++s) kf[kb][s] = load8(kp + 64 * s);
+  }
+#pragma unroll
+  for (int s = 0; s < DH / 64; ++s)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) qf[s][e] = load8(q + 64 * s + 32 * e + 8 * g);
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int kk = kv0 + 8 * kb + t;
+      vr[kb][t] = *reinterpret_cast<const VRow*>(cache + static_cast<int64_t>(kk < nk ? kk : 0) * row2 + d + EPL * n);
+    }
+  __builtin_amdgcn_sched_barrier(0);  // the value loads stay ahead of the scores
+
+  const int qpos = a.pos + (NQ == 1 ? 0 : n);
+  float p[KB][2];
+  float m = -INFINITY;
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb) {
+    floatx4 s0{0.f, 0.f, 0.f, 0.f}, s1{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < DH / 64; ++s) {
+      s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][s], qf[s][0], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][s], qf[s][1], s1, 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {  // groups 0, 1: rows 0-7 of s0; 2, 3: rows 8-15 of s1
+      const float give = g < 2 ? s0[2 + t] : s1[t], keep = g < 2 ? s0[t] : s1[2 + t];
+      const float x = keep + __shfl_xor(give, 32, 64);
+      const int kk = kv0 + 8 * kb + t;
+      p[kb][t] = (kk < nk && kk <= qpos) ? x * sl2 - al2 * static_cast<float>(qpos - kk) : -INFINITY;
+      m = fmaxf(m, p[kb][t]);
+    }
+  }
+  m = fmaxf(m, __shfl_xor(m, 16, 64));
+  m = fmaxf(m, __shfl_xor(m, 32, 64));
+  float l = 0.f;
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      p[kb][t] = m == -INFINITY ? 0.f : exp2f(p[kb][t] - m);
+      l += p[kb][t];
+    }
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  if (lane < NQ) {
+    ml[wave][lane][0] = m;
+    ml[wave][lane][1] = l;
+  }
 
   if constexpr (NQ == 1) {
-    // one query row: each lane's 8 dimensions of a key, dot products summed
-    // over the key's lanes (keys of rows past the last position read row 0)
-    bf16x8 kr[NP];
+    float o[EPL];
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      const int kk = k0 + p * KPP + kg;
-      kr[p] = load8(cache + static_cast<int64_t>(kk < nk ? kk : 0) * row2 + h * DH + sl * 8);
+    for (int e = 0; e < EPL; ++e) o[e] = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) o[e] = __builtin_fmaf(p[kb][t], static_cast<float>(vr[kb][t][e]), o[e]);
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      o[e] += __shfl_xor(o[e], 16, 64);
+      o[e] += __shfl_xor(o[e], 32, 64);
     }
-    float q[8];
-    {
-      const bf16x8 v = load8(qkv + static_cast<int64_t>(b) * a.ld_qkv + h * DH + sl * 8);
+    if (g == 0)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) q[e] = static_cast<float>(v[e]) * (a.scale * kLog2e);
-    }
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      const int kl = wave * 64 + p * KPP + kg;
-      const int kk = k0 + p * KPP + kg;
-      float s = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s = __builtin_fmaf(q[e], static_cast<float>(kr[p][e]), s);
-#pragma unroll
-      for (int o = LPK / 2; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-      if (sl == 0) sc[0][kl] = (kk < nk && kk <= a.pos) ? s - al2 * static_cast<float>(a.pos - kk) : -INFINITY;
-    }
+      for (int e = 0; e < EPL; ++e) red[wave][0][EPL * n + e] = o[e];
   } else {
-    // several query rows: S^T = K Q^T on the matrix cores (16x16x32), 8 keys a
-    // time.  Lane l loads 16 bytes of key l % 8 at dimension 64 s + 32 ((l / 8)
-    // % 2) + 8 (l / 16), so an instruction takes 8 whole 128-byte lines (32
-    // keys of 32 bytes each took four times as long to issue: the load cost
-    // goes by the lines touched).  As A operand its lanes hold the keys twice,
-    // rows 0-7 with dimensions 0-31 of the 64 and rows 8-15 with 32-63, so
-    // each load feeds two products, against the query rows' (B operand, row
-    // l % 16, zero past n_new) first and last 32 dimensions; the two rows of a
-    // key are added.
-    const int qm = lane & 15, qg = lane >> 4;
-    bf16x8 qf[DH / 64][2], kf[8][DH / 64];
+    floatx4 o[EPL];
 #pragma unroll
-    for (int s = 0; s < DH / 64; ++s)
+    for (int e = 0; e < EPL; ++e) o[e] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int e = 0; e < 2; ++e)
-        qf[s][e] = qm < a.n_new ? load8(qkv + (static_cast<int64_t>(b) * a.n_new + qm) * a.ld_qkv + h * DH + 64 * s +
-                                        32 * e + 8 * qg)
-                                : zero8();
+    for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-    for (int kb = 0; kb < 8; ++kb) {
-      const int kk = k0 + kb * 8 + (lane & 7);
-      const bf16* kp = cache + static_cast<int64_t>(kk < nk ? kk : 0) * row2 + h * DH + 32 * ((lane >> 3) & 1) + 8 * qg;
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int s = 0; s < DH / 64; ++s) kf[kb][s] = load8(kp + 64 * s);
-    }
-    const int qpos = a.pos + qm;
-    const float sl2 = a.scale * kLog2e;
+        for (int e = 0; e < EPL; ++e)
+          o[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[kb][t], static_cast<float>(vr[kb][t][e]), o[e], 0, 0, 0);
+    if (4 * g < NQ)  // the lane's rows 4 g + i
 #pragma unroll
-    for (int kb = 0; kb < 8; ++kb) {
-      floatx4 s0{0.f, 0.f, 0.f, 0.f}, s1{0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int s = 0; s < DH / 64; ++s) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][s], qf[s][0], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][s], qf[s][1], s1, 0, 0, 0);
-      }
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {  // lane groups 0, 1: keys 4 qg + v of s0; 2, 3: of s1
-        const float lo = s0[v], hi = s1[v];
-        float t = qg < 2 ? lo : hi;
-        t += __shfl_xor(t, 32, 64);
-        const int kl = kb * 8 + 4 * qg + v, kk = k0 + kl;
-        if (qg < 2 && qm < a.n_new)
-          sc[qm][wave * 64 + kl] =
-              (kk < nk && kk <= qpos) ? t * sl2 - al2 * static_cast<float>(qpos - kk) : -INFINITY;
-      }
-    }
-  }
-  // values of the same positions, in flight during the softmax
-  bf16x8 vr[NP];
-#pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    const int kk = k0 + p * KPP + kg;
-    vr[p] = load8(cache + static_cast<int64_t>(kk < nk ? kk : 0) * row2 + d + h * DH + sl * 8);
+        for (int e = 0; e < EPL; ++e) red[wave][(4 * g + i) % NQ][EPL * n + e] = o[e][i];
   }
   __syncthreads();
 
-  // per query row: chunk maximum, probabilities, sum
-  const int64_t prow = (static_cast<int64_t>(b) * a.H + h) * a.n_chunks + c;
-  for (int j = wave; j < a.n_new; j += 4) {
-    float m = -INFINITY;
-    for (int i = lane; i < kDecKeys; i += 64) m = fmaxf(m, sc[j][i]);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    float l = 0.f;
-    for (int i = lane; i < kDecKeys; i += 64) {
-      const float pr = m == -INFINITY ? 0.f : exp2f(sc[j][i] - m);
-      sc[j][i] = pr;
-      l += pr;
-    }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) l += __shfl_xor(l, o, 64);
-    if (lane == 0) {
-      a.part_ml[(prow * kDecMaxRows + j) * 2] = m;
-      a.part_ml[(prow * kDecMaxRows + j) * 2 + 1] = l;
-    }
-  }
-  __syncthreads();
-
-  // P V in groups of at most four rows: each lane its key's 8 dimensions,
-  // then a sum over the wave's key groups (lane exchanges) and over the four
-  // waves (LDS, in wave order)
-  constexpr int JG = NQ < 4 ? NQ : 4;
-#pragma unroll 1
-  for (int j0 = 0; j0 < NQ; j0 += JG) {
-    float o[JG][8];
-#pragma unroll
-    for (int j = 0; j < JG; ++j)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) o[j][e] = 0.f;
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      const int kl = wave * 64 + p * KPP + kg;
-#pragma unroll
-      for (int j = 0; j < JG; ++j) {
-        const float pr = j0 + j < a.n_new ? sc[j0 + j][kl] : 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[j][e] = __builtin_fmaf(pr, static_cast<float>(vr[p][e]), o[j][e]);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < JG; ++j)
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-#pragma unroll
-        for (int off = LPK; off < 64; off <<= 1) o[j][e] += __shfl_xor(o[j][e], off, 64);
-    if (kg == 0)
-#pragma unroll
-      for (int j = 0; j < JG; ++j)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) red[wave][j0 + j][sl * 8 + e] = o[j][e];
-  }
-  __syncthreads();
-  for (int e = tid; e < a.n_new * DH; e += 256) {
+  // sum over the waves, in wave order, each scaled to the chunk's maximum
+  for (int e = tid; e < a.n_new * DH; e += 512) {
     const int j = e / DH, col = e % DH;
-    const float s = red[0][j][col] + red[1][j][col] + red[2][j][col] + red[3][j][col];
-    a.part_o[(prow * kDecMaxRows + j) * DH + col] = s;
+    float mw[8], M = -INFINITY, L = 0.f, s = 0.f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) {
+      mw[w] = ml[w][j][0];
+      M = fmaxf(M, mw[w]);
+    }
+#pragma unroll
+    for (int w = 0; w < 8; ++w) {
+      const float f = mw[w] == -INFINITY ? 0.f : exp2f(mw[w] - M);
+      L = __builtin_fmaf(f, ml[w][j][1], L);
+      s = __builtin_fmaf(f, red[w][j][col], s);
+    }
+    if (a.n_chunks == 1) {
+      static_cast<bf16*>(a.out)[(static_cast<int64_t>(b) * a.n_new + j) * d + h * DH + col] =
+          static_cast<bf16>(s * (1.f / L));
+    } else {
+      const int64_t pr = ((static_cast<int64_t>(b) * a.H + h) * a.n_chunks + c) * a.n_new + j;
+      a.part_o[pr * DH + col] = s;
+      if (col == 0) {
+        a.part_ml[pr * 2] = M;
+        a.part_ml[pr * 2 + 1] = L;
+      }
+    }
   }
 }
 
-// One wave per (sequence, head, query row): merge the chunks.
+// One wave per (sequence, head, query row): merge the chunks, eight chunks'
+// partial rows in flight.
 template <int DH>
 __global__ __launch_bounds__(256) void ld_attn_decode_combine(DecAttnArgs a) {
-  constexpr int NQ = kDecMaxRows;   // row stride of the partials
-  constexpr int CL = DH / 64;
+  constexpr int CL = DH / 64, U = 8;
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= a.n_seq * a.H * a.n_new) return;
   const int b = r / (a.H * a.n_new), h = (r / a.n_new) % a.H, j = r % a.n_new;
-  const int64_t p0 = (static_cast<int64_t>(b) * a.H + h) * a.n_chunks;
+  const int64_t p0 = (static_cast<int64_t>(b) * a.H + h) * a.n_chunks * a.n_new + j;  // + c n_new
+  const float* po = a.part_o + p0 * DH + lane * CL;
+  const float* pm = a.part_ml + p0 * 2;
   float M = -INFINITY;
-  for (int c = 0; c < a.n_chunks; ++c) M = fmaxf(M, a.part_ml[((p0 + c) * NQ + j) * 2]);
+  for (int c = lane; c < a.n_chunks; c += 64) M = fmaxf(M, pm[static_cast<int64_t>(c) * a.n_new * 2]);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
   float L = 0.f, acc[CL];
 #pragma unroll
   for (int cc = 0; cc < CL; ++cc) acc[cc] = 0.f;
-  for (int c = 0; c < a.n_chunks; ++c) {
-    const float mc = a.part_ml[((p0 + c) * NQ + j) * 2];
-    const float wgt = mc == -INFINITY ? 0.f : exp2f(mc - M);
-    L = __builtin_fmaf(wgt, a.part_ml[((p0 + c) * NQ + j) * 2 + 1], L);
+  for (int c0 = 0; c0 < a.n_chunks; c0 += U) {
+    float mc[U], lc[U], v[U][CL];
 #pragma unroll
-    for (int cc = 0; cc < CL; ++cc)
-      acc[cc] = __builtin_fmaf(wgt, a.part_o[((p0 + c) * NQ + j) * DH + lane * CL + cc], acc[cc]);
+    for (int u = 0; u < U; ++u) {
+      const int64_t c = static_cast<int64_t>(min(c0 + u, a.n_chunks - 1)) * a.n_new;
+      mc[u] = pm[c * 2];
+      lc[u] = pm[c * 2 + 1];
+#pragma unroll
+      for (int cc = 0; cc < CL; ++cc) v[u][cc] = po[c * DH + cc];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float wgt = c0 + u >= a.n_chunks || mc[u] == -INFINITY ? 0.f : exp2f(mc[u] - M);
+      L = __builtin_fmaf(wgt, lc[u], L);
+#pragma unroll
+      for (int cc = 0; cc < CL; ++cc) acc[cc] = __builtin_fmaf(wgt, v[u][cc], acc[cc]);
+    }
   }
   const float inv = 1.f / L;
-  bf16* out = static_cast<bf16*>(a.out) + (static_cast<int64_t>(b) * a.n_new + j) * (a.H * DH) + h * DH;
+  bf16* out = static_cast<bf16*>(a.out) + (static_cast<int64_t>(b) * a.n_new + j) * (static_cast<int64_t>(a.H) * DH) + h * DH;
 #pragma unroll
   for (int cc = 0; cc < CL; ++cc) out[lane * CL + cc] = static_cast<bf16>(acc[cc] * inv);
 }
@@ -786,12 +802,32 @@ hipError_t launch_kv_store(const KvArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Blocks of 8 keys per wave (1, 2 or 4: chunks of 64, 128 or 256 keys).  Up to
+// 256 keys: one chunk and no second launch.  Beyond, the largest chunk that
+// still gives every CU a workgroup, as far as the partial rows fit the scratch,
+// which is sized for kDecMaxRows rows of 256-key chunks.  One row over 778
+// keys and 16 heads: 64 workgroups of 256 keys -> 208 of 64.
+int dec_attn_blocks(const DecAttnArgs& a) {
+  const int64_t nk = static_cast<int64_t>(a.pos) + a.n_new, rows = static_cast<int64_t>(a.n_seq) * a.H;
+  if (nk <= kDecKeys) return nk <= 64 ? 1 : nk <= 128 ? 2 : 4;
+  int kb = 4;
+  while (kb > 1 && rows * ((nk + 64 * kb - 1) / (64 * kb)) < kDecCus && a.n_new * (4 / (kb / 2)) <= kDecMaxRows) kb /= 2;
+  return kb;
+}
+
 template <int DH, int NQ>
-hipError_t attn_decode_t(const DecAttnArgs& a, hipStream_t s) {
+hipError_t attn_decode_t(DecAttnArgs a, hipStream_t s) {
+  const int kb = dec_attn_blocks(a);
+  a.n_chunks = static_cast<int32_t>((static_cast<int64_t>(a.pos) + a.n_new + 64 * kb - 1) / (64 * kb));
   const dim3 grid(a.n_chunks, a.H, a.n_seq);
-  hipLaunchKernelGGL((ld_attn_decode_bf16<DH, NQ>), grid, dim3(256), 0, s, a);
+  if (kb == 1)
+    hipLaunchKernelGGL((ld_attn_decode_bf16<DH, NQ, 1>), grid, dim3(512), 0, s, a);
+  else if (kb == 2)
+    hipLaunchKernelGGL((ld_attn_decode_bf16<DH, NQ, 2>), grid, dim3(512), 0, s, a);
+  else
+    hipLaunchKernelGGL((ld_attn_decode_bf16<DH, NQ, 4>), grid, dim3(512), 0, s, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || a.n_chunks == 1) return e;
   const int rows = a.n_seq * a.H * a.n_new;
   hipLaunchKernelGGL(ld_attn_decode_combine<DH>, dim3((rows + 3) / 4), dim3(256), 0, s, a);
   return hipGetLastError();
@@ -800,7 +836,6 @@ hipError_t attn_decode_t(const DecAttnArgs& a, hipStream_t s) {
 template <int DH>
 hipError_t attn_decode_dh(const DecAttnArgs& a, hipStream_t s) {
   if (a.n_new <= 1) return attn_decode_t<DH, 1>(a, s);
-  if (a.n_new <= 2) return attn_decode_t<DH, 2>(a, s);
   if (a.n_new <= 4) return attn_decode_t<DH, 4>(a, s);
   return attn_decode_t<DH, 8>(a, s);
 }

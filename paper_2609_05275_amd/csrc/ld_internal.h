@@ -326,16 +326,18 @@ struct KvArgs {
 };
 
 // Decode attention: queries (rows b*n_new + j of qkv, position pos + j) over
-// the cached keys/values of positions 0..pos+n_new-1, in chunks of kDecKeys
-// keys with float32 partials combined by a second kernel.
+// the cached keys/values of positions 0..pos+n_new-1, in chunks of up to
+// kDecKeys keys (n_chunks is the launch's choice) with float32 partials
+// combined by a second kernel.  The scratch holds kDecMaxRows rows of each of
+// the cache's kDecKeys-key chunks.
 struct DecAttnArgs {
   const void* qkv;
   int64_t ld_qkv;
   const void* cache;
   int32_t s_max;
   void* out;        // [n_seq * n_new, H * dh]
-  float* part_o;    // [n_seq][H][n_chunks][kDecMaxRows][dh]
-  float* part_ml;   // [n_seq][H][n_chunks][kDecMaxRows][2]: base-2 max, sum
+  float* part_o;    // [n_seq][H][n_chunks][n_new][dh]
+  float* part_ml;   // [n_seq][H][n_chunks][n_new][2]: base-2 max, sum
   int32_t n_seq, H, dh, n_new, pos, n_chunks;
   float scale;
   int32_t alibi;

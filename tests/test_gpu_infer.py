@@ -175,6 +175,34 @@ def test_attn_decode(dh, H, alibi, pos, n):
         assert rel(got[b * n:(b + 1) * n], want) < 1e-2, b
 
 
+@pytest.mark.parametrize("dh,H", [(64, 4), (128, 3)])
+@pytest.mark.parametrize("B,pos,n", [
+    (2, 62, 2), (2, 63, 2), (2, 126, 2), (2, 125, 4), (2, 128, 1), (2, 254, 2), (2, 255, 4),  # one chunk and its edges
+    (2, 300, 1), (2, 320, 2), (2, 319, 3), (1, 383, 1), (2, 4300, 1), (1, 1023, 4),           # 64- and 128-key chunks
+    (30, 640, 4), (30, 1100, 1), (11, 1100, 2)])                                              # larger ones for more rows
+def test_attn_decode_chunks(dh, H, B, pos, n):
+    """Every chunk size of the decode attention, whole and ragged last chunks,
+    against float64 (bf16 output: 2^-8 of the largest element and less; the
+    probabilities and sums are float32).  The cache ends at the last position
+    and the scratch is exactly what the query asks for."""
+    rng = np.random.default_rng(pos * 31 + n + dh + B)
+    d, s_max = H * dh, pos + n
+    qkv = _rng_bf16(rng, (B * n, 3 * d))
+    kv = _rng_bf16(rng, (B, s_max, 2 * d))
+    kv[:, pos:] = qkv.view(B, n, 3 * d)[:, :, d:]
+    o = torch.zeros(B * n, d, dtype=torch.bfloat16, device=DEV)
+    ws_n = ld.ld_attn_decode_ws_bytes(B, H, dh, s_max)
+    ws = _buf(ws_n + 64)
+    ws[ws_n:] = 77
+    ld.ld_attn_decode(B, H, dh, pos, n, qkv.to(DEV), kv.to(DEV), s_max, o, ws[:ws_n])
+    torch.cuda.synchronize()
+    assert bool((ws[ws_n:] == 77).all())
+    q64, kv64, got = f64(qkv), f64(kv), f64(o)
+    for b in range(B):
+        want = infer.attention_rows(q64[b * n:(b + 1) * n, :d], kv64[b, :, :d], kv64[b, :, d:], pos + np.arange(n), H, None)
+        assert rel(got[b * n:(b + 1) * n], want) < 1e-2, b
+
+
 # ------------------------------------------------------ evaluation form
 
 ACTIVE = {"all": None, "exit": "exit", "skip": "skip"}
