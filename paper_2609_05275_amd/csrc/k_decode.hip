@@ -152,19 +152,22 @@ __device__ __forceinline__ float bf16r(float x) { return static_cast<float>(stat
 // blocks mix the halves and are dropped.  (Dot products on the vector ALU,
 // which this replaces, read every row of A from LDS once per 8 columns: at 8
 // rows the LDS, at one row the padding to 8 rows, cost more than the weights.
-// 1B shape at 8 rows, before -> now: QKV 14.8 -> 9.4 us, gate/up 18.5 -> 11.8,
-// output 6.6 -> 5.1, down 11.6 -> 10.4, 25, 45, 8 and 23 MB of weights.  At 48
-// rows, against split-K GEMMs and their reductions: the four projections with
-// their norms and activation 95 -> 75 us; there every CU reading all the
-// activations is what bounds it, at about 15 bytes a clock.)
+// 1B shape at 8 rows: QKV 14.8 -> 8.4 us, gate/up 18.5 -> 10.9, output 6.6 -> 5.0,
+// down 11.6 -> 10.4, for 25, 45, 8 and 23 MB of weights.  At 48 rows, against
+// split-K GEMMs and their reductions: the four projections with their norms and
+// activation 95 -> 68 us; there every CU reading all the activations is what
+// bounds it, at about 15 bytes a clock.)
 //
 // The waves take interleaved chunks.  ld_gemm_bf16_dec keeps its waves'
 // activations in registers (K <= 2048 at up to 48 rows, 4096 at up to 16):
-// loaded straight from memory in operand layout, normalised there when a gain
-// is given (partial sums of squares per wave, one exchange through LDS), and
-// used for every tile the workgroup takes in turn, so a CU reads A once; the
+// loaded straight from memory in operand layout and used for every tile the workgroup takes in turn, so a CU reads A once; the
 // first two tiles' weights are requested before anything waits where the
-// registers allow.  ld_gemm_bf16_dec_long streams the activations beside the
+// registers allow.  With a gain, RMSNorm costs the operand one multiplication:
+// the sums of squares are the diagonals of x x^T on the matrix cores, exchanged
+// with the first tile's sums, and 1/rms scales the outputs.  (Squares and both
+// scalings on the vector ALU, and a barrier before the first product: QKV and
+// gate/up 19.0 and 25.1 us at 48 rows, now 16.8 and 21.1; 9.4 and 12.0 at 8, now
+// 8.4 and 10.9.)  ld_gemm_bf16_dec_long streams the activations beside the
 // weights.
 //
 // Partial sums go over the waves in wave order through LDS; the epilogue
@@ -200,7 +203,8 @@ __device__ __forceinline__ void dec_put(float* red, const floatx4 (&acc)[NR][MB]
 
 // Element (row em, column en) of the output from the waves' sums.
 template <int MB, int ACT, int NW>
-__device__ __forceinline__ void dec_finish(const SkinnyArgs& g, const float* red, int em, int c, int en, uint16_t resid) {
+__device__ __forceinline__ void dec_finish(const SkinnyArgs& g, const float* red, int em, int c, int en, uint16_t resid,
+                                           float alpha) {
   constexpr int NR = ACT == kDecActSwiglu ? 2 : 1;
   constexpr int kWave = dec_red_floats<MB, NR>();
   const int at = em * kDecCols + c;
@@ -214,12 +218,12 @@ __device__ __forceinline__ void dec_finish(const SkinnyArgs& g, const float* red
   }
   bf16* C = static_cast<bf16*>(g.C) + static_cast<int64_t>(em) * g.ldc + en;
   if constexpr (ACT == kDecActSwiglu) {
-    *C = static_cast<bf16>(swiglu_fwd_f(bf16r(g.alpha * s0), bf16r(g.alpha * s1)));
+    *C = static_cast<bf16>(swiglu_fwd_f(bf16r(alpha * s0), bf16r(alpha * s1)));
   } else if constexpr (ACT == kDecActRelu2) {
-    const float z = fmaxf(bf16r(g.alpha * s0), 0.f);
+    const float z = fmaxf(bf16r(alpha * s0), 0.f);
     *C = static_cast<bf16>(z * z);
   } else {
-    const bf16 o = static_cast<bf16>(g.alpha * s0 + (g.R ? static_cast<float>(__builtin_bit_cast(bf16, resid)) : 0.f));
+    const bf16 o = static_cast<bf16>(alpha * s0 + (g.R ? static_cast<float>(__builtin_bit_cast(bf16, resid)) : 0.f));
     *C = o;
     if (g.kv && en >= g.kv_d) {
       const int64_t b = em / g.kv_n, jj = em % g.kv_n;
@@ -244,6 +248,17 @@ __device__ __forceinline__ void dec_mask(bf16x8& v, bool keep) {
   v = __builtin_bit_cast(bf16x8, t);
 }
 
+// The wave's number.  It decides which chunks a wave takes, so neighbouring
+// workgroups of an XCD (every 8th) count from different waves: started in step,
+// all would ask the same few L2 channels for the same lines of A first.  Sums
+// go by this number, so the results do not depend on it.  QKV and gate/up of
+// the 1B shape: 8.1 -> 7.5 and 11.8 -> 11.1 us at one row, 9.1 -> 8.4 and 11.7 ->
+// 10.8 us at 8.
+template <int NW>
+__device__ __forceinline__ int dec_wave() {
+  return __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) + (blockIdx.x >> 3)) & (NW - 1);
+}
+
 // K <= 64 NW CPW; MB blocks of 8 rows; one thread per output element of a tile
 // (NW * 64 >= 64 MB).
 template <int MB, int ACT, bool NORM, int NW, int CPW>
@@ -253,13 +268,12 @@ __global__ __launch_bounds__(NW * 64) void ld_gemm_bf16_dec(SkinnyArgs g) {
   static_assert(NW * 64 >= MB * 8 * kDecCols, "a thread per output element");
   __shared__ __align__(16) float red[2][kRed];
   __shared__ float ssq[NORM ? NW : 1][MB * 8];
-  __shared__ __align__(16) bf16 gs[NORM ? NW * CPW * 64 : 8];  // the gain
-  static_assert(!NORM || NW * CPW * 64 <= NW * 64 * 8, "one gain chunk per thread");
   // the second tile's weights go out before the normalisation if the registers allow
   constexpr bool kTwo = CPW * NR <= 8;  // two tiles' weights in hand, else one
   constexpr bool kBoth = kTwo && (!NORM || MB <= 2 || NR == 1);
   const int M = g.M, N = g.N, K = g.K;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = dec_wave<NW>();
   const int tiles = (N + kDecCols - 1) / kDecCols;
   const int lk = 32 * ((lane >> 3) & 1) + 8 * (lane >> 4);  // the lane's k of a chunk
   const bf16* W = static_cast<const bf16*>(g.W);
@@ -290,8 +304,15 @@ __global__ __launch_bounds__(NW * 64) void ld_gemm_bf16_dec(SkinnyArgs g) {
     r1 = dec_resid(g, em, (blockIdx.x + gridDim.x) * kDecCols + c);
   }
 
-  // this wave's activations in operand layout (rows past M repeat the last)
-  bf16x8 x[CPW][MB];
+  // this wave's gains and activations in operand layout (rows past M repeat the last)
+  bf16x8 gv[CPW], x[CPW][MB];
+  if constexpr (NORM) {
+#pragma unroll
+    for (int u = 0; u < CPW; ++u) {
+      const int k = (wave + NW * u) * 64 + lk;
+      gv[u] = load8(static_cast<const bf16*>(g.g) + (k < K ? k : 0));
+    }
+  }
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     const bf16* xr = static_cast<const bf16*>(g.A) + static_cast<int64_t>(min(mb * 8 + (lane & 7), M - 1)) * g.lda;
@@ -308,46 +329,31 @@ __global__ __launch_bounds__(NW * 64) void ld_gemm_bf16_dec(SkinnyArgs g) {
       for (int mb = 0; mb < MB; ++mb) dec_mask(x[u][mb], (wave + NW * u) * 64 + lk < K);
     }
   if constexpr (NORM) {
-    if (8 * tid < NW * CPW * 64)
-      *reinterpret_cast<bf16x8*>(gs + 8 * tid) =
-          8 * tid < K ? load8(static_cast<const bf16*>(g.g) + 8 * tid) : zero8();
+    // Sums of squares from the products of the rows with themselves (the
+    // diagonals of the two blocks); the gain goes on the operand, 1/rms on the
+    // outputs, so nothing here waits for the other waves.
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
-      float ss = 0.f;
+      floatx4 q{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int u = 0; u < CPW; ++u)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float f = static_cast<float>(x[u][mb][i]);
-          ss = __builtin_fmaf(f, f, ss);
-        }
-#pragma unroll
-      for (int o = 8; o < 64; o <<= 1) ss += __shfl_xor(ss, o, 64);
-      if (lane < 8) ssq[wave][mb * 8 + lane] = ss;
-    }
-    __syncthreads();
-    float rstd[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      float tot = 0.f;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) tot += ssq[w][mb * 8 + (lane & 7)];
-      rstd[mb] = rsqrtf(tot / static_cast<float>(K) + g.eps);
+      for (int u = 0; u < CPW; ++u) q = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[u][mb], x[u][mb], q, 0, 0, 0);
+      // lane l: D rows 4 (l / 16) + e of column l % 16
+      const int e = lane & 3;
+      float ss = e == 0 ? q[0] : e == 1 ? q[1] : e == 2 ? q[2] : q[3];
+      ss += __shfl_xor(ss, 40, 64);
+      if ((lane & 40) == 0 && (lane & 15) >> 2 == lane >> 4) ssq[wave][mb * 8 + (lane & 7)] = ss;
     }
 #pragma unroll
     for (int u = 0; u < CPW; ++u) {
-      const bf16x8 gv = load8(gs + (wave + NW * u) * 64 + lk);
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        // opaque here, or the float32 values squared above are kept for this
-        int4v xi = __builtin_bit_cast(int4v, x[u][mb]);
-        asm volatile("" : "+v"(xi));
-        const bf16x8 xv = __builtin_bit_cast(bf16x8, xi);
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-          x[u][mb][i] = static_cast<bf16>(static_cast<float>(xv[i]) * rstd[mb] * static_cast<float>(gv[i]));
+          x[u][mb][i] = static_cast<bf16>(static_cast<float>(x[u][mb][i]) * static_cast<float>(gv[u][i]));
+      if ((wave + NW * u) * 64 + 64 > K) {  // wave-uniform
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) dec_mask(x[u][mb], (wave + NW * u) * 64 + lk < K);
       }
-      __builtin_amdgcn_sched_barrier(0);  // a chunk at a time: all chunks' gains at once would spill
     }
   }
   if (kTwo && !kBoth) load_w(w1, blockIdx.x + gridDim.x);
@@ -355,6 +361,7 @@ __global__ __launch_bounds__(NW * 64) void ld_gemm_bf16_dec(SkinnyArgs g) {
   // one tile: products, the request of the buffer's next tile, the waves' sums
   // into red[buf], and after the barrier the outputs (the other buffer's
   // readers are past the barrier before it is written again)
+  float scale = g.alpha;
   auto do_tile = [&](WBuf& wb, int tile, int next, int buf, uint16_t& resid) {
     floatx4 acc[NR][MB];
 #pragma unroll
@@ -381,7 +388,15 @@ __global__ __launch_bounds__(NW * 64) void ld_gemm_bf16_dec(SkinnyArgs g) {
     dec_put<MB, NR>(red[buf] + wave * dec_red_floats<MB, NR>(), acc, lane);
     __syncthreads();
     const int en = tile * kDecCols + c;
-    if (erow && en < N) dec_finish<MB, ACT, NW>(g, red[buf], em, c, en, r);
+    if (erow && en < N) {
+      if (NORM && tile == static_cast<int>(blockIdx.x)) {
+        float tot = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) tot += ssq[w][em];
+        scale = g.alpha * rsqrtf(tot / static_cast<float>(K) + g.eps);
+      }
+      dec_finish<MB, ACT, NW>(g, red[buf], em, c, en, r, scale);
+    }
   };
   const int step = gridDim.x;
   if constexpr (kTwo) {
@@ -403,7 +418,8 @@ __global__ __launch_bounds__(NW * 64) void ld_gemm_bf16_dec_long(SkinnyArgs g) {
   static_assert(NW * 64 >= MB * 8 * kDecCols, "a thread per output element");
   __shared__ __align__(16) float red[NW * dec_red_floats<MB, NR>()];
   const int M = g.M, N = g.N, K = g.K;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = dec_wave<NW>();
   const int lk = 32 * ((lane >> 3) & 1) + 8 * (lane >> 4);
   const int col = min(blockIdx.x * kDecCols + (lane & 7), N - 1);  // columns past N repeat the last
   const bf16 *wrow[NR], *xrow[MB];
@@ -465,7 +481,7 @@ __global__ __launch_bounds__(NW * 64) void ld_gemm_bf16_dec_long(SkinnyArgs g) {
   }
   dec_put<MB, NR>(red + wave * dec_red_floats<MB, NR>(), acc, lane);
   __syncthreads();
-  if (eval) dec_finish<MB, ACT, NW>(g, red, em, c, en, resid);
+  if (eval) dec_finish<MB, ACT, NW>(g, red, em, c, en, resid, g.alpha);
 }
 
 // ------------------------------------------------------------ KV store

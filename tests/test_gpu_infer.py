@@ -118,6 +118,35 @@ def test_gemm_dec(M, N, K, mode):
     assert rel(f64(outs[0]), want) < 1e-2
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 40, 64), (3, 264, 200), (8, 2056, 2048), (7, 520, 4096), (8, 24, 4088)])
+@pytest.mark.parametrize("act", [0, 1])
+def test_gemm_dec_norm_row_scales(M, N, K, act):
+    """RMSNorm fused into the decoding projection, rows of very different size
+    (one below sqrt(eps), where eps decides, one all zeros when there are
+    several), against float64 row by row.  Per output: gain products and stored
+    u, v round to bf16 (2^-9 each), so 1e-2 of the row's largest."""
+    rng = np.random.default_rng(M + N + K + act)
+    scale = 10.0 ** np.linspace(-4, 4, M)[:, None]
+    if M > 1:
+        scale[M // 2] = 0.0
+    A = _bf16(rng.standard_normal((M, K)) * scale)
+    W = _rng_bf16(rng, (2 * N if act else N, K), 0.05)
+    G = _bf16(1.0 + 0.2 * rng.standard_normal(K))
+    C = torch.full((M, N), 3.0, dtype=torch.bfloat16, device=DEV)
+    ld.ld_gemm_dec(A.to(DEV), W.to(DEV), C, g=G.to(DEV), eps=1e-5, alpha=0.75,
+                   act=ld.DEC_ACT_SWIGLU if act else ld.DEC_ACT_NONE)
+    torch.cuda.synchronize()
+    a, _ = block.rmsnorm(f64(A), f64(G), 1e-5)
+    y = 0.75 * (a @ f64(W).T)
+    want = block.silu(y[:, :N]) * y[:, N:] if act else y
+    got = f64(C)
+    for m in range(M):
+        if scale[m] == 0.0:
+            assert not got[m].any()
+        else:
+            assert rel(got[m], want[m]) < 1e-2, m
+
+
 def test_gemm_dec_rejects():
     A = torch.zeros(9, 64, dtype=torch.bfloat16, device=DEV)
     W = torch.zeros(32, 64, dtype=torch.bfloat16, device=DEV)
