@@ -675,48 +675,53 @@ __global__ __launch_bounds__(512) void ld_attn_decode_bf16(DecAttnArgs a) {
   }
 }
 
-// One wave per (sequence, head, query row): merge the chunks, eight chunks'
-// partial rows in flight.
+// One wave per (sequence, head, query row): merge the chunks, up to 16 at
+// once so that their partial rows are all in flight, rescaling what was summed
+// before to the new maximum.  13 chunks of 16 rows (one sequence of 778 keys): 3.8 ->
+// 3.0 us.
 template <int DH>
 __global__ __launch_bounds__(256) void ld_attn_decode_combine(DecAttnArgs a) {
-  constexpr int CL = DH / 64, U = 8;
+  constexpr int CL = DH / 64, U = 16;
+  typedef float FRow __attribute__((ext_vector_type(CL)));
   const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int r = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   if (r >= a.n_seq * a.H * a.n_new) return;
   const int b = r / (a.H * a.n_new), h = (r / a.n_new) % a.H, j = r % a.n_new;
   const int64_t p0 = (static_cast<int64_t>(b) * a.H + h) * a.n_chunks * a.n_new + j;  // + c n_new
   const float* po = a.part_o + p0 * DH + lane * CL;
   const float* pm = a.part_ml + p0 * 2;
-  float M = -INFINITY;
-  for (int c = lane; c < a.n_chunks; c += 64) M = fmaxf(M, pm[static_cast<int64_t>(c) * a.n_new * 2]);
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
-  float L = 0.f, acc[CL];
-#pragma unroll
-  for (int cc = 0; cc < CL; ++cc) acc[cc] = 0.f;
+  float M = -INFINITY, L = 0.f;
+  FRow acc = 0.f;
   for (int c0 = 0; c0 < a.n_chunks; c0 += U) {
-    float mc[U], lc[U], v[U][CL];
+    FRow v[U];
+    float mc[U], lc[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < U; ++u) {  // past the last chunk: the last again, dropped below
       const int64_t c = static_cast<int64_t>(min(c0 + u, a.n_chunks - 1)) * a.n_new;
+      v[u] = *reinterpret_cast<const FRow*>(po + c * DH);
       mc[u] = pm[c * 2];
       lc[u] = pm[c * 2 + 1];
-#pragma unroll
-      for (int cc = 0; cc < CL; ++cc) v[u][cc] = po[c * DH + cc];
     }
     __builtin_amdgcn_sched_barrier(0);
+    float m = M;
+#pragma unroll
+    for (int u = 0; u < U; ++u) m = fmaxf(m, mc[u]);
+    const float keep = M == -INFINITY ? 0.f : exp2f(M - m);
+    L *= keep;
+    acc *= keep;
+    M = m;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const float wgt = c0 + u >= a.n_chunks || mc[u] == -INFINITY ? 0.f : exp2f(mc[u] - M);
+      const float wgt = c0 + u >= a.n_chunks || mc[u] == -INFINITY ? 0.f : exp2f(mc[u] - m);
       L = __builtin_fmaf(wgt, lc[u], L);
-#pragma unroll
-      for (int cc = 0; cc < CL; ++cc) acc[cc] = __builtin_fmaf(wgt, v[u][cc], acc[cc]);
+      acc += wgt * v[u];
     }
   }
-  const float inv = 1.f / L;
-  bf16* out = static_cast<bf16*>(a.out) + (static_cast<int64_t>(b) * a.n_new + j) * (static_cast<int64_t>(a.H) * DH) + h * DH;
+  acc *= 1.f / L;
+  bf16* out = static_cast<bf16*>(a.out) + (static_cast<int64_t>(b) * a.n_new + j) * (static_cast<int64_t>(a.H) * DH) +
+              h * DH + lane * CL;
 #pragma unroll
-  for (int cc = 0; cc < CL; ++cc) out[lane * CL + cc] = static_cast<bf16>(acc[cc] * inv);
+  for (int cc = 0; cc < CL; ++cc) out[cc] = static_cast<bf16>(acc[cc]);
 }
 
 int grid_for(int64_t items) {
