@@ -335,10 +335,38 @@ def _attn_ref(qkv, n, S, H, dh, alibi=0):
     return q64, outs, probs
 
 
+@pytest.mark.parametrize("S,dh", [(40, 16), (70, 32), (33, 64)])
+def test_attention_f32_masked_infinities(S, dh):
+    """float32: what the causal mask cuts off is not multiplied, so an infinite
+    last key and value leave the outputs and dQ of all earlier rows as they
+    are, bit for bit."""
+    n, H = 1, 2
+    d = H * dh
+    g = torch.Generator().manual_seed(S)
+    qkv, go = torch.randn(S, 3 * d, generator=g), torch.randn(S, d, generator=g)
+    outs = []
+    for inf in (False, True):
+        q = qkv.clone()
+        if inf:
+            q[-1, d:] = float("inf")
+        qd, god = q.to(DEV), go.to(DEV)
+        o, gq = torch.empty(S, d, device=DEV), torch.empty(S, 3 * d, device=DEV)
+        lse = torch.empty(n, H, S, device=DEV)
+        ws = torch.empty(ld.ld_attn_bwd_ws_bytes(n, S, H), dtype=torch.uint8, device=DEV)
+        ld.ld_attn_fwd(n, S, H, dh, qd, o, lse)
+        ld.ld_attn_bwd(n, S, H, dh, qd, o, lse, god, gq, ws)
+        torch.cuda.synchronize()
+        outs.append((o[:-1].cpu(), lse[..., :-1].cpu(), gq[:-1, :d].cpu()))
+    for a, b in zip(*outs):
+        assert bool(torch.isfinite(b).all()) and torch.equal(a, b)
+
+
 @pytest.mark.parametrize("alibi", [0, 1])
 @pytest.mark.parametrize("dt,n,S,H,dh", [("bf16", 2, 64, 2, 128), ("bf16", 2, 192, 2, 64), ("bf16", 2, 256, 2, 128),
                                          ("bf16", 1, 1024, 1, 128), ("bf16", 1, 512, 6, 128),
-                                         ("f32", 3, 32, 4, 16), ("f32", 2, 100, 2, 64)])
+                                         ("f32", 3, 32, 4, 16), ("f32", 2, 100, 2, 64), ("f32", 2, 1, 2, 16),
+                                         ("f32", 2, 15, 3, 32), ("f32", 1, 17, 2, 64), ("f32", 2, 65, 2, 32),
+                                         ("f32", 1, 128, 2, 16), ("f32", 1, 193, 2, 32)])
 def test_attention_fwd_bwd(dt, n, S, H, dh, alibi):
     d = H * dh
     g = torch.Generator().manual_seed(5)
