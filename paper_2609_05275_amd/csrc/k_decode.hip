@@ -526,7 +526,7 @@ __global__ __launch_bounds__(256) void ld_kv_store_k(KvArgs a) {
 //
 // The split of the cache into chunks is dec_attn_blocks's.  Measured per layer
 // of 16 heads of 128, before -> now: one row over 778 keys 9.2 -> 4.3 us; six
-// rows of 8 sequences over 1506 keys 34.2 -> 27.5 us (3.6 TB/s of cache); one
+// rows of 8 sequences over 1506 keys 34.2 -> 23.3 us (4.2 TB/s of cache); one
 // row of 8 sequences over 2048 keys 27.4 -> 28.4 us (4.7 TB/s, what a large copy
 // reaches), its combine 5.5 -> 4.6.  Before, waves of
 // 64 keys loaded the values after the scores, the probabilities went through
@@ -823,17 +823,31 @@ hipError_t launch_kv_store(const KvArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Blocks of 8 keys per wave (1, 2 or 4: chunks of 64, 128 or 256 keys).  Up to
-// 256 keys: one chunk and no second launch.  Beyond, the largest chunk that
-// still gives every CU a workgroup, as far as the partial rows fit the scratch,
-// which is sized for kDecMaxRows rows of 256-key chunks.  One row over 778
-// keys and 16 heads: 64 workgroups of 256 keys -> 208 of 64.
+// Blocks of 8 keys per wave (1 to 4: chunks of 64 to 256 keys).  Up to 256
+// keys: one chunk and no second launch.  Beyond, what costs least: rounds of
+// two workgroups per CU (what the registers of the largest chunks admit), each
+// its keys and about another 64 keys' worth of start and end; at equal cost the
+// largest chunk.  The partial rows must fit the scratch, which is sized for
+// kDecMaxRows rows of 256-key chunks.  One row over 778 keys and 16 heads takes
+// 208 workgroups of 64 keys (64 of 256: 9.2 us, now 4.2); six rows of 8
+// sequences over 1506 keys take 1024 of 192, two full rounds (768 of 256, one
+// and a half: 27.4 us, now 23.3).
 int dec_attn_blocks(const DecAttnArgs& a) {
-  const int64_t nk = static_cast<int64_t>(a.pos) + a.n_new, rows = static_cast<int64_t>(a.n_seq) * a.H;
-  if (nk <= kDecKeys) return nk <= 64 ? 1 : nk <= 128 ? 2 : 4;
-  int kb = 4;
-  while (kb > 1 && rows * ((nk + 64 * kb - 1) / (64 * kb)) < kDecCus && a.n_new * (4 / (kb / 2)) <= kDecMaxRows) kb /= 2;
-  return kb;
+  const int64_t nk = static_cast<int64_t>(a.pos) + a.n_new, heads = static_cast<int64_t>(a.n_seq) * a.H;
+  const int64_t scratch_rows = (nk + kDecKeys - 1) / kDecKeys * kDecMaxRows;
+  if (nk <= kDecKeys) return static_cast<int>((nk + 63) / 64);
+  int best = 4;
+  int64_t best_cost = INT64_MAX;
+  for (int kb = 4; kb >= 1; --kb) {
+    const int64_t chunks = (nk + 64 * kb - 1) / (64 * kb);
+    if (chunks * a.n_new > scratch_rows) break;
+    const int64_t cost = (heads * chunks + 2 * kDecCus - 1) / (2 * kDecCus) * (kb + 1);
+    if (cost < best_cost) {
+      best = kb;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
 template <int DH, int NQ>
@@ -845,6 +859,8 @@ hipError_t attn_decode_t(DecAttnArgs a, hipStream_t s) {
     hipLaunchKernelGGL((ld_attn_decode_bf16<DH, NQ, 1>), grid, dim3(512), 0, s, a);
   else if (kb == 2)
     hipLaunchKernelGGL((ld_attn_decode_bf16<DH, NQ, 2>), grid, dim3(512), 0, s, a);
+  else if (kb == 3)
+    hipLaunchKernelGGL((ld_attn_decode_bf16<DH, NQ, 3>), grid, dim3(512), 0, s, a);
   else
     hipLaunchKernelGGL((ld_attn_decode_bf16<DH, NQ, 4>), grid, dim3(512), 0, s, a);
   hipError_t e = hipGetLastError();

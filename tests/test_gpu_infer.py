@@ -208,6 +208,7 @@ def test_attn_decode(dh, H, alibi, pos, n):
 @pytest.mark.parametrize("B,pos,n", [
     (2, 62, 2), (2, 63, 2), (2, 126, 2), (2, 125, 4), (2, 128, 1), (2, 254, 2), (2, 255, 4),  # one chunk and its edges
     (2, 300, 1), (2, 320, 2), (2, 319, 3), (1, 383, 1), (2, 4300, 1), (1, 1023, 4),           # 64- and 128-key chunks
+    (2, 180, 1), (2, 190, 2), (2, 190, 3), (43, 1100, 6), (43, 1146, 6),                      # 192-key chunks
     (30, 640, 4), (30, 1100, 1), (11, 1100, 2)])                                              # larger ones for more rows
 def test_attn_decode_chunks(dh, H, B, pos, n):
     """Every chunk size of the decode attention, whole and ragged last chunks,
