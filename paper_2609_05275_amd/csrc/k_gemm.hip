@@ -764,7 +764,7 @@ __device__ __forceinline__ void epilogue_rows_edge(const GemmArgs& g, float* par
   }
 }
 
-constexpr int kEpiPlain = 0, kEpiGluFwd = 1, kEpiGluBwd = 2, kEpiRelu2Fwd = 3, kEpiRelu2Bwd = 4;
+constexpr int kEpiPlain = 0, kEpiGluFwd = 1, kEpiGluBwd = 2, kEpiRelu2Fwd = 3, kEpiRelu2Bwd = 4, kEpiKv = 5;
 
 __device__ __forceinline__ uint2 pack4_bf16(float a, float b, float c, float d) {
   __attribute__((aligned(8))) bf16 o[4] = {static_cast<bf16>(a), static_cast<bf16>(b), static_cast<bf16>(c),
@@ -828,7 +828,7 @@ __device__ __forceinline__ void glu_bwd_rows(const GemmArgs& g, const float* sta
 }
 
 // Fused squared-ReLU forward: staged values (alpha applied) of rows r0 + 2 it,
-// columns n..n+3, go to C as u (bf16, kept for the backward) and to aux as
+// columns n..n+3, go to C (if given) as u (bf16, kept for the backward) and to aux as
 // s = relu(u)^2 of the float32 u (one rounding fewer than from a stored u).
 __device__ __forceinline__ void relu2_fwd_one(const GemmArgs& g, float4 v, int64_t m, int n) {
   const float u[4] = {v.x, v.y, v.z, v.w};
@@ -838,7 +838,7 @@ __device__ __forceinline__ void relu2_fwd_one(const GemmArgs& g, float4 v, int64
     const float z = fmaxf(u[e], 0.f);
     q[e] = z * z;
   }
-  *reinterpret_cast<uint2*>(static_cast<bf16*>(g.C) + m * g.ldc + n) = pack4_bf16(u[0], u[1], u[2], u[3]);
+  if (g.C) *reinterpret_cast<uint2*>(static_cast<bf16*>(g.C) + m * g.ldc + n) = pack4_bf16(u[0], u[1], u[2], u[3]);
   *reinterpret_cast<uint2*>(static_cast<bf16*>(g.aux) + m * g.glu_f + n) = pack4_bf16(q[0], q[1], q[2], q[3]);
 }
 
@@ -1108,27 +1108,29 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
       for (int i = 0; i < 2; ++i) {
         const int mb = m0 + wm * 64 + i * 32;
         if (mb >= M) break;
+        if (C) {  // [u v], unless nothing reads them later
 #pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
+          for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-          for (int j = 0; j < NJ; ++j) {
-            const floatx4& a = acc[2 * i + ii][j];
-            *reinterpret_cast<uint2*>(st16 + (16 * ii + l16) * SH::Pitch + j * 16 + q16) =
-                pack4_bf16(alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]);
+            for (int j = 0; j < NJ; ++j) {
+              const floatx4& a = acc[2 * i + ii][j];
+              *reinterpret_cast<uint2*>(st16 + (16 * ii + l16) * SH::Pitch + j * 16 + q16) =
+                  pack4_bf16(alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]);
+            }
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          // staged columns below GW are gate (u) columns, the others up (v) columns
+          const int gcol = cc < GW ? f0 + cc : g.glu_f + f0 + cc - GW;
+#pragma unroll
+          for (int k = 0; k < LU / 2; ++k) {
+            const int row = 64 / LU * k + rr;
+            const bf16* src = st16 + row * SH::Pitch + cc;
+            const uint2 lo = *reinterpret_cast<const uint2*>(src), hi = *reinterpret_cast<const uint2*>(src + 4);
+            if (mb + row < M)
+              *reinterpret_cast<uint4*>(C + static_cast<int64_t>(mb + row) * g.ldc + gcol) =
+                  make_uint4(lo.x, lo.y, hi.x, hi.y);
           }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        // staged columns below GW are gate (u) columns, the others up (v) columns
-        const int gcol = cc < GW ? f0 + cc : g.glu_f + f0 + cc - GW;
-#pragma unroll
-        for (int k = 0; k < LU / 2; ++k) {
-          const int row = 64 / LU * k + rr;
-          const bf16* src = st16 + row * SH::Pitch + cc;
-          const uint2 lo = *reinterpret_cast<const uint2*>(src), hi = *reinterpret_cast<const uint2*>(src + 4);
-          if (mb + row < M)
-            *reinterpret_cast<uint4*>(C + static_cast<int64_t>(mb + row) * g.ldc + gcol) =
-                make_uint4(lo.x, lo.y, hi.x, hi.y);
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         // s = silu(u) v from the float32 accumulators (see below)
 #pragma unroll
         for (int ii = 0; ii < 2; ++ii)
@@ -1156,7 +1158,7 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
       return;
     }
   }
-  if constexpr (EPI == kEpiPlain) {
+  if constexpr (EPI == kEpiPlain || EPI == kEpiKv) {
     if (!part && !g.R && !g.c_f32 && !g.out_map.idx && full_cols) {
       bf16* st16 = reinterpret_cast<bf16*>(stage);
       constexpr int LU = WC / 8;                       // lanes per row
@@ -1190,6 +1192,17 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
 #pragma unroll
         for (int k = 0; k < LU / 2; ++k)
           *reinterpret_cast<uint4*>(C + static_cast<int64_t>(mb + 64 / LU * k + rr) * g.ldc + n0 + wn * WC + cc) = v[k];
+        if constexpr (EPI == kEpiKv) {
+          // the key and value columns once more, into the cache; S % 32 == 0,
+          // so the block row lies in one sequence
+          const int col = n0 + wn * WC + cc - g.kv_d, b = mb / g.kv_S;
+          if (col >= 0) {
+            bf16* kv = static_cast<bf16*>(g.kv) + (static_cast<int64_t>(b) * g.kv_s_max + mb - b * g.kv_S) * 2 * g.kv_d + col;
+#pragma unroll
+            for (int k = 0; k < LU / 2; ++k)
+              *reinterpret_cast<uint4*>(kv + static_cast<int64_t>(64 / LU * k + rr) * 2 * g.kv_d) = v[k];
+          }
+        }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // reads done before the block is rewritten
       }
       return;
@@ -1258,6 +1271,19 @@ LD_BIG_ATTRS void ld_gemm_bf16_nt_glu_128(GemmArgs g) {
 LD_BIG_ATTRS void ld_gemm_bf16_nt_relu2_128(GemmArgs g) {
   __shared__ __align__(16) bf16 ring[kRingElems];
   gemm_big_body<true, true, kEpiRelu2Fwd, 128>(g, ring, blockIdx.x, gridDim.x, 0, 1);
+}
+
+// The QKV projection of an evaluation with a cache: key and value columns also
+// go there (see GemmArgs).  3264 x 6144 x 2048: 89.9 -> 90.4 us, in place of a
+// launch of 9.7 us that read them back; a kernel of its own, so the other plain
+// GEMMs' registers and code stay as they are.
+LD_BIG_ATTRS void ld_gemm_bf16_nt_kv_256(GemmArgs g) {
+  __shared__ __align__(16) bf16 ring[kRingElems];
+  gemm_big_body<true, true, kEpiKv>(g, ring, blockIdx.x, gridDim.x, 0, 1);
+}
+LD_BIG_ATTRS void ld_gemm_bf16_nt_kv_128(GemmArgs g) {
+  __shared__ __align__(16) bf16 ring[kRingElems];
+  gemm_big_body<true, true, kEpiKv, 128>(g, ring, blockIdx.x, gridDim.x, 0, 1);
 }
 
 // Up to three GEMMs in one launch: weight-gradient GEMMs g1 (tiles1 tiles,
@@ -1406,6 +1432,13 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
   return p;
 }
 
+// Whole block rows and columns only (an edge is stored on another path), and
+// 16-byte pieces that stay within the key and value columns.
+bool gemm_stores_kv(const GemmPlan& p, const GemmArgs& g) {
+  return p.big && !g.R && !g.c_f32 && !g.dev_count && !g.out_map.idx && g.N % GB == 0 && g.kv_d % 8 == 0 &&
+         g.N == 3 * g.kv_d && g.kv_S % 32 == 0 && g.M % 32 == 0 && reinterpret_cast<uintptr_t>(g.kv) % 16 == 0;
+}
+
 size_t gemm_part_bytes(const GemmPlan& p, int64_t M, int64_t N) {
   return p.splits > 1 ? 4ull * p.splits * M * N : 0;
 }
@@ -1433,7 +1466,13 @@ hipError_t launch_gemm_plan(int dtype, int a_kcontig, int b_kcontig, const GemmP
       g.part = nullptr;
     }
     const dim3 grid(static_cast<unsigned>(tiles), p.splits), block(kBigThreads);
-    if (a_kcontig && b_kcontig && p.bm == 128)
+    if (g.kv) {
+      if (p.splits != 1 || !gemm_stores_kv(p, g)) return hipErrorInvalidValue;
+      if (p.bm == 128)
+        hipLaunchKernelGGL(ld_gemm_bf16_nt_kv_128, grid, block, 0, s, g);
+      else
+        hipLaunchKernelGGL(ld_gemm_bf16_nt_kv_256, grid, block, 0, s, g);
+    } else if (a_kcontig && b_kcontig && p.bm == 128)
       hipLaunchKernelGGL(ld_gemm_bf16_nt_128, grid, block, 0, s, g);
     else if (a_kcontig && b_kcontig)
       hipLaunchKernelGGL(ld_gemm_bf16_nt_256, grid, block, 0, s, g);

@@ -255,7 +255,13 @@ struct GemmArgs {
   //   backward (NN part of ld_gemm_bf16_tn_nn_relu2_256): the product (gs,
   //     rounded to bf16) is not stored: aux holds the u rows and C receives
   //     gu = gs 2 relu(u).
+  // Both forward epilogues leave out [u v] or u when C is null.
   int32_t relu2;
+  // QKV projection of kv_S rows per sequence (N = 3 kv_d): when kv is set, key
+  // and value columns of row b kv_S + i also go to position i of sequence b
+  // of the cache kv [., kv_s_max, 2 kv_d] (where gemm_stores_kv).
+  void* kv;
+  int32_t kv_d, kv_S, kv_s_max;
 };
 
 // Kernel choice for one GEMM: the 256x256 MFMA kernel (optionally split
@@ -390,6 +396,8 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
 // Rows of the tiles (256 or 128) of a forward projection of m rows (the kept
 // rows where the host knows them) and n columns.
 int plan_rows(int64_t m, int64_t n);
+// Whether launch_gemm_plan can store this GEMM's key and value columns too.
+bool gemm_stores_kv(const GemmPlan& p, const GemmArgs& g);
 size_t gemm_part_bytes(const GemmPlan& p, int64_t M, int64_t N);
 // Weight-gradient GEMMs g1 and g3 (both operands mn-contiguous, float32
 // out; g3 optional and never split, g1 absent when g1.M = 0) and an

@@ -282,6 +282,32 @@ def test_stack_eval(sh, name):
                 assert (c == 5.0).all()
 
 
+@pytest.mark.parametrize("d,H,f,S,B", [(320, 5, 640, 64, 3), (256, 4, 512, 64, 1), (256, 2, 520, 448, 3),
+                                       (1024, 8, 2816, 512, 4), (768, 6, 1408, 1088, 2)])
+@pytest.mark.parametrize("kind", [0, 1])
+def test_stack_eval_cache_variants(d, H, f, S, B, kind):
+    """Keys and values stored by the QKV projection's own epilogue (3 d a
+    multiple of 256; 128- and 256-row tiles) or by a launch of their own (d =
+    320): the cache against the oracle, nothing written past position S, and the
+    hidden states bit for bit those of the call without a cache."""
+    sh = inp.Shape(1, d, H, f, S, B, "bf16", kind)
+    cfg, w = _cfg(sh), _weights(sh)[0]
+    x, s_max = inp.hidden(sh), S + 24
+    kv = torch.full((B, s_max, 2 * d), 5.0, dtype=torch.bfloat16, device=DEV)
+    outs = []
+    for cache in (None, [kv]):
+        xd = x.to(DEV)
+        ld.ld_stack_eval(cfg, [w[0]], xd, _buf(ld.ld_eval_ws_bytes(cfg)), r_eval=[0.9], kv=cache, s_max=s_max)
+        torch.cuda.synchronize()
+        outs.append(xd.cpu())
+    assert torch.equal(outs[0], outs[1])
+    XL, okv = infer.eval_forward(inp.f64(x), [w[1]], [1], H, kind=kind, r_eval=[0.9])
+    t, c = tol("bf16"), f64(kv)
+    assert rel(f64(outs[0]), XL) < t
+    assert rel(c[:, :S, :d], okv[0][0]) < t and rel(c[:, :S, d:], okv[0][1]) < t
+    assert (c[:, S:] == 5.0).all()
+
+
 # ------------------------------------------------------------- decoding
 
 def _decode_case(sh, steps, s_max, batch=None):
