@@ -527,8 +527,8 @@ __global__ __launch_bounds__(256) void ld_kv_store_k(KvArgs a) {
 // The split of the cache into chunks is dec_attn_blocks's.  Measured per layer
 // of 16 heads of 128, before -> now: one row over 778 keys 9.2 -> 4.3 us; six
 // rows of 8 sequences over 1506 keys 34.2 -> 23.3 us (4.2 TB/s of cache); one
-// row of 8 sequences over 2048 keys 27.4 -> 28.4 us (4.7 TB/s, what a large copy
-// reaches), its combine 5.5 -> 4.6.  Before, waves of
+// row of 8 sequences over 2048 keys 27.4 -> 25.9 us (5.2 TB/s), its combine 5.5 ->
+// 4.8.  Before, waves of
 // 64 keys loaded the values after the scores, the probabilities went through
 // LDS, and the sum over keys through lane exchanges.
 template <int DH, int NQ, int KB>
@@ -824,21 +824,21 @@ hipError_t launch_kv_store(const KvArgs& a, hipStream_t s) {
 }
 
 // Blocks of 8 keys per wave (1 to 4: chunks of 64 to 256 keys).  Up to 256
-// keys: one chunk and no second launch.  Beyond, what costs least: rounds of
-// two workgroups per CU (what the registers of the largest chunks admit), each
-// its keys and about another 64 keys' worth of start and end; at equal cost the
-// largest chunk.  The partial rows must fit the scratch, which is sized for
-// kDecMaxRows rows of 256-key chunks.  One row over 778 keys and 16 heads takes
-// 208 workgroups of 64 keys (64 of 256: 9.2 us, now 4.2); six rows of 8
-// sequences over 1506 keys take 1024 of 192, two full rounds (768 of 256, one
-// and a half: 27.4 us, now 23.3).
+// keys: one chunk and no second launch.  Beyond, of 64, 128 and 192 keys what
+// costs least: rounds of two workgroups per CU, each its keys and about another
+// 64 keys' worth of start and end; at equal cost the largest chunk.  The partial
+// rows must fit the scratch, which is sized for kDecMaxRows rows of 256-key
+// chunks: 256 keys are for where 192 do not fit.  One row over 778 keys and 16
+// heads takes 208 workgroups of 64 keys (64 of 256: 9.2 us, now 4.2); six rows of 8
+// sequences over 1506 keys 1024 of 192 (768 of 256: 27.4 us, now 23.3); one row
+// of 8 sequences over 2048 keys 1408 of 192 (1024 of 256: 28.5 us, now 25.9).
 int dec_attn_blocks(const DecAttnArgs& a) {
   const int64_t nk = static_cast<int64_t>(a.pos) + a.n_new, heads = static_cast<int64_t>(a.n_seq) * a.H;
   const int64_t scratch_rows = (nk + kDecKeys - 1) / kDecKeys * kDecMaxRows;
   if (nk <= kDecKeys) return static_cast<int>((nk + 63) / 64);
   int best = 4;
   int64_t best_cost = INT64_MAX;
-  for (int kb = 4; kb >= 1; --kb) {
+  for (int kb = 3; kb >= 1; --kb) {
     const int64_t chunks = (nk + 64 * kb - 1) / (64 * kb);
     if (chunks * a.n_new > scratch_rows) break;
     const int64_t cost = (heads * chunks + 2 * kDecCus - 1) / (2 * kDecCus) * (kb + 1);
