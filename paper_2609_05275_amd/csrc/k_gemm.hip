@@ -24,6 +24,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "gemm_extent.h"
 #include "ld_internal.h"
 
 namespace ld {
@@ -548,24 +549,25 @@ __device__ __forceinline__ OpLanes<KC> op_lanes(int64_t ld, int lane, int wave, 
 
 // Load instruction p (0-3) of operand X's rows r0.. (k-contiguous: slot rows
 // 64p..64p+63; mn-contiguous: k rows 16p..16p+15) of the k step at k0 into the
-// slot at `lds`, 16 bytes per lane.  Columns past the end of a valid row read
-// real memory; they only reach outputs that are never stored, except a k tail
-// of a k-contiguous operand, which is fetched out of range (zeros), as is
-// everything of a step that starts at or past K.
+// slot at `lds`, 16 bytes per lane.  Columns past the end of an mn-contiguous
+// row read the next row's, or zeros past the operand's last element; they only
+// reach outputs that are never stored.  A k tail of a k-contiguous operand is
+// fetched out of range (zeros), as is everything of a step that starts at or
+// past K.  `extent`: mc_extent of the split's k rows (mn-contiguous only).
 template <bool KC>
-__device__ __forceinline__ void tile_part(bf16* lds, const OpLanes<KC>& o, const bf16* X, int64_t ld,
+__device__ __forceinline__ void tile_part(bf16* lds, const OpLanes<KC>& o, const bf16* X, int64_t ld, int64_t extent,
                                           int r0, int R, int k0, int K, int wave, int p) {
   if constexpr (KC) {
-    const v4i rs = dma_make_rsrc(X + static_cast<int64_t>(r0) * ld, (static_cast<int64_t>(R) - r0) * ld * 2);
+    const v4i rs = dma_make_rsrc(X + static_cast<int64_t>(r0) * ld, kc_extent(R, r0, ld));
     const uint32_t u = static_cast<uint32_t>((static_cast<int64_t>(p) * 64 * ld + k0) * 2);
     const uint32_t off = k0 + o.kchunk < K ? o.ld_off + u : kOob;
     dma16(rs, lds + (p * 8 + wave) * 512, off);
   } else {
-    const v4i rs = dma_make_rsrc(X + static_cast<int64_t>(k0) * ld, (static_cast<int64_t>(K) - k0) * ld * 2);
+    const int64_t at = mc_offset(k0, ld);
+    const v4i rs = dma_make_rsrc(reinterpret_cast<const char*>(X) + at, extent - at);
     const uint32_t u = static_cast<uint32_t>((static_cast<int64_t>(p) * 16 * ld + r0) * 2);
     dma16(rs, lds + (p * 8 + wave) * 512, o.ld_off + u);
   }
-  (void)R;
 }
 
 // B slot of the fused SwiGLU forward: each wave's WC columns pair WC / 2 gate
@@ -949,17 +951,18 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
 
   const OpLanes<AK> oa = op_lanes<AK>(g.lda, lane, wave, wm * 64);
   const OpLanes<BKC> ob = op_lanes<BKC>(g.ldb, lane, wave, wn * WC);
+  const int64_t ea = mc_extent(kend, M, g.lda), eb = mc_extent(kend, g.N, g.ldb);
   bf16* const ra = ring;                     // A's slots
   bf16* const rb = ring + SH::NSA * SH::SlotA;  // B's slots
   // Load instruction q of A or B for k step kt into slot sl.
   auto load_a = [&](int sl, int kt, int q) {
-    tile_part<AK>(ra + sl * SH::SlotA, oa, A, g.lda, m0, M, (kt0 + kt) * GK, kend, wave, q);
+    tile_part<AK>(ra + sl * SH::SlotA, oa, A, g.lda, ea, m0, M, (kt0 + kt) * GK, kend, wave, q);
   };
   auto load_b = [&](int sl, int kt, int q) {
     if constexpr (EPI == kEpiGluFwd)
       tile_part_glu<WC>(rb + sl * kSlot, ob, B, g.ldb, tn, g.glu_f, (kt0 + kt) * GK, kend, wave, q);
     else
-      tile_part<BKC>(rb + sl * kSlot, ob, B, g.ldb, n0, g.N, (kt0 + kt) * GK, kend, wave, q);
+      tile_part<BKC>(rb + sl * kSlot, ob, B, g.ldb, eb, n0, g.N, (kt0 + kt) * GK, kend, wave, q);
   };
   // The compiler's own loads (the kept count among them) are done with here:
   // left pending on some path, it would wait for one -- for every load of

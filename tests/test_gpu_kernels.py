@@ -265,6 +265,30 @@ def test_gemm_bf16_few_tiles(layout, M, N, K, off, pad):
     assert (C[:, N:] == 7.0).all() and (f64(buf)[:off] == 7.0).all() and (f64(buf)[off + M * ldc:] == 7.0).all()
 
 
+@pytest.mark.parametrize("layout", [(1, 1), (1, 0), (0, 0), (0, 1)])
+@pytest.mark.parametrize("M,N,K", [(8, 8, 8), (64, 264, 72), (264, 56, 136), (520, 520, 64)])
+def test_gemm_bf16_column_slices(layout, M, N, K):
+    """Operands that are the last columns of a wider matrix, at its buffer's
+    end (which lanes may read what is checked on the host, test_gemm_extent):
+    one rounding to 8 significant bits of sums of K exact products."""
+    ak, bk = layout
+    g = torch.Generator().manual_seed(14)
+    A = torch.randn(M, K, generator=g).to(torch.bfloat16)
+    B = torch.randn(N, K, generator=g).to(torch.bfloat16)
+
+    def last_columns(t):
+        parent = torch.full((t.shape[0], t.shape[1] + 4096), float("nan"), dtype=t.dtype)
+        parent[:, 4096:] = t
+        return parent.to(DEV)[:, 4096:]
+    Ad, Bd = last_columns(A if ak else A.t()), last_columns(B if bk else B.t())
+    C = torch.full((M, N), 7.0, dtype=torch.bfloat16, device=DEV)
+    ld.ld_gemm(ak, bk, M, N, K, Ad, Ad.stride(0), Bd, Bd.stride(0), C, N)
+    torch.cuda.synchronize()
+    ref = f64(A) @ f64(B).T
+    bound = K * 2.0 ** -24 * (np.abs(f64(A)) @ np.abs(f64(B)).T) + 2.0 ** -8 * np.abs(ref)
+    assert np.all(np.abs(f64(C) - ref) <= 1.01 * bound)
+
+
 @pytest.mark.parametrize("layout", [(0, 0), (1, 0)])
 def test_gemm_bf16_split_k(layout):
     """float32 output with split-K partials summed in a fixed order."""
