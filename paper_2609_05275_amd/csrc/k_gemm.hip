@@ -1396,9 +1396,12 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
   }
   const int64_t big_tiles = ((max_m + GB - 1) / GB) * ((g.N + GB - 1) / GB);
   // the big tile's epilogue stores 4 consecutive columns at once
-  // each operand is addressed through one buffer descriptor: spans < 2 GiB
-  const int64_t a_span = 2 * g.lda * (a_kcontig ? max_m : max_k);
-  const int64_t b_span = 2 * g.ldb * (b_kcontig ? static_cast<int64_t>(g.N) : max_k);
+  // each operand is addressed through one buffer descriptor: spans < 2 GiB (an
+  // mn-contiguous one is fetched 64 k rows at a time, whatever K is, with
+  // 32-bit offsets that must not wrap back into it)
+  const int64_t k_rows = std::max<int64_t>(max_k, GK);
+  const int64_t a_span = 2 * g.lda * (a_kcontig ? max_m : k_rows);
+  const int64_t b_span = 2 * g.ldb * (b_kcontig ? static_cast<int64_t>(g.N) : k_rows);
   // split-K only for float32 outputs without a residual (weight gradients);
   // such a GEMM fills the CUs through its splits even with few tiles
   const bool splittable = allow_split && g.c_f32 && !g.R && !g.out_map.idx && g.ldc == g.N && max_k >= 16 * kPlanK;

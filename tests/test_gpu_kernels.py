@@ -289,6 +289,25 @@ def test_gemm_bf16_column_slices(layout, M, N, K):
     assert np.all(np.abs(f64(C) - ref) <= 1.01 * bound)
 
 
+def test_gemm_bf16_far_apart_k_rows():
+    """Eight k rows 2^26 elements apart: the k rows past K that a tile of 64
+    asks for lie a multiple of 4 GiB on, and must not come back as earlier
+    rows.  float32 sums of K exact products."""
+    M, N, K, ld_ = 64, 128, 8, 1 << 26
+    g = torch.Generator().manual_seed(15)
+    A = torch.randn(K, M, generator=g).to(torch.bfloat16)
+    B = torch.randn(K, N, generator=g).to(torch.bfloat16)
+    base = torch.empty((K - 1) * ld_ + M + N, dtype=torch.bfloat16, device=DEV)
+    Ad, Bd = base.as_strided((K, M), (ld_, 1)), base.as_strided((K, N), (ld_, 1), M)
+    Ad.copy_(A)
+    Bd.copy_(B)
+    C = torch.full((M, N), 7.0, device=DEV)
+    ld.ld_gemm(0, 0, M, N, K, Ad, ld_, Bd, ld_, C, N, c_f32=True)
+    torch.cuda.synchronize()
+    ref = f64(A).T @ f64(B)
+    assert np.all(np.abs(f64(C) - ref) <= K * 2.0 ** -24 * (np.abs(f64(A)).T @ np.abs(f64(B))))
+
+
 @pytest.mark.parametrize("layout", [(0, 0), (1, 0)])
 def test_gemm_bf16_split_k(layout):
     """float32 output with split-K partials summed in a fixed order."""
