@@ -599,7 +599,7 @@ __global__ __launch_bounds__(512) void ld_attn_decode_bf16(DecAttnArgs a) {
   for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      p[kb][t] = m == -INFINITY ? 0.f : exp2f(p[kb][t] - m);
+      p[kb][t] = p[kb][t] == -INFINITY ? 0.f : exp2f(p[kb][t] - m);  // a NaN score stays one
       l += p[kb][t];
     }
   l += __shfl_xor(l, 16, 64);

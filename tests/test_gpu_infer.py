@@ -233,6 +233,24 @@ def test_attn_decode_chunks(dh, H, B, pos, n):
         assert rel(got[b * n:(b + 1) * n], want) < 1e-2, b
 
 
+@pytest.mark.parametrize("dh,H", [(64, 4), (128, 3)])
+@pytest.mark.parametrize("pos,n,keys", [(8, 1, (8, 9)), (40, 1, (8, 16)), (40, 2, (8, 16)), (300, 1, (296, 304)),
+                                        (700, 8, (64, 96)), (1000, 6, (960, 968))])
+def test_attn_decode_nan_scores(dh, H, pos, n, keys):
+    """NaN keys of one head, all the keys that a wave holds, make that head's
+    outputs NaN and no other's."""
+    rng = np.random.default_rng(pos + n + dh)
+    d, s_max = H * dh, pos + n
+    qkv, kv = _rng_bf16(rng, (n, 3 * d)), _rng_bf16(rng, (1, s_max, 2 * d))
+    kv[:, keys[0]:keys[1], dh:2 * dh] = float("nan")
+    o = torch.zeros(n, d, dtype=torch.bfloat16, device=DEV)
+    ld.ld_attn_decode(1, H, dh, pos, n, qkv.to(DEV), kv.to(DEV), s_max, o, _buf(ld.ld_attn_decode_ws_bytes(1, H, dh, s_max)))
+    torch.cuda.synchronize()
+    got = f64(o).reshape(n, H, dh)
+    assert np.isnan(got[:, 1]).all()
+    assert np.isfinite(np.delete(got, 1, 1)).all()
+
+
 # ------------------------------------------------------ evaluation form
 
 ACTIVE = {"all": None, "exit": "exit", "skip": "skip"}
