@@ -571,6 +571,13 @@ __global__ __launch_bounds__(512) void ld_attn_decode_bf16(DecAttnArgs a) {
       vr[kb][t] = *reinterpret_cast<const VRow*>(cache + static_cast<int64_t>(kk < nk ? kk : 0) * row2 + d + EPL * n);
     }
   __builtin_amdgcn_sched_barrier(0);  // the value loads stay ahead of the scores
+  if (k0 + 8 * KB > nk) {  // wave-uniform: what was read in place of keys past the last counts as zeros
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        if (kv0 + 8 * kb + t >= nk) vr[kb][t] = static_cast<bf16>(0.f);
+  }
 
   const int qpos = a.pos + (NQ == 1 ? 0 : n);
   float p[KB][2];
@@ -712,9 +719,10 @@ __global__ __launch_bounds__(256) void ld_attn_decode_combine(DecAttnArgs a) {
     M = m;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const float wgt = c0 + u >= a.n_chunks || mc[u] == -INFINITY ? 0.f : exp2f(mc[u] - m);
+      const bool in = c0 + u < a.n_chunks;  // else selected out: 0 times an infinity in v would be NaN
+      const float wgt = !in || mc[u] == -INFINITY ? 0.f : exp2f(mc[u] - m);
       L = __builtin_fmaf(wgt, lc[u], L);
-      acc += wgt * v[u];
+      acc += wgt * (in ? v[u] : FRow(0.f));
     }
   }
   acc *= 1.f / L;

@@ -234,6 +234,35 @@ def test_attn_decode_chunks(dh, H, B, pos, n):
 
 
 @pytest.mark.parametrize("dh,H", [(64, 4), (128, 3)])
+@pytest.mark.parametrize("B,pos,n", [(1, 0, 1), (2, 8, 1), (2, 41, 3), (2, 255, 1), (2, 300, 1), (1, 777, 1), (1, 1023, 4),
+                                     (2, 700, 8), (43, 1100, 6)])
+def test_attn_decode_infinite_values(dh, H, B, pos, n):
+    """An infinite value of a key every query sees makes its column infinite
+    and leaves the others alone, whichever chunk holds the key: the first key
+    (read in place of keys past the last one), the last cached one, one in
+    between."""
+    rng = np.random.default_rng(pos + n + dh)
+    d, s_max = H * dh, pos + n
+    qkv, kv = _rng_bf16(rng, (B * n, 3 * d)), _rng_bf16(rng, (B, s_max, 2 * d))
+    ws = _buf(ld.ld_attn_decode_ws_bytes(B, H, dh, s_max))
+    at = sorted({0, pos // 2, pos})
+    outs = []
+    for key in [None] + at:
+        c = kv.clone()
+        if key is not None:
+            c[:, key, d + 5] = float("inf")
+            c[:, key, d + dh + 7] = float("-inf")
+        o = torch.zeros(B * n, d, dtype=torch.bfloat16, device=DEV)
+        ld.ld_attn_decode(B, H, dh, pos, n, qkv.to(DEV), c.to(DEV), s_max, o, ws)
+        torch.cuda.synchronize()
+        outs.append(f64(o))
+    rest = [c for c in range(d) if c not in (5, dh + 7)]
+    for key, o in zip(at, outs[1:]):
+        assert np.all(o[:, 5] == np.inf) and np.all(o[:, dh + 7] == -np.inf), key
+        assert np.array_equal(o[:, rest], outs[0][:, rest]), key
+
+
+@pytest.mark.parametrize("dh,H", [(64, 4), (128, 3)])
 @pytest.mark.parametrize("pos,n,keys", [(8, 1, (8, 9)), (40, 1, (8, 16)), (40, 2, (8, 16)), (300, 1, (296, 304)),
                                         (700, 8, (64, 96)), (1000, 6, (960, 968))])
 def test_attn_decode_nan_scores(dh, H, pos, n, keys):
