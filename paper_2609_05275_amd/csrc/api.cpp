@@ -2003,6 +2003,8 @@ int ld_gemm(int32_t dtype, int32_t a_kcontig, int32_t b_kcontig, int32_t M, int3
   g.out_map = {nullptr, 1};
   g.alpha = alpha;
   g.c_f32 = c_f32;
+  // a workspace smaller than the query: no split
+  if (ws && ws_bytes < ld_gemm_ws_bytes(dtype, a_kcontig, b_kcontig, M, N, K, ldc, c_f32)) ws = nullptr;
   return run_gemm(dtype, a_kcontig ? 1 : 0, b_kcontig ? 1 : 0, g, M, M, K, as_stream(stream),
                   static_cast<float*>(ws), ws ? ws_bytes : 0, K);
 }

@@ -332,6 +332,25 @@ def test_gemm_bf16_split_k(layout):
     assert rel(outs[0].double().numpy(), 0.25 * (f64(A) @ f64(B).T)) < 1e-5
 
 
+@pytest.mark.parametrize("M,N,K", [(256, 1536, 4096), (512, 768, 4096), (1024, 1024, 4096)])
+def test_gemm_bf16_workspace_too_small_to_split(M, N, K):
+    """With less workspace than the query asks for, the GEMM is not split: the
+    result is that of a call without one, and the workspace is left alone."""
+    g = torch.Generator().manual_seed(16)
+    A = torch.randn(K, M, generator=g).to(torch.bfloat16).to(DEV)
+    B = torch.randn(K, N, generator=g).to(torch.bfloat16).to(DEV)
+    wsb = ld.ld_gemm_ws_bytes(ld.LD_BF16, 0, 0, M, N, K, N, 1)
+    assert wsb > 0
+    outs = []
+    for ws in (None, torch.full((wsb - 1,), 77, dtype=torch.uint8, device=DEV)):
+        C = torch.full((M, N), 7.0, device=DEV)
+        ld.ld_gemm(0, 0, M, N, K, A, M, B, N, C, N, c_f32=True, ws=ws)
+        torch.cuda.synchronize()
+        outs.append(C.cpu())
+    assert bool((ws == 77).all()) and torch.equal(outs[0], outs[1])
+    assert rel(outs[1].double().numpy(), f64(A).T @ f64(B)) < 1e-5
+
+
 @pytest.mark.parametrize("layout", [(1, 1), (1, 0), (0, 0), (0, 1)])
 @pytest.mark.parametrize("M,N,K", [(4, 4, 4), (32, 36, 32), (36, 64, 100), (100, 172, 64), (1100, 1028, 36),
                                    (6, 10, 7)])
