@@ -1184,13 +1184,32 @@ int check_host_counts(const Dims& D, const LayerMasks& lm, const std::vector<int
 // Scratch of ld_stack_decode for n_new rows per sequence and caches of s_max
 // positions.
 struct DecLayout {
-  size_t h, rstd, qkv, att, z, uv, s, part_o, part_ml, total;
+  size_t h, rstd, qkv, att, z, uv, s, part_o, part_ml, skp, skp_bytes, total;
 };
 
 size_t skinny_part_bytes(int64_t M, int64_t N, int64_t K) {
   if (M > kSkinnyMaxM) return 0;
   const int ks = skinny_ksplit(M, N, K);
   return ks > 1 ? static_cast<size_t>(ks) * M * N * 4 : 0;
+}
+
+// Partials of a skinny GEMM whose reduction is fused with what follows it
+// (written even with one split).
+size_t skinny_fused_part_bytes(int64_t M, int64_t N, int64_t K) {
+  return static_cast<size_t>(skinny_ksplit(M, N, K)) * M * N * 4;
+}
+
+// Rows M of width d whose projections go through the split-K skinny GEMMs.
+// First, those whose norm the fused projections cannot take in
+// (dec_gemm_fuses_norm): they would stream the activations beside the weights,
+// once per 8 columns.  Per layer, fused -> split: 64 rows of d = 4096, d_ff = 11008
+// 423 -> 288 us, 17 rows of 2560 and 6912 132 -> 112; where the norm fits, 16 rows of
+// 2560 84 -> 112.  Then more than 32 rows of d <= 1024, where a projection's few
+// tiles leave each workgroup waiting for its share of the rows: 33 rows of 512 and
+// 1408 45 -> 39 us, of 1024 and 8192 69 -> 60, 48 of 1024 and 2816 62 -> 58; but 33 of
+// 1536 and 4096 62 -> 75, 32 of 1024 and 2816 49 -> 53.
+bool dec_split_k(int64_t M, int64_t d) {
+  return M <= kSkinnyMaxM && (!dec_gemm_fuses_norm(M, d) || (M > 32 && d <= 1024));
 }
 
 int64_t dec_chunks(int64_t keys) { return (keys + kDecKeys - 1) / kDecKeys; }
@@ -1214,6 +1233,11 @@ DecLayout dec_layout(const Dims& D, int64_t n_new, int64_t s_max) {
   const size_t pc = static_cast<size_t>(D.B) * D.H * dec_chunks(s_max) * kDecMaxRows;
   L.part_o = take(4 * pc * D.dh);
   L.part_ml = take(4 * pc * 2);
+  if (dec_split_k(M, D.d)) {
+    const int64_t shapes[4][2] = {{3 * D.d, D.d}, {D.d, D.d}, {D.fw, D.d}, {D.d, D.f}};
+    for (const auto& sh : shapes) L.skp_bytes = std::max(L.skp_bytes, skinny_fused_part_bytes(M, sh[0], sh[1]));
+    L.skp = take(L.skp_bytes);
+  }
   L.total = o;
   return L;
 }
@@ -1278,6 +1302,37 @@ int dec_proj(const void* A, int64_t lda, const void* g, float eps, const void* W
   const double wrows = act == kDecActSwiglu ? 2.0 * N : static_cast<double>(N);
   ps.end(2.0 * M * wrows * K, 2.0 * (M * K + wrows * K + M * N) + (R ? 2.0 * M * N : 0.0));
   return LD_OK;
+}
+
+// Skinny GEMM (at most kSkinnyMaxM rows), its k range split over ks workgroups
+// per 32 columns with partials in `part`.  g.part_only: only the partials are
+// written, for a fused reduction launched next.
+int run_skinny(SkinnyArgs& g, int& ks, float* part, size_t part_bytes, hipStream_t s) {
+  const double M = g.M, N = g.N, K = g.K;
+  ks = skinny_ksplit(g.M, g.N, g.K);
+  if (ks > 1 || g.part_only) {
+    if (static_cast<size_t>(ks) * g.M * g.N * 4 > part_bytes) return fail(LD_E_WORKSPACE, "skinny GEMM scratch too small");
+    g.part = part;
+  }
+  ProfScope ps(g.M <= 32 ? "ld_gemm_bf16_skinny<1>" : "ld_gemm_bf16_skinny<2>", s);
+  const hipError_t e = launch_gemm_skinny(g, ks, s);
+  if (e != hipSuccess) return fail(LD_E_HIP, "skinny GEMM: %s", hipGetErrorString(e));
+  ps.end(2.0 * M * N * K, 2.0 * (M * K + N * K) + (g.part_only ? 4.0 * ks * M * N : 2.0 * M * N + (g.R ? 2.0 * M * N : 0.0)));
+  return LD_OK;
+}
+
+SkinnyArgs skinny_args(const void* A, int64_t lda, const void* W, int64_t ldw, int64_t M, int64_t N, int64_t K,
+                       float alpha) {
+  SkinnyArgs g{};
+  g.A = A;
+  g.lda = lda;
+  g.W = W;
+  g.ldw = ldw;
+  g.M = static_cast<int32_t>(M);
+  g.N = static_cast<int32_t>(N);
+  g.K = static_cast<int32_t>(K);
+  g.alpha = alpha;
+  return g;
 }
 
 }  // namespace
@@ -1619,10 +1674,14 @@ int ld_stack_decode(const ld_config* cfg, int32_t n_layers, const ld_weights* w,
     ps.end(0, 4.0 * M * d);
     return static_cast<int>(LD_OK);
   };
-  // At most 64 rows: each projection is one fused launch that applies the
-  // residual or the FFN activation, and normalises its input rows itself
-  // where they stay in registers (else a norm launch goes before it).
-  const bool fused = M <= kSkinnyMaxM, fused_norm = fused && dec_gemm_fuses_norm(M, d);
+  // Fused: one launch per projection, which normalises its input rows and
+  // applies the residual or the FFN activation.  Part-fused: split-K skinny
+  // GEMMs whose partial sums are reduced together with what follows them, the
+  // residual and the next RMSNorm (output and down projections) or the FFN
+  // activation.  Else (more than 64 rows) the general GEMM.
+  const bool part_fused = dec_split_k(M, d), fused = !part_fused && dec_gemm_fuses_norm(M, d);
+  float* skp = reinterpret_cast<float*>(base + L.skp);
+  bool h_ready = false;  // L.h holds RMSNorm(x) with this layer's gain
   const int act = D.kind == LD_BLOCK_SWIGLU ? kDecActSwiglu : kDecActRelu2;
   for (int32_t l = 0; l < n_layers; ++l) {
     if (active && !active[l]) continue;
@@ -1630,12 +1689,24 @@ int ld_stack_decode(const ld_config* cfg, int32_t n_layers, const ld_weights* w,
     const ld_weights& wl = w[l];
     // h = RMSNorm(x); qkv = h W_qkv^T; new keys/values into the cache
     const KvOut ko{kv[l], static_cast<int32_t>(d), n_new, s_max, pos};
-    if (!fused_norm)
+    if (!fused && !h_ready)
       if (int rc = norm(x, wl.g_attn)) return rc;
+    h_ready = false;
     if (fused) {
-      if (int rc = dec_proj(fused_norm ? x : P(L.h), d, fused_norm ? wl.g_attn : nullptr, cfg->rms_eps, wl.w_qkv, d,
-                            P(L.qkv), 3 * d, nullptr, 0, M, 3 * d, d, 1.f, kDecActNone, s, &ko))
+      if (int rc = dec_proj(x, d, wl.g_attn, cfg->rms_eps, wl.w_qkv, d, P(L.qkv), 3 * d, nullptr, 0, M, 3 * d, d, 1.f,
+                            kDecActNone, s, &ko))
         return rc;
+    } else if (part_fused) {
+      SkinnyArgs g = skinny_args(P(L.h), d, wl.w_qkv, d, M, 3 * d, d, 1.f);
+      g.C = P(L.qkv);
+      g.ldc = 3 * d;
+      g.kv = ko.kv;
+      g.kv_d = ko.d;
+      g.kv_n = ko.n;
+      g.kv_s_max = ko.s_max;
+      g.kv_pos = ko.pos;
+      int ks = 1;
+      if (int rc = run_skinny(g, ks, skp, L.skp_bytes, s)) return rc;
     } else {
       if (int rc = dec_gemm(P(L.h), d, wl.w_qkv, d, P(L.qkv), 3 * d, nullptr, 0, M, 3 * d, d, 1.f, s)) return rc;
       KvArgs k{};
@@ -1677,15 +1748,47 @@ int ld_stack_decode(const ld_config* cfg, int32_t n_layers, const ld_weights* w,
     if (fused) {
       if (int rc = dec_proj(P(L.att), d, nullptr, 0.f, wl.w_o, d, P(L.z), d, x, d, M, d, d, r, kDecActNone, s))
         return rc;
-      if (!fused_norm)
-        if (int rc = norm(P(L.z), wl.g_mlp)) return rc;
-      if (int rc = dec_proj(fused_norm ? P(L.z) : P(L.h), d, fused_norm ? wl.g_mlp : nullptr, cfg->rms_eps,
-                            wl.w_gate_up, d, P(L.s), D.f, nullptr, 0, M, D.f, d, 1.f, act, s))
+      if (int rc = dec_proj(P(L.z), d, wl.g_mlp, cfg->rms_eps, wl.w_gate_up, d, P(L.s), D.f, nullptr, 0, M, D.f, d, 1.f,
+                            act, s))
         return rc;
       // x = z + r (s W_down^T)
       if (int rc = dec_proj(P(L.s), D.f, nullptr, 0.f, wl.w_down, D.f, x, d, P(L.z), d, M, d, D.f, r,
                             kDecActNone, s))
         return rc;
+      continue;
+    }
+    if (part_fused) {
+      int ks = 1;
+      // z = x + r (att W_o^T) and h = RMSNorm(z)
+      SkinnyArgs g = skinny_args(P(L.att), d, wl.w_o, d, M, d, d, r);
+      g.part_only = 1;
+      if (int rc = run_skinny(g, ks, skp, L.skp_bytes, s)) return rc;
+      g.C = P(L.z);
+      g.ldc = d;
+      g.R = x;
+      g.ldr = d;
+      if ((e = launch_skinny_reduce_norm(g, ks, wl.g_mlp, cfg->rms_eps, P(L.h), s)) != hipSuccess)
+        return fail(LD_E_HIP, "skinny reduce: %s", hipGetErrorString(e));
+      // s = act(h W_gate_up^T)
+      g = skinny_args(P(L.h), d, wl.w_gate_up, d, M, D.fw, d, 1.f);
+      g.part_only = 1;
+      if (int rc = run_skinny(g, ks, skp, L.skp_bytes, s)) return rc;
+      if ((e = launch_skinny_reduce_act(g, ks, act, static_cast<int>(D.f), P(L.s), s)) != hipSuccess)
+        return fail(LD_E_HIP, "skinny reduce: %s", hipGetErrorString(e));
+      // x = z + r (s W_down^T), and the next active layer's h = RMSNorm(x)
+      g = skinny_args(P(L.s), D.f, wl.w_down, D.f, M, d, D.f, r);
+      g.part_only = 1;
+      if (int rc = run_skinny(g, ks, skp, L.skp_bytes, s)) return rc;
+      g.C = x;
+      g.ldc = d;
+      g.R = P(L.z);
+      g.ldr = d;
+      int32_t next = l + 1;
+      while (next < n_layers && active && !active[next]) ++next;
+      const void* gain = next < n_layers ? w[next].g_attn : nullptr;
+      if ((e = launch_skinny_reduce_norm(g, ks, gain, cfg->rms_eps, P(L.h), s)) != hipSuccess)
+        return fail(LD_E_HIP, "skinny reduce: %s", hipGetErrorString(e));
+      h_ready = gain != nullptr;
       continue;
     }
     if (int rc = dec_gemm(P(L.att), d, wl.w_o, d, P(L.z), d, x, d, M, d, d, r, s)) return rc;
@@ -1848,26 +1951,13 @@ int ld_gemm_skinny(int32_t M, int32_t N, int32_t K, const void* A, int32_t lda, 
   if (!std::isfinite(alpha)) return fail(LD_E_INVALID, "alpha not finite");
   const size_t need = ld_gemm_skinny_ws_bytes(M, N, K);
   if (need && (!ws || ws_bytes < need)) return fail(LD_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
-  SkinnyArgs g{};
-  g.A = A;
-  g.lda = lda;
-  g.W = W;
-  g.ldw = ldw;
+  SkinnyArgs g = skinny_args(A, lda, W, ldw, M, N, K, alpha);
   g.C = C;
   g.ldc = ldc;
   g.R = R;
   g.ldr = ldr;
-  g.M = M;
-  g.N = N;
-  g.K = K;
-  g.alpha = alpha;
-  g.part = static_cast<float*>(ws);
-  hipStream_t s = as_stream(stream);
-  ProfScope ps(M <= 32 ? "ld_gemm_bf16_skinny<1>" : "ld_gemm_bf16_skinny<2>", s);
-  const hipError_t e = launch_gemm_skinny(g, skinny_ksplit(M, N, K), s);
-  if (e != hipSuccess) return fail(LD_E_HIP, "skinny GEMM: %s", hipGetErrorString(e));
-  ps.end(2.0 * M * N * K, 2.0 * (1.0 * M * K + 1.0 * N * K + 1.0 * M * N) + (R ? 2.0 * M * N : 0.0));
-  return LD_OK;
+  int ks = 1;
+  return run_skinny(g, ks, static_cast<float*>(ws), ws ? ws_bytes : 0, as_stream(stream));
 }
 
 int ld_gemm_dec(int32_t M, int32_t N, int32_t K, const void* A, int32_t lda, const void* g, float eps,

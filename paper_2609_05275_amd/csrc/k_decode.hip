@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256) void ld_gemm_bf16_skinny(SkinnyArgs g) {
     const int m = mb * 32 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
     const int n = n0 + (l & 31);
     if (m < g.M && n < g.N) {
-      if (gridDim.y > 1)
+      if (gridDim.y > 1 || g.part_only)
         g.part[(static_cast<int64_t>(blockIdx.y) * g.M + m) * g.N + n] = sum;
       else
         skinny_store(g, m, n, sum);
@@ -136,8 +136,83 @@ __global__ __launch_bounds__(256) void ld_skinny_reduce_k(SkinnyArgs g, int kspl
 
 __device__ __forceinline__ float bf16r(float x) { return static_cast<float>(static_cast<bf16>(x)); }
 
+// Split-K sums (split order) of one row of a skinny GEMM with alpha and the
+// residual, stored as C, then (when a gain is given) the RMSNorm of the
+// stored row (sum of squares over the workgroup in a fixed order):
+// h = bf16(C rstd gain).  One workgroup of 1024 threads per row.
+__global__ __launch_bounds__(1024) void ld_skinny_reduce_norm_k(SkinnyArgs g, int ksplit, const bf16* gain,
+                                                                 float eps, bf16* h) {
+  constexpr int kPer = 4;  // columns per thread and pass: one pass up to 4096 columns
+  __shared__ float wsum[16];
+  const int m = blockIdx.x, tid = threadIdx.x;
+  const int64_t mn = static_cast<int64_t>(g.M) * g.N;
+  const float* prow = g.part + static_cast<int64_t>(m) * g.N;
+  bf16* C = static_cast<bf16*>(g.C) + static_cast<int64_t>(m) * g.ldc;
+  const bf16* R = g.R ? static_cast<const bf16*>(g.R) + static_cast<int64_t>(m) * g.ldr : nullptr;
+  float ss = 0.f;
+  for (int n0 = 0; n0 < g.N; n0 += 1024 * kPer) {
+    float sum[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) sum[i] = 0.f;
+    // the splits in order; every column's loads of a split are independent
+#pragma unroll 2
+    for (int sp = 0; sp < ksplit; ++sp)
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        const int n = n0 + i * 1024 + tid;
+        if (n < g.N) sum[i] += prow[sp * mn + n];
+      }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int n = n0 + i * 1024 + tid;
+      if (n < g.N) {
+        const bf16 o = static_cast<bf16>(g.alpha * sum[i] + (R ? static_cast<float>(R[n]) : 0.f));
+        C[n] = o;
+        const float of = static_cast<float>(o);
+        ss = __builtin_fmaf(of, of, ss);
+      }
+    }
+  }
+  if (!gain) return;  // no norm follows (workgroup-uniform)
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+  if ((tid & 63) == 0) wsum[tid >> 6] = ss;
+  __syncthreads();
+  float tot = 0.f;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) tot += wsum[w];
+  const float rstd = rsqrtf(tot / static_cast<float>(g.N) + eps);
+  bf16* hr = h + static_cast<int64_t>(m) * g.N;
+  for (int n = tid; n < g.N; n += 1024)  // this thread's own stores, read back
+    hr[n] = static_cast<bf16>(static_cast<float>(C[n]) * rstd * static_cast<float>(gain[n]));
+}
+
+// The FFN activation from a skinny GEMM's partials: u (and v = column f + n
+// for SwiGLU) rounded to bf16 as stored outputs would be, s = act(u, v).
+__global__ __launch_bounds__(256) void ld_skinny_reduce_act_k(SkinnyArgs g, int ksplit, int act, int f, bf16* so) {
+  const int64_t mn = static_cast<int64_t>(g.M) * g.N, total = static_cast<int64_t>(g.M) * f;
+  for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < total; i += gridDim.x * 256ll) {
+    const int64_t m = i / f, n = i % f, iu = m * g.N + n;
+    float su = g.part[iu];
+#pragma unroll 4
+    for (int sp = 1; sp < ksplit; ++sp) su += g.part[sp * mn + iu];
+    const float u = bf16r(g.alpha * su);
+    float out;
+    if (act == kDecActSwiglu) {
+      float sv = g.part[iu + f];
+#pragma unroll 4
+      for (int sp = 1; sp < ksplit; ++sp) sv += g.part[sp * mn + iu + f];
+      out = swiglu_fwd_f(u, bf16r(g.alpha * sv));
+    } else {
+      const float z = fmaxf(u, 0.f);
+      out = z * z;
+    }
+    so[m * f + n] = static_cast<bf16>(out);
+  }
+}
+
 // ------------------------------------------------ fused decode projection
-// At most 64 rows.  Bound by the weight stream: W is read once, and the
+// At most 48 rows.  Bound by the weight stream: W is read once, and the
 // rest is kept out of its way.  A tile is 8 output columns (8 rows of W; with
 // SwiGLU the 8 gate rows and the 8 up rows of those columns) over the whole
 // k range, so every column is finished in one workgroup (no split-K partials,
@@ -761,14 +836,29 @@ hipError_t launch_gemm_skinny(const SkinnyArgs& g, int ksplit, hipStream_t s) {
   else
     hipLaunchKernelGGL(ld_gemm_bf16_skinny<2>, grid, dim3(256), 0, s, g);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || ksplit == 1) return e;
+  if (e != hipSuccess || ksplit == 1 || g.part_only) return e;
   hipLaunchKernelGGL(ld_skinny_reduce_k, dim3(grid_for(static_cast<int64_t>(g.M) * g.N)), dim3(256), 0,
                      s, g, ksplit);
   return hipGetLastError();
 }
 
+hipError_t launch_skinny_reduce_norm(const SkinnyArgs& g, int ksplit, const void* gain, float eps, void* h,
+                                     hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  hipLaunchKernelGGL(ld_skinny_reduce_norm_k, dim3(g.M), dim3(1024), 0, s, g, ksplit, static_cast<const bf16*>(gain),
+                     eps, static_cast<bf16*>(h));
+  return hipGetLastError();
+}
+
+hipError_t launch_skinny_reduce_act(const SkinnyArgs& g, int ksplit, int act, int f, void* s_out, hipStream_t s) {
+  if (g.M <= 0 || f <= 0) return hipSuccess;
+  hipLaunchKernelGGL(ld_skinny_reduce_act_k, dim3(grid_for(static_cast<int64_t>(g.M) * f)), dim3(256), 0, s, g,
+                     ksplit, act, f, static_cast<bf16*>(s_out));
+  return hipGetLastError();
+}
+
 bool dec_gemm_fuses_norm(int64_t M, int64_t K) {
-  return M >= 1 && ((M <= 48 && K <= 2048) || (M <= 16 && K <= 4096));
+  return M >= 1 && ((M <= kDecGemmMaxM && K <= 2048) || (M <= 16 && K <= 4096));
 }
 
 // Rows of the tiles' weights in flight per CU, and the activations' registers,
@@ -776,31 +866,35 @@ bool dec_gemm_fuses_norm(int64_t M, int64_t K) {
 // each) for up to 48 rows, of K <= 4096 (8 chunks) for up to 16, beyond which
 // they would spill, one workgroup per CU, each CU taking the same number of
 // tiles; else streamed activations, 16 waves while their registers allow.
+// Decoding passes a gain with every activation, ld_gemm_dec (8 rows) either.
 template <int MB, int ACT>
 hipError_t gemm_dec_t(const SkinnyArgs& g, hipStream_t s) {
+  constexpr bool kBare = MB == 1 || ACT == kDecActNone;  // without a gain
   const int tiles = (g.N + kDecCols - 1) / kDecCols;
+  const int rounds = (tiles + kDecCus - 1) / kDecCus;
+  const dim3 block(512), grid((tiles + rounds - 1) / rounds);
   if (dec_gemm_fuses_norm(g.M, g.K)) {
-    const int rounds = (tiles + kDecCus - 1) / kDecCus, grid = (tiles + rounds - 1) / rounds;
-    const dim3 block(512);
     if (g.K <= 2048) {
-      if constexpr (MB <= 6) {
-        if (g.g)
-          hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, true, 8, 4>), dim3(grid), block, 0, s, g);
-        else
-          hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, false, 8, 4>), dim3(grid), block, 0, s, g);
-      }
-    } else {
-      if constexpr (MB <= 2) {
-        if (g.g)
-          hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, true, 8, 8>), dim3(grid), block, 0, s, g);
-        else
-          hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, false, 8, 8>), dim3(grid), block, 0, s, g);
-      }
+      if (g.g)
+        hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, true, 8, 4>), grid, block, 0, s, g);
+      else if constexpr (kBare)
+        hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, false, 8, 4>), grid, block, 0, s, g);
+      else
+        return hipErrorInvalidValue;
+    } else if constexpr (MB <= 2) {
+      if (g.g)
+        hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, true, 8, 8>), grid, block, 0, s, g);
+      else if constexpr (kBare)
+        hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, false, 8, 8>), grid, block, 0, s, g);
+      else
+        return hipErrorInvalidValue;
     }
-  } else {
+  } else if constexpr (kBare) {
     if (g.g) return hipErrorInvalidValue;
     constexpr int NW = MB <= 3 ? 16 : 8, U = MB <= 2 && ACT != kDecActSwiglu ? 4 : 2;
     hipLaunchKernelGGL((ld_gemm_bf16_dec_long<MB, ACT, NW, U>), dim3(tiles), dim3(NW * 64), 0, s, g);
+  } else {
+    return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
@@ -814,14 +908,13 @@ hipError_t gemm_dec_act(const SkinnyArgs& g, hipStream_t s) {
 
 hipError_t launch_gemm_dec(const SkinnyArgs& g, hipStream_t s) {
   if (g.N <= 0) return hipSuccess;
-  if (g.M < 1 || g.M > kSkinnyMaxM || g.K < 8 || g.K % 8) return hipErrorInvalidValue;
+  if (g.M < 1 || g.M > kDecGemmMaxM || g.K < 8 || g.K % 8) return hipErrorInvalidValue;
   const int mb = (g.M + 7) / 8;  // blocks of 8 rows
   return mb <= 1   ? gemm_dec_act<1>(g, s)
          : mb <= 2 ? gemm_dec_act<2>(g, s)
          : mb <= 3 ? gemm_dec_act<3>(g, s)
          : mb <= 4 ? gemm_dec_act<4>(g, s)
-         : mb <= 6 ? gemm_dec_act<6>(g, s)
-                   : gemm_dec_act<8>(g, s);
+                   : gemm_dec_act<6>(g, s);
 }
 
 hipError_t launch_kv_store(const KvArgs& a, hipStream_t s) {

@@ -424,15 +424,48 @@ def test_decode_across_key_chunks(sh):
 
 @pytest.mark.parametrize("d,H,f,batch,n", [
     (256, 2, 2120, 2, 8), (256, 2, 2120, 3, 7), (256, 2, 2120, 5, 6), (256, 2, 2120, 6, 8), (256, 2, 2120, 7, 7),
-    (256, 2, 2120, 8, 8), (2304, 18, 264, 2, 8), (2304, 18, 264, 3, 6), (2304, 18, 264, 8, 8)])
+    (256, 2, 2120, 8, 8), (2304, 18, 264, 2, 8), (2304, 18, 264, 3, 6), (2304, 18, 264, 8, 8),
+    (1280, 10, 2120, 5, 7), (1280, 10, 264, 6, 8)])
 @pytest.mark.parametrize("kind", [0, 1])
 def test_decode_projection_variants(d, H, f, batch, n, kind):
-    """Every row-block variant of the fused projections (16 to 64 rows): the
+    """Every row-block variant of the fused projections (16 to 48 rows): the
     activations kept in registers (K <= 2048, or 4096 up to 16 rows) or
-    streamed (a d_ff of 2120 ends in a chunk of 8), the RMSNorm fused or
-    before them (d = 2304 beyond 16 rows, any d beyond 48)."""
+    streamed (a d_ff of 2120 ends in a chunk of 8); and the split-K ones that
+    take over (d = 2304 beyond 16 rows, 256 beyond 32, any d beyond 48)."""
     sh = inp.Shape(1, d, H, f, 64, batch, "bf16", kind)
     _decode_case(sh, [(n, None)], s_max=64 + n)
+
+
+@pytest.mark.parametrize("d,H,f,batch,n,split", [
+    (256, 2, 520, 4, 8, False), (256, 2, 520, 11, 3, True), (1024, 8, 520, 5, 7, True), (1152, 9, 520, 6, 8, False),
+    (1152, 9, 520, 7, 7, True), (2304, 18, 520, 2, 8, False), (2304, 18, 520, 3, 6, True), (512, 8, 520, 8, 8, True)])
+@pytest.mark.parametrize("kind", [0, 1])
+def test_decode_split_k_projections(d, H, f, batch, n, split, kind):
+    """Which rows take the split-K skinny GEMMs, on both sides of each line of
+    the rule: a stack whose middle layer a draft skips (the reduction of a down
+    projection holds the norm of the next active layer), then all of it."""
+    sh = inp.Shape(3, d, H, f, 64, batch, "bf16", kind)
+    ld.ld_prof_start("ld_gemm_bf16_dec")
+    try:
+        _decode_case(sh, [(n, [1, 0, 1]), (n, None)], s_max=64 + n)
+        launches = ld.ld_prof_result()["launches"]
+    finally:
+        ld.ld_prof_stop()
+    assert launches == (0 if split else 4 * 5)
+
+
+def test_decode_split_k_scratch():
+    """The partial sums stay within the scratch that the query asks for."""
+    sh = inp.Shape(1, 2304, 18, 264, 64, 8, "bf16", 0)
+    cfg, w = _cfg(sh), _weights(sh)[0][0]
+    ws_n = ld.ld_decode_ws_bytes(cfg, 8, 8)
+    ws = _buf(ws_n + 64)
+    ws[ws_n:] = 77
+    x = torch.ones(8, 8, 2304, dtype=torch.bfloat16, device=DEV)
+    kv = torch.zeros(8, 8, 2 * 2304, dtype=torch.bfloat16, device=DEV)
+    ld.ld_stack_decode(cfg, [w], x, [kv], 8, 0, 8, ws[:ws_n])
+    torch.cuda.synchronize()
+    assert bool((ws[ws_n:] == 77).all())
 
 
 def test_decode_more_rows_than_the_skinny_kernel():
