@@ -472,9 +472,9 @@ int attn_forward_part(const ld_config* cfg, const Dims& D, const ld_weights& w, 
   hipError_t e;
   // Evaluation keeps nothing for a backward: every row is processed and X stands
   // until the down projection, so the residual is read from X itself and no
-  // float32 copy is made (where the GEMM's wide residual loads can read it):
-  // norm of 3264 x 2048 13.8 -> 8.2 us, projection with residual 63 -> 59.5.
-  const bool from_x = !mv.count && !scatter && reinterpret_cast<uintptr_t>(xs.p) % 16 == 0;
+  // float32 copy is made: norm of 3264 x 2048 13.8 -> 8.2 us, projection with
+  // residual 63 -> 59.5.
+  const bool from_x = !mv.count && !scatter;
 
   // gather kept rows of X + RMSNorm (attention input)
   {

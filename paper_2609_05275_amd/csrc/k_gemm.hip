@@ -631,6 +631,30 @@ __device__ __forceinline__ bool tile_coords(int pid, int tiles_m, int tiles_n, i
   return true;
 }
 
+// Loads and stores of outputs and residuals, 8 or 16 bytes at the alignment of
+// their elements: gradients may be views into a flat buffer, at any offset.
+// (gfx950 takes such addresses in one instruction; the types say so to the
+// compiler.)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2)));
+
+__device__ __forceinline__ float4 load_f4(const float* p) {
+  const f32x4u v = *reinterpret_cast<const f32x4u*>(p);
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ void store_f4(float* p, float4 v) {
+  *reinterpret_cast<f32x4u*>(p) = f32x4u{v.x, v.y, v.z, v.w};
+}
+__device__ __forceinline__ uint2 load_b4(const bf16* p) {
+  const u32x2u v = *reinterpret_cast<const u32x2u*>(p);
+  return make_uint2(v[0], v[1]);
+}
+__device__ __forceinline__ void store_b4(bf16* p, uint2 v) { *reinterpret_cast<u32x2u*>(p) = u32x2u{v.x, v.y}; }
+__device__ __forceinline__ void store_b8(bf16* p, uint4 v) {
+  *reinterpret_cast<u32x4u*>(p) = u32x4u{v.x, v.y, v.z, v.w};
+}
+
 // Epilogue of one staged 32-row block row: the lane's rows are r0 + RPI it
 // (it < NIT), its 4 columns n..n+3; the staged values (alpha applied) sit at
 // stage[(RPI it + sub) * Pitch + c], sub the lane's row of each RPI.
@@ -687,7 +711,7 @@ __device__ __forceinline__ void epilogue_rows_full(const GemmArgs& g, float* par
 #pragma unroll
       for (int it = 0; it < NR; ++it) {
         const int64_t rrow = g.r_mapped ? orow[it] : r0 + RPI * (NR * h + it);
-        rv[it] = *reinterpret_cast<const float4*>(R + rrow * g.ldr + n);
+        rv[it] = load_f4(R + rrow * g.ldr + n);
       }
 #pragma unroll
       for (int it = 0; it < NR; ++it) {
@@ -702,7 +726,7 @@ __device__ __forceinline__ void epilogue_rows_full(const GemmArgs& g, float* par
 #pragma unroll
       for (int it = 0; it < NR; ++it) {
         const int64_t rrow = g.r_mapped ? orow[it] : r0 + RPI * (NR * h + it);
-        rv[it] = *reinterpret_cast<const uint2*>(R + rrow * g.ldr + n);
+        rv[it] = load_b4(R + rrow * g.ldr + n);
       }
 #pragma unroll
       for (int it = 0; it < NR; ++it) {
@@ -716,14 +740,13 @@ __device__ __forceinline__ void epilogue_rows_full(const GemmArgs& g, float* par
     if (g.c_f32) {
 #pragma unroll
       for (int it = 0; it < NR; ++it)
-        *reinterpret_cast<float4*>(static_cast<float*>(g.C) + static_cast<int64_t>(orow[it]) * g.ldc + n) = v[it];
+        store_f4(static_cast<float*>(g.C) + static_cast<int64_t>(orow[it]) * g.ldc + n, v[it]);
     } else {
 #pragma unroll
       for (int it = 0; it < NR; ++it) {
         __attribute__((aligned(8))) bf16 o[4] = {static_cast<bf16>(v[it].x), static_cast<bf16>(v[it].y),
                                                  static_cast<bf16>(v[it].z), static_cast<bf16>(v[it].w)};
-        *reinterpret_cast<uint2*>(static_cast<bf16*>(g.C) + static_cast<int64_t>(orow[it]) * g.ldc + n) =
-            *reinterpret_cast<const uint2*>(o);
+        store_b4(static_cast<bf16*>(g.C) + static_cast<int64_t>(orow[it]) * g.ldc + n, *reinterpret_cast<const uint2*>(o));
       }
     }
   }
@@ -747,21 +770,21 @@ __device__ __forceinline__ void epilogue_rows_edge(const GemmArgs& g, float* par
     if (g.R) {
       const int64_t rrow = g.r_mapped ? orow : m;
       if (g.r_f32) {
-        const float4 r = *reinterpret_cast<const float4*>(static_cast<const float*>(g.R) + rrow * g.ldr + n);
+        const float4 r = load_f4(static_cast<const float*>(g.R) + rrow * g.ldr + n);
         v.x += r.x; v.y += r.y; v.z += r.z; v.w += r.w;
       } else {
-        const uint2 r = *reinterpret_cast<const uint2*>(static_cast<const bf16*>(g.R) + rrow * g.ldr + n);
+        const uint2 r = load_b4(static_cast<const bf16*>(g.R) + rrow * g.ldr + n);
         const bf16* rb = reinterpret_cast<const bf16*>(&r);
         v.x += static_cast<float>(rb[0]); v.y += static_cast<float>(rb[1]);
         v.z += static_cast<float>(rb[2]); v.w += static_cast<float>(rb[3]);
       }
     }
     if (g.c_f32) {
-      *reinterpret_cast<float4*>(static_cast<float*>(g.C) + orow * g.ldc + n) = v;
+      store_f4(static_cast<float*>(g.C) + orow * g.ldc + n, v);
     } else {
       __attribute__((aligned(8))) bf16 o[4] = {static_cast<bf16>(v.x), static_cast<bf16>(v.y),
                                                static_cast<bf16>(v.z), static_cast<bf16>(v.w)};
-      *reinterpret_cast<uint2*>(static_cast<bf16*>(g.C) + orow * g.ldc + n) = *reinterpret_cast<const uint2*>(o);
+      store_b4(static_cast<bf16*>(g.C) + orow * g.ldc + n, *reinterpret_cast<const uint2*>(o));
     }
   }
 }
@@ -910,7 +933,7 @@ __device__ __forceinline__ void epilogue_plain_edge_bf16(const GemmArgs& g, cons
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         const floatx4& a = ii ? a1[j] : a0[j];
-        *reinterpret_cast<uint2*>(C + j * 16) = pack4_bf16(alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]);
+        store_b4(C + j * 16, pack4_bf16(alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]));
       }
     }
   }
@@ -1194,7 +1217,7 @@ __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int
         bf16* C = static_cast<bf16*>(g.C);
 #pragma unroll
         for (int k = 0; k < LU / 2; ++k)
-          *reinterpret_cast<uint4*>(C + static_cast<int64_t>(mb + 64 / LU * k + rr) * g.ldc + n0 + wn * WC + cc) = v[k];
+          store_b8(C + static_cast<int64_t>(mb + 64 / LU * k + rr) * g.ldc + n0 + wn * WC + cc, v[k]);
         if constexpr (EPI == kEpiKv) {
           // the key and value columns once more, into the cache; S % 32 == 0,
           // so the block row lies in one sequence
@@ -1347,7 +1370,7 @@ __global__ __launch_bounds__(256) void ld_splitk_reduce(const float* part, int s
       if (k < splits) {
         sum.x += t[k].x; sum.y += t[k].y; sum.z += t[k].z; sum.w += t[k].w;
       }
-    reinterpret_cast<float4*>(C)[i4] = sum;
+    store_f4(C + 4 * i4, sum);
   }
 }
 
@@ -1407,11 +1430,11 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
   const bool splittable = allow_split && g.c_f32 && !g.R && !g.out_map.idx && g.ldc == g.N && max_k >= 16 * kPlanK;
   // The big kernel takes every size (at 64 rows of 2048 columns and K = 2048,
   // a few tiles, the 128x128 one takes 33 us and it 23; NN 60 and 41): the
-  // 128x128 kernel is for what its loads and stores of 8 and 16 bytes do not.
-  auto aligned = [](const void* q, int bytes) { return reinterpret_cast<uintptr_t>(q) % bytes == 0; };
-  p.big = g.N % 4 == 0 && g.ldc % 4 == 0 && (!g.R || g.ldr % 4 == 0) && aligned(g.A, 16) && aligned(g.B, 16) &&
-          aligned(g.C, g.c_f32 ? 16 : 8) && aligned(g.R, g.r_f32 || g.c_f32 ? 16 : 8) && a_span < kBigMaxSpan &&
-          b_span < kBigMaxSpan;
+  // 128x128 kernel is for operands its 16-byte loads into LDS do not take and
+  // widths its stores of 4 columns do not.
+  auto aligned = [](const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; };
+  p.big = g.N % 4 == 0 && g.ldc % 4 == 0 && (!g.R || g.ldr % 4 == 0) && aligned(g.A) && aligned(g.B) &&
+          a_span < kBigMaxSpan && b_span < kBigMaxSpan;
   if (p.big) {
     if (splittable) {
       double best = 0;

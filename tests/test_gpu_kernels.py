@@ -239,12 +239,14 @@ def test_gemm_bf16_big_k_steps(layout, K):
 @pytest.mark.parametrize("layout", [(1, 1), (1, 0), (0, 0), (0, 1)])
 @pytest.mark.parametrize("M,N,K", [(1, 4, 8), (8, 264, 64), (64, 512, 136), (136, 256, 328), (264, 520, 192),
                                    (3264, 264, 72)])
-@pytest.mark.parametrize("off,pad", [(0, 0), (1, 0), (0, 1)], ids=["aligned", "offset", "odd_ldc"])
+@pytest.mark.parametrize("off,pad", [(0, 0), (1, 0), (4, 0), (0, 4), (0, 1)],
+                         ids=["aligned", "offset2", "offset8", "ldc4", "odd_ldc"])
 def test_gemm_bf16_few_tiles(layout, M, N, K, off, pad):
     """One to a few tiles (128-row ones among them), rows and columns short of
-    and past a tile edge; with C off 8 bytes' alignment or an odd leading
-    dimension the 128x128 kernel.  bf16 output and residual: one rounding to 8
-    significant bits (2^-8) of sums of K exact products."""
+    and past a tile edge; C 2 or 8 bytes off a 16-byte boundary, or with rows 8
+    bytes off one (block rows are stored 16 bytes at a time); with an odd
+    leading dimension the 128x128 kernel.  bf16 output and residual: one rounding
+    to 8 significant bits (2^-8) of sums of K exact products."""
     ak, bk = layout
     if (not ak and M % 8) or (not bk and N % 8):
         pytest.skip("mn-contiguous operands come in eights")

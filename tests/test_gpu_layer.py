@@ -93,6 +93,46 @@ def test_layer_fwd_bwd(sh, forced):
     _check_grads(dw, grads, t, forced)
 
 
+@pytest.mark.parametrize("sh,kernel", [(MID_BF16, "ld_gemm_bf16_tn_nn_glu_256"), (MID_P, "ld_gemm_bf16_tn_nn_relu2_256")],
+                         ids=["mid_bf16", "paper_mid_bf16"])
+@pytest.mark.parametrize("off", [1, 2, 3])
+def test_layer_bwd_gradient_views(sh, kernel, off):
+    """Weight gradients that are views into one flat float32 buffer, off any
+    16-byte boundary: the same launches (the fused activation backward among
+    them) and the same bits as with tensors of their own."""
+    cfg, wd = _cfg(sh), layer_weights_dev(sh, 0)[0]
+    ctx, ws = _buf(ld.ld_layer_ctx_bytes(cfg)), _buf(ld.ld_layer_ws_bytes(cfg))
+    xd = inp.hidden(sh).to(DEV)
+    ld.ld_layer_fwd(cfg, wd, 0, 0.0, 0, 0, xd, ctx, ws)
+    shapes = inp.weight_shapes(sh)
+    runs = []
+    for flat in (False, True):
+        dw, at = zero_grads(sh), off
+        if flat:
+            buf = torch.full((sum(v.numel() + 8 for v in dw.values()) + off,), 7.0, device=DEV)
+            for k, v in dw.items():
+                dw[k] = buf[at:at + v.numel()].view(shapes[k])
+                at += v.numel() + 8
+        gd = inp.upstream_grad(sh).to(DEV)
+        ld.ld_prof_start(kernel)
+        try:
+            ld.ld_layer_bwd(cfg, wd, ctx, gd, dw, ws)
+            launches = ld.ld_prof_result()["launches"]
+        finally:
+            ld.ld_prof_stop()
+        runs.append((launches, gd.cpu(), {k: v.cpu().clone() for k, v in dw.items()}))
+    assert runs[0][0] == runs[1][0] == 1
+    assert torch.equal(runs[0][1], runs[1][1])
+    for k in shapes:
+        assert torch.equal(runs[0][2][k], runs[1][2][k]), k
+    pads = buf.clone()
+    at = off
+    for v in dw.values():
+        pads[at:at + v.numel()] = 7.0
+        at += v.numel() + 8
+    assert bool((pads == 7.0).all())
+
+
 @pytest.mark.parametrize("sh", [inp.SHAPES["tiny"], SMALL_BF16, TINY_P, SMALL_P],
                          ids=["tiny_f32", "small_bf16", "paper_tiny_f32", "paper_small_bf16"])
 @pytest.mark.parametrize("p_max", [0.0, 0.2, 0.6, 1.0])
