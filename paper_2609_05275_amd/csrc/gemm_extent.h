@@ -9,7 +9,7 @@ namespace ld {
 
 // k-contiguous operand X[r * ld + k], rows r0..R-1: whole rows (k past the end
 // of the last one is cut off by the loads' own test).
-constexpr int64_t kc_extent(int64_t R, int64_t r0, int64_t ld) { return R > r0 ? (R - r0) * ld * 2 : 0; }
+constexpr int64_t kc_extent(int64_t R, int64_t r0, int64_t ld) { return (R - r0) * ld * 2; }
 
 // mn-contiguous operand X[k * ld + r], K k rows of R elements each: up to the
 // last row's last element.  A tile fetches 256 elements of every k row; with
