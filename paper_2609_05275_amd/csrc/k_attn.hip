@@ -20,8 +20,8 @@
 //   dK/dV kernel per (128-key tile, head, sequence) walks the query blocks at
 //   and after the diagonal recomputing P from the saved log-sum-exp.  Heavy
 //   causal tiles are scheduled first.
-// fp32 path: SIMT kernels, 16 lanes per query (or key) row, used by the fp32
-// configuration only.
+// fp32 path: SIMT kernels, 16 lanes per query (or key) row, or one thread per row
+// in a backward of many rows, used by the fp32 configuration only.
 #include <mutex>
 #include <type_traits>
 
@@ -1194,6 +1194,130 @@ __global__ __launch_bounds__(256) void ld_attn_bwd_dkdv_f32(AttnArgs a) {
   }
 }
 
+// The backward kernels with one thread per row, its whole head in registers:
+// every LDS read serves 64 rows, so where the rows of all sequences and heads
+// fill the chip several times over they take less than the kernels above (see
+// f32_bwd_rows); below that each thread's serial chain is what counts.
+
+template <int DH>
+__global__ __launch_bounds__(64) void ld_attn_bwd_dq_f32_row(AttnArgs a) {
+  __shared__ float Ks[FT][DH], Vs[FT][DH];
+  const int S = a.S, H = a.H;
+  const int head = blockIdx.y, seq = blockIdx.z;
+  const float al = a.alibi ? alibi_slope(head, H) : 0.f;  // ALiBi slope (natural units)
+  if (seq >= seq_count(a)) return;
+  const int q0 = blockIdx.x * FT, q = q0 + threadIdx.x, qc = min(q, S - 1);  // rows past S repeat the last
+  const int64_t ldq = 3ll * H * DH, ldo = static_cast<int64_t>(H) * DH;
+  const float* base = static_cast<const float*>(a.qkv) + static_cast<int64_t>(seq) * S * ldq + head * DH;
+  const int64_t orow = (static_cast<int64_t>(seq) * S + qc) * ldo + head * DH;
+  const float *go = static_cast<const float*>(a.go) + orow, *op = static_cast<const float*>(a.o) + orow;
+  float qv[DH], dov[DH], dq[DH], dl = 0.f;
+  for (int i = 0; i < DH; ++i) {
+    qv[i] = base[qc * ldq + i];
+    dov[i] = go[i];
+    dl = __builtin_fmaf(go[i], op[i], dl);
+    dq[i] = 0.f;
+  }
+  dl = -dl;
+  const int64_t srow = (static_cast<int64_t>(seq) * H + head) * S + qc;
+  const float lse = a.lse[srow];
+  if (q < S) a.delta[srow] = dl;
+  const int kv_end = min(S, q0 + FT);
+  for (int k0 = 0; k0 < kv_end; k0 += FT) {
+    for (int e = threadIdx.x; e < FT * DH; e += FT) {
+      const int r = e / DH, c = e % DH;
+      const int64_t row = min(k0 + r, S - 1);
+      Ks[r][c] = base[row * ldq + H * DH + c];
+      Vs[r][c] = base[row * ldq + 2 * H * DH + c];
+    }
+    __syncthreads();
+    for (int j = 0; j < FT; ++j) {
+      const int key = k0 + j;
+      if (key > qc) break;
+      float s = 0.f, dp = 0.f;
+      for (int i = 0; i < DH; ++i) {
+        s = __builtin_fmaf(qv[i], Ks[j][i], s);
+        dp = __builtin_fmaf(dov[i], Vs[j][i], dp);
+      }
+      const float p = expf(s * a.scale - al * static_cast<float>(qc - key) - lse);
+      const float ds = p * (dp + dl);
+      for (int i = 0; i < DH; ++i) dq[i] = __builtin_fmaf(ds, Ks[j][i], dq[i]);
+    }
+    __syncthreads();
+  }
+  if (q < S) {
+    float* G = static_cast<float*>(a.out) + (static_cast<int64_t>(seq) * S + q) * ldq + head * DH;
+    for (int i = 0; i < DH; ++i) G[i] = dq[i] * a.scale;
+  }
+}
+
+template <int DH>
+__global__ __launch_bounds__(64) void ld_attn_bwd_dkdv_f32_row(AttnArgs a) {
+  __shared__ float Qs[FT][DH], Os[FT][DH], ls[FT], dls[FT];
+  const int S = a.S, H = a.H;
+  const int head = blockIdx.y, seq = blockIdx.z;
+  const float al = a.alibi ? alibi_slope(head, H) : 0.f;  // ALiBi slope (natural units)
+  if (seq >= seq_count(a)) return;
+  const int k0 = blockIdx.x * FT, key = k0 + threadIdx.x, kc = min(key, S - 1);  // rows past S repeat the last
+  const int64_t ldq = 3ll * H * DH, ldo = static_cast<int64_t>(H) * DH;
+  const float* base = static_cast<const float*>(a.qkv) + static_cast<int64_t>(seq) * S * ldq + head * DH;
+  const float* go = static_cast<const float*>(a.go) + static_cast<int64_t>(seq) * S * ldo + head * DH;
+  const float* lse = a.lse + (static_cast<int64_t>(seq) * H + head) * S;
+  const float* del = a.delta + (static_cast<int64_t>(seq) * H + head) * S;
+  float kv[DH], vv[DH], dk[DH], dv[DH];
+  for (int i = 0; i < DH; ++i) {
+    kv[i] = base[kc * ldq + H * DH + i];
+    vv[i] = base[kc * ldq + 2 * H * DH + i];
+    dk[i] = dv[i] = 0.f;
+  }
+  for (int qb = k0; qb < S; qb += FT) {
+    for (int e = threadIdx.x; e < FT * DH; e += FT) {
+      const int r = e / DH, c = e % DH;
+      const int64_t row = min(qb + r, S - 1);
+      Qs[r][c] = base[row * ldq + c];
+      Os[r][c] = go[row * ldo + c];
+    }
+    ls[threadIdx.x] = lse[min(qb + static_cast<int>(threadIdx.x), S - 1)];
+    dls[threadIdx.x] = del[min(qb + static_cast<int>(threadIdx.x), S - 1)];
+    __syncthreads();
+    const int n = min(FT, S - qb);
+    for (int j = 0; j < n; ++j) {
+      const int q = qb + j;
+      if (q < key) continue;
+      float s = 0.f, dp = 0.f;
+      for (int i = 0; i < DH; ++i) {
+        s = __builtin_fmaf(Qs[j][i], kv[i], s);
+        dp = __builtin_fmaf(Os[j][i], vv[i], dp);
+      }
+      const float p = expf(s * a.scale - al * static_cast<float>(q - key) - ls[j]);
+      const float ds = p * (dp + dls[j]);
+      for (int i = 0; i < DH; ++i) {
+        dv[i] = __builtin_fmaf(p, Os[j][i], dv[i]);
+        dk[i] = __builtin_fmaf(ds, Qs[j][i], dk[i]);
+      }
+    }
+    __syncthreads();
+  }
+  if (key < S) {
+    float* G = static_cast<float*>(a.out) + (static_cast<int64_t>(seq) * S + key) * ldq + head * DH;
+    for (int i = 0; i < DH; ++i) {
+      G[H * DH + i] = dk[i] * a.scale;
+      G[2 * H * DH + i] = dv[i];
+    }
+  }
+}
+
+// Whether a backward kernel runs with one thread per row: when that makes enough
+// wavefronts of 64 rows.  us with 16 lanes per row -> one thread: dK/dV of heads of
+// 16, 2048 wavefronts (512 heads of 256 rows) 178 -> 156, 4096 (512 of 512) 675 -> 370;
+// of heads of 32 295 -> 262 and 1134 -> 847; dQ of heads of 16 105 -> 116 and 389 -> 285,
+// of 32 176 -> 219 and 671 -> 677; both kernels of heads of 64 (512 of 512) 3789 -> 6423.
+template <int DH>
+bool f32_bwd_rows(const AttnArgs& a, int part) {
+  const int64_t waves = static_cast<int64_t>(a.n_seq) * a.H * ((a.S + FT - 1) / FT);
+  return part == 1 ? waves >= 2048 : DH == 16 && waves >= 4096;
+}
+
 template <int DH>
 hipError_t fwd_dh(int dtype, const AttnArgs& a, hipStream_t s) {
   if constexpr (DH >= 64) {
@@ -1241,6 +1365,17 @@ hipError_t bwd_dh(int dtype, int part, const AttnArgs& a, hipStream_t s) {
   }
   if constexpr (DH <= 64) {
     const dim3 grid((a.S + FR - 1) / FR, a.H, a.n_seq);
+    if constexpr (DH <= 32) {
+      if (f32_bwd_rows<DH>(a, part)) {
+        const dim3 rgrid((a.S + FT - 1) / FT, a.H, a.n_seq);
+        if (part == 1) {
+          hipLaunchKernelGGL(ld_attn_bwd_dkdv_f32_row<DH>, rgrid, dim3(FT), 0, s, a);
+        } else if constexpr (DH == 16) {
+          hipLaunchKernelGGL(ld_attn_bwd_dq_f32_row<DH>, rgrid, dim3(FT), 0, s, a);
+        }
+        return hipGetLastError();
+      }
+    }
     if (part == 0)
       hipLaunchKernelGGL(ld_attn_bwd_dq_f32<DH>, grid, dim3(256), 0, s, a);
     else

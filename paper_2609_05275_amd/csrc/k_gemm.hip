@@ -1680,8 +1680,13 @@ hipError_t launch_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& 
   const bool vec = reinterpret_cast<uintptr_t>(g.A) % 16 == 0 && reinterpret_cast<uintptr_t>(g.B) % 16 == 0 &&
                    g.lda % 4 == 0 && g.ldb % 4 == 0 && ((!a_kcontig && !b_kcontig) || g.K % 4 == 0) &&
                    (a_kcontig || g.M % 4 == 0) && (b_kcontig || g.N % 4 == 0);
-  if (vec) {
-    const int64_t t64 = ((max_m + 63) / 64) * ((g.N + 63) / 64);
+  // At K <= 16 half of their k tile is padding and there is no next one to load
+  // ahead: with tiles for every CU the plain kernel takes less (16384 x 2048 x 16
+  // 66 -> 53 us; 16384 x 64 x 16, B not k-contiguous, 13.4 -> 9.2; both operands
+  // mn-contiguous, where its loads are the slower ones, from 1024 tiles up)
+  const int64_t t64 = ((max_m + 63) / 64) * ((g.N + 63) / 64);
+  const bool shallow = g.K <= FK && !(g.dev_count && g.count_dim) && t64 >= (a_kcontig || b_kcontig ? 256 : 1024);
+  if (vec && !shallow) {
     // 64 x 64 tiles do twice the arithmetic per LDS read; below a tile per CU
     // the latency of a tile counts, and 32 x 32 ones spread it over more CUs
     return t64 >= 256 ? launch_f32_vec<64>(a_kcontig, b_kcontig, g, max_m, s)

@@ -426,6 +426,40 @@ def test_attention_f32_masked_infinities(S, dh):
 
 
 @pytest.mark.parametrize("alibi", [0, 1])
+@pytest.mark.parametrize("n,S,H,dh", [(64, 17, 32, 16), (128, 17, 32, 16), (64, 65, 16, 32), (86, 130, 16, 16)])
+def test_attention_f32_many_rows(n, S, H, dh, alibi):
+    """float32 backward with rows enough for one thread each (2048 wavefronts
+    of 64 rows for dK/dV, 4096 for dQ): against single sequences, which take 16
+    lanes per row, and the float64 reference; an infinite last key and value
+    leave dQ of the earlier rows as it is."""
+    d = H * dh
+    g = torch.Generator().manual_seed(S + n)
+    qkv, go = torch.randn(n * S, 3 * d, generator=g), torch.randn(n * S, d, generator=g)
+
+    def run(q, gout, m):
+        qd, god = q.to(DEV), gout.to(DEV)
+        o, gq = torch.empty(m * S, d, device=DEV), torch.empty(m * S, 3 * d, device=DEV)
+        lse = torch.empty(m, H, S, device=DEV)
+        ws = torch.empty(ld.ld_attn_bwd_ws_bytes(m, S, H), dtype=torch.uint8, device=DEV)
+        ld.ld_attn_fwd(m, S, H, dh, qd, o, lse, alibi=alibi)
+        ld.ld_attn_bwd(m, S, H, dh, qd, o, lse, god, gq, ws, alibi=alibi)
+        torch.cuda.synchronize()
+        return gq.cpu()
+    full = run(qkv, go, n)
+    for b in (0, n // 2, n - 1):
+        t = slice(b * S, (b + 1) * S)
+        assert rel(f64(full[t]), f64(run(qkv[t], go[t], 1))) < 1e-5
+    last = slice((n - 1) * S, n * S)
+    q64, _, probs = _attn_ref(qkv[last], 1, S, H, dh, alibi)
+    want = block.causal_attention_bwd(q64[0][:, :d], q64[0][:, d:2 * d], q64[0][:, 2 * d:], probs[0], f64(go[last]), H)
+    assert rel(f64(full[last]), np.concatenate(want, 1)) < TOL_F32
+    inf = qkv.clone()
+    inf.view(n, S, 3 * d)[:, -1, d:] = float("inf")
+    a, b = (x.view(n, S, 3 * d)[:, :-1, :d] for x in (full, run(inf, go, n)))
+    assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("alibi", [0, 1])
 @pytest.mark.parametrize("dt,n,S,H,dh", [("bf16", 2, 64, 2, 128), ("bf16", 2, 192, 2, 64), ("bf16", 2, 256, 2, 128),
                                          ("bf16", 1, 1024, 1, 128), ("bf16", 1, 512, 6, 128),
                                          ("f32", 3, 32, 4, 16), ("f32", 2, 100, 2, 64), ("f32", 2, 1, 2, 16),
