@@ -636,7 +636,7 @@ __device__ __forceinline__ bool tile_coords(int pid, int tiles_m, int tiles_n, i
 // (gfx950 takes such addresses in one instruction; the types say so to the
 // compiler.)
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(2)));
+typedef __bf16 bf16x4u __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2)));
 
 __device__ __forceinline__ float4 load_f4(const float* p) {
@@ -647,10 +647,11 @@ __device__ __forceinline__ void store_f4(float* p, float4 v) {
   *reinterpret_cast<f32x4u*>(p) = f32x4u{v.x, v.y, v.z, v.w};
 }
 __device__ __forceinline__ uint2 load_b4(const bf16* p) {
-  const u32x2u v = *reinterpret_cast<const u32x2u*>(p);
-  return make_uint2(v[0], v[1]);
+  return __builtin_bit_cast(uint2, *reinterpret_cast<const bf16x4u*>(p));
 }
-__device__ __forceinline__ void store_b4(bf16* p, uint2 v) { *reinterpret_cast<u32x2u*>(p) = u32x2u{v.x, v.y}; }
+__device__ __forceinline__ void store_b4(bf16* p, float a, float b, float c, float d) {
+  *reinterpret_cast<bf16x4u*>(p) = bf16x4u{static_cast<bf16>(a), static_cast<bf16>(b), static_cast<bf16>(c), static_cast<bf16>(d)};
+}
 __device__ __forceinline__ void store_b8(bf16* p, uint4 v) {
   *reinterpret_cast<u32x4u*>(p) = u32x4u{v.x, v.y, v.z, v.w};
 }
@@ -743,11 +744,8 @@ __device__ __forceinline__ void epilogue_rows_full(const GemmArgs& g, float* par
         store_f4(static_cast<float*>(g.C) + static_cast<int64_t>(orow[it]) * g.ldc + n, v[it]);
     } else {
 #pragma unroll
-      for (int it = 0; it < NR; ++it) {
-        __attribute__((aligned(8))) bf16 o[4] = {static_cast<bf16>(v[it].x), static_cast<bf16>(v[it].y),
-                                                 static_cast<bf16>(v[it].z), static_cast<bf16>(v[it].w)};
-        store_b4(static_cast<bf16*>(g.C) + static_cast<int64_t>(orow[it]) * g.ldc + n, *reinterpret_cast<const uint2*>(o));
-      }
+      for (int it = 0; it < NR; ++it)
+        store_b4(static_cast<bf16*>(g.C) + static_cast<int64_t>(orow[it]) * g.ldc + n, v[it].x, v[it].y, v[it].z, v[it].w);
     }
   }
 }
@@ -782,9 +780,7 @@ __device__ __forceinline__ void epilogue_rows_edge(const GemmArgs& g, float* par
     if (g.c_f32) {
       store_f4(static_cast<float*>(g.C) + orow * g.ldc + n, v);
     } else {
-      __attribute__((aligned(8))) bf16 o[4] = {static_cast<bf16>(v.x), static_cast<bf16>(v.y),
-                                               static_cast<bf16>(v.z), static_cast<bf16>(v.w)};
-      store_b4(static_cast<bf16*>(g.C) + orow * g.ldc + n, *reinterpret_cast<const uint2*>(o));
+      store_b4(static_cast<bf16*>(g.C) + orow * g.ldc + n, v.x, v.y, v.z, v.w);
     }
   }
 }
@@ -933,7 +929,7 @@ __device__ __forceinline__ void epilogue_plain_edge_bf16(const GemmArgs& g, cons
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         const floatx4& a = ii ? a1[j] : a0[j];
-        store_b4(C + j * 16, pack4_bf16(alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]));
+        store_b4(C + j * 16, alpha * a[0], alpha * a[1], alpha * a[2], alpha * a[3]);
       }
     }
   }
