@@ -350,7 +350,11 @@ GemmArgs gemm_args() {
 int run_gemm(int dtype, int a_k, int b_k, GemmArgs g, int64_t max_m, int64_t host_m,
              int64_t host_k, hipStream_t s, float* part = nullptr, size_t part_bytes = 0,
              int64_t max_k = 0) {
-  const GemmPlan plan = plan_gemm(dtype, a_k, b_k, g, max_m, max_k, part != nullptr, host_m);
+  GemmPlan plan = plan_gemm(dtype, a_k, b_k, g, max_m, max_k, part != nullptr, host_m);
+  if (gemm_prefers_small(plan, a_k, b_k, g, max_m)) {
+    plan.big = 0;
+    plan.name = gemm_kernel_name(dtype, a_k, b_k);
+  }
   if (plan.splits > 1) {
     if (gemm_part_bytes(plan, g.M, g.N) > part_bytes) return fail(LD_E_WORKSPACE, "split-K scratch too small");
     g.part = part;

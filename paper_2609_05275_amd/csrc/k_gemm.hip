@@ -1457,6 +1457,29 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
   return p;
 }
 
+// Where a GEMM on its own takes less on the 128x128 kernel than on the ring one:
+// a few k steps over a ragged edge.  The ring kernel's edge block rows are
+// stored row by row, and their code and its first fills cost about 2 us more than
+// the small kernel's, which a few k steps do not make up.  us on 128x128 and ring:
+//   B or A mn-contiguous, columns no multiple of 128, at most a tile per CU (two of
+//   at most 32 columns): NN 2048 x 264 x 64 10.2 and 12.1, x 128 11.6 and 13.0, x 256
+//   15.4 and 15.7, 8192 x 776 x 128 (448 tiles) 15.9 and 14.0; TN 2048 x 136 x 64 10.3
+//   and 10.9, x 128 12.0 and 11.5; NN 2048 x 32 x 256 12.3 and 15.4, x 512 18.9 and
+//   19.7, 65536 x 32 x 64 9.0 and 12.8.
+//   Both k-contiguous, at most 96 columns, no multiple of a wave's, too many rows
+//   for one round of 128-row ring tiles: 65536 x 32 x 64 8.2 and 12.2, x 64 x 512 20.2
+//   and 21.7, x 96 x 192 15.2 and 15.8, x 96 x 512 22.7 and 22.3; but 66000 x 64 x 64,
+//   on 128-row tiles without an edge, 17.7 and 13.6.
+bool gemm_prefers_small(const GemmPlan& p, int a_kcontig, int b_kcontig, const GemmArgs& g, int64_t max_m) {
+  if (!p.big || p.splits > 1 || g.kv || (g.dev_count && g.count_dim)) return false;
+  if (a_kcontig && b_kcontig)
+    return g.N <= 96 && g.N % (p.bm == 128 ? 64 : 128) != 0 && big_tiles_of(max_m, g.N, 128) > 256 &&
+           g.K <= (g.N <= 64 ? 1024 : 192);
+  const int64_t tiles = ((max_m + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+  const int most_k = g.N <= 32 ? (a_kcontig || b_kcontig ? 384 : 128) : a_kcontig || b_kcontig ? 128 : 64;
+  return g.N % BN != 0 && tiles <= (g.N <= 32 ? 512 : 256) && g.K <= most_k;
+}
+
 // Whole block rows and columns only (an edge is stored on another path), and
 // 16-byte pieces that stay within the key and value columns.
 bool gemm_stores_kv(const GemmPlan& p, const GemmArgs& g) {

@@ -405,6 +405,9 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
 // Rows of the tiles (256 or 128) of a forward projection of m rows (the kept
 // rows where the host knows them) and n columns.
 int plan_rows(int64_t m, int64_t n);
+// Whether a GEMM planned for the ring kernel is better off on the 128x128 one
+// when it is launched on its own.
+bool gemm_prefers_small(const GemmPlan& p, int a_kcontig, int b_kcontig, const GemmArgs& g, int64_t max_m);
 // Whether launch_gemm_plan can store this GEMM's key and value columns too.
 bool gemm_stores_kv(const GemmPlan& p, const GemmArgs& g);
 size_t gemm_part_bytes(const GemmPlan& p, int64_t M, int64_t N);

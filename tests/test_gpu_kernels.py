@@ -291,6 +291,36 @@ def test_gemm_bf16_column_slices(layout, M, N, K):
     assert np.all(np.abs(f64(C) - ref) <= 1.01 * bound)
 
 
+@pytest.mark.parametrize("layout,M,N,K,small", [
+    ((1, 0), 2048, 264, 128, True), ((1, 0), 2048, 264, 136, False), ((1, 0), 2048, 256, 64, False),
+    ((1, 0), 8192, 504, 64, True), ((1, 0), 8320, 504, 64, False), ((1, 0), 264, 24, 384, True),
+    ((1, 0), 264, 32, 392, False), ((0, 1), 264, 200, 128, True), ((0, 0), 264, 200, 64, True),
+    ((0, 0), 264, 200, 72, False), ((0, 0), 264, 24, 128, True), ((1, 1), 66000, 60, 1024, True),
+    ((1, 1), 66000, 96, 192, True), ((1, 1), 66000, 96, 200, False), ((1, 1), 66000, 100, 8, False),
+    ((1, 1), 66000, 64, 64, False), ((1, 1), 40000, 64, 64, True), ((1, 1), 264, 60, 64, False)])
+def test_gemm_bf16_short_ragged_route(layout, M, N, K, small):
+    """Few k steps over a ragged edge take the 128x128 kernel: both sides of
+    each line of the rule, the route and the result (float32 output: sums of K
+    exact products)."""
+    ak, bk = layout
+    g = torch.Generator().manual_seed(17)
+    A = torch.randn(M, K, generator=g).to(torch.bfloat16).to(DEV)
+    B = torch.randn(N, K, generator=g).to(torch.bfloat16).to(DEV)
+    Ad, Bd = A if ak else A.t().contiguous(), B if bk else B.t().contiguous()
+    C = torch.full((M, N), 7.0, device=DEV)
+    name = "ld_gemm_bf16_" + {(1, 1): "nt", (1, 0): "nn", (0, 0): "tn", (0, 1): "tt"}[layout]
+    ld.ld_prof_start(name)
+    try:
+        ld.ld_gemm(ak, bk, M, N, K, Ad, K if ak else M, Bd, K if bk else N, C, N, c_f32=True)
+        launches = ld.ld_prof_result()["launches"]
+    finally:
+        ld.ld_prof_stop()
+    assert launches == int(small)
+    a, b = A.double(), B.double()
+    bound = K * 2.0 ** -24 * (a.abs() @ b.abs().t().contiguous())
+    assert bool(((C.double() - a @ b.t().contiguous()).abs() <= bound).all())
+
+
 def test_gemm_bf16_far_apart_k_rows():
     """Eight k rows 2^26 elements apart: the k rows past K that a tile of 64
     asks for lie a multiple of 4 GiB on, and must not come back as earlier
