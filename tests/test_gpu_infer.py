@@ -147,6 +147,33 @@ def test_gemm_dec_norm_row_scales(M, N, K, act):
             assert rel(got[m], want[m]) < 1e-2, m
 
 
+@pytest.mark.parametrize("d,H,M", [(256, 2, 9), (256, 2, 16), (1152, 9, 24), (1152, 9, 32), (1152, 9, 40), (1152, 9, 48),
+                                   (2304, 18, 16)])
+@pytest.mark.parametrize("kind", [0, 1])
+def test_decode_norm_row_scales(d, H, M, kind):
+    """RMSNorm fused into the decoding projections at every row-block count:
+    sequences of very different size (one all zeros) at position 0, where the
+    attention gives the key's own value, each row against the evaluation form
+    in float64 within bf16's bound of its own largest."""
+    sh = inp.Shape(1, d, H, 520, 64, M, "bf16", kind)
+    cfg, w = _cfg(sh), _weights(sh)[0]
+    rng = np.random.default_rng(M + d)
+    scale = 10.0 ** np.linspace(-4, 4, M)[:, None, None]
+    scale[M // 2] = 0.0
+    x = _bf16(rng.standard_normal((M, 1, d)) * scale)
+    kv = torch.zeros(M, 1, 2 * d, dtype=torch.bfloat16, device=DEV)
+    xd = x.to(DEV)
+    ld.ld_stack_decode(cfg, [w[0]], xd, [kv], 1, 0, 1, _buf(ld.ld_decode_ws_bytes(cfg, 1, 1)))
+    torch.cuda.synchronize()
+    want, _ = infer.eval_forward(inp.f64(x), [w[1]], [1], H, kind=kind)
+    got = f64(xd)
+    for m in range(M):
+        if m == M // 2:
+            assert not got[m].any()
+        else:
+            assert rel(got[m], want[m]) < tol("bf16"), m
+
+
 def test_gemm_dec_rejects():
     A = torch.zeros(9, 64, dtype=torch.bfloat16, device=DEV)
     W = torch.zeros(32, 64, dtype=torch.bfloat16, device=DEV)
@@ -209,7 +236,8 @@ def test_attn_decode(dh, H, alibi, pos, n):
     (2, 62, 2), (2, 63, 2), (2, 126, 2), (2, 125, 4), (2, 128, 1), (2, 254, 2), (2, 255, 4),  # one chunk and its edges
     (2, 300, 1), (2, 320, 2), (2, 319, 3), (1, 383, 1), (2, 4300, 1), (1, 1023, 4),           # 64- and 128-key chunks
     (2, 180, 1), (2, 190, 2), (2, 190, 3), (43, 1100, 6), (43, 1146, 6),                      # 192-key chunks
-    (30, 640, 4), (30, 1100, 1), (11, 1100, 2)])                                              # larger ones for more rows
+    (30, 640, 4), (30, 1100, 1), (11, 1100, 2),                                               # larger ones for more rows
+    (2, 692, 8), (2, 760, 8), (3, 505, 7), (1, 1017, 7)])                                     # 256-key chunks: 192 do not fit
 def test_attn_decode_chunks(dh, H, B, pos, n):
     """Every chunk size of the decode attention, whole and ragged last chunks,
     against float64 (bf16 output: 2^-8 of the largest element and less; the
