@@ -353,7 +353,7 @@ int run_gemm(int dtype, int a_k, int b_k, GemmArgs g, int64_t max_m, int64_t hos
   GemmPlan plan = plan_gemm(dtype, a_k, b_k, g, max_m, max_k, part != nullptr, host_m);
   if (gemm_prefers_small(plan, a_k, b_k, g, max_m)) {
     plan.big = 0;
-    plan.name = gemm_kernel_name(dtype, a_k, b_k);
+    plan.name = gemm_kernel_name(a_k, b_k);
   }
   if (plan.splits > 1) {
     if (gemm_part_bytes(plan, g.M, g.N) > part_bytes) return fail(LD_E_WORKSPACE, "split-K scratch too small");
@@ -1973,7 +1973,7 @@ int ld_gemm_dec(int32_t M, int32_t N, int32_t K, const void* A, int32_t lda, con
   if (N < 1 || K < 8 || K % 8) return fail(LD_E_SHAPE, "need N >= 1, K >= 8, K %% 8 == 0");
   if (act != kDecActNone && act != kDecActSwiglu && act != kDecActRelu2) return fail(LD_E_INVALID, "unknown act");
   if (act != kDecActNone && R) return fail(LD_E_INVALID, "a residual only without activation");
-  if (K > (g ? kMaxKNorm : kMaxK)) return fail(LD_E_UNSUPPORTED, "K = %d does not fit the staged rows", K);
+  if (K > (g ? kMaxKNorm : kMaxK)) return fail(LD_E_UNSUPPORTED, "K = %d above %d", K, g ? kMaxKNorm : kMaxK);
   if (lda < K || ldw < K || ldc < N || (R && ldr < N)) return fail(LD_E_SHAPE, "leading dimension too small");
   if (lda % 8 || ldw % 8) return fail(LD_E_SHAPE, "lda, ldw must be multiples of 8");
   if (!A || !W || !C) return fail(LD_E_INVALID, "NULL pointer");

@@ -1,21 +1,27 @@
 // GEMM kernels: C[m, n] = (R ? R[m, n] : 0) + alpha * sum_k A(m, k) B(n, k).
 //
-// bf16: gfx950 MFMA v_mfma_f32_32x32x16_bf16, fp32 accumulation.  Workgroup
-// tile 128x128, K step 64, four waves each owning a 64x64 quarter (2x2 MFMA
-// blocks).  Both operands are staged in LDS as [row][k] with k contiguous so
-// every MFMA fragment is one 16-byte LDS read.  An operand whose k is not
-// contiguous in HBM (input and weight gradients) is transposed on its way into
-// LDS: each thread loads four k-rows of eight consecutive m/n values (16-byte
-// coalesced loads) and writes eight 8-byte [m][k0..k0+3] pieces.  LDS is
-// double buffered and the next tile's global loads are issued before the
-// current tile's MFMAs, one barrier per K step.
+// bf16 (gfx950 MFMA, float32 accumulation), two kinds:
+//   the ring kernels (ld_gemm_bf16_*_256, _128; "big" below): 256 x 256 or 128 x
+//   256 tiles, operands fetched straight into an LDS ring, fused epilogues;
+//   nearly every GEMM.  Described where they start.
+//   the 128x128 kernels (ld_gemm_bf16_nt, _nn, _tn, _tt): for operands or widths
+//   the ring kernels do not take, and short products over a ragged edge
+//   (gemm_prefers_small).  K step 64, four waves each owning a 64x64 quarter (2x2
+//   blocks of v_mfma_f32_32x32x16_bf16).  Both operands are staged in LDS as
+//   [row][k] with k contiguous so every MFMA fragment is one 16-byte LDS read; an
+//   operand whose k is not contiguous in HBM is transposed on its way: each
+//   thread loads four k-rows of eight consecutive m/n values (16-byte coalesced
+//   loads) and writes eight 8-byte [m][k0..k0+3] pieces.  LDS is double buffered
+//   and the next tile's global loads are issued before the current tile's MFMAs,
+//   one barrier per K step.
 //
 // The row count (forward and input-gradient GEMMs) or the reduction length
 // (weight-gradient GEMMs) can be read from a device kept count, so the grid is
 // sized for the whole batch and tiles past the kept rows exit at once.
 //
-// fp32: a plain SIMT kernel (64x64 tiles, 4x4 per thread) used by the fp32
-// configuration only.
+// fp32 (the fp32 configuration only): SIMT kernels, ld_gemm_f32_vec_k with 64x64
+// or 32x32 tiles, 16-byte loads and double-buffered LDS, and ld_gemm_f32_k with
+// 64x64 tiles for unaligned or very short operands (f32_vec).
 #include <algorithm>
 #include <functional>
 #include <initializer_list>
@@ -912,9 +918,6 @@ __device__ __forceinline__ void relu2_bwd_rows(const GemmArgs& g, const float* s
   }
 }
 
-// One workgroup's tile of a GEMM: `pid` in [0, n_tiles) picks the tile
-// (n_tiles covers every row the grid was sized for), `sp` of `splits` the
-// k range; `ring` is the workgroup's LDS.
 // Plain bf16 output of a 32-row block row that crosses M: straight from the
 // accumulators, each row checked (lane: row 16 ii + l16, columns 16 j + q16).
 template <int NJ>
@@ -935,6 +938,9 @@ __device__ __forceinline__ void epilogue_plain_edge_bf16(const GemmArgs& g, cons
   }
 }
 
+// One workgroup's tile of a GEMM: `pid` in [0, n_tiles) picks the tile
+// (n_tiles covers every row the grid was sized for), `sp` of `splits` the
+// k range; `ring` is the workgroup's LDS.
 template <bool AK, bool BKC, int EPI = kEpiPlain, int BM = 256>
 __device__ __forceinline__ void gemm_big_body(const GemmArgs& g, bf16* ring, int pid, int n_tiles, int sp,
                                               int splits) {
@@ -1386,9 +1392,33 @@ void set_attrs() {
 
 }  // namespace
 
+constexpr int kCus = 256;   // compute units the plans are made for
 constexpr int kPlanK = 32;  // unit of k in the launch estimates
 
 static int64_t big_tiles_of(int64_t M, int64_t N, int bm) { return ((M + bm - 1) / bm) * ((N + GB - 1) / GB); }
+
+static int64_t f32_tiles(const GemmArgs& g, int64_t max_m) { return ((max_m + 63) / 64) * ((g.N + 63) / 64); }
+
+// Whether a float32 GEMM takes ld_gemm_f32_vec_k: 16-byte aligned rows whose ends
+// the 4-wide loads meet exactly.  At K <= 16 half of its k tile is padding and
+// there is no next one to load ahead: with tiles for every CU the plain kernel
+// takes less (16384 x 2048 x 16 66 -> 53 us; 16384 x 64 x 16, B not k-contiguous,
+// 13.4 -> 9.2; both operands mn-contiguous, where its loads are the slower ones,
+// from 1024 tiles up).
+static bool f32_vec(int a_kcontig, int b_kcontig, const GemmArgs& g, int64_t max_m) {
+  const bool vec = reinterpret_cast<uintptr_t>(g.A) % 16 == 0 && reinterpret_cast<uintptr_t>(g.B) % 16 == 0 &&
+                   g.lda % 4 == 0 && g.ldb % 4 == 0 && ((!a_kcontig && !b_kcontig) || g.K % 4 == 0) &&
+                   (a_kcontig || g.M % 4 == 0) && (b_kcontig || g.N % 4 == 0);
+  const bool shallow = g.K <= FK && !(g.dev_count && g.count_dim) &&
+                       f32_tiles(g, max_m) >= (a_kcontig || b_kcontig ? kCus : 1024);
+  return vec && !shallow;
+}
+
+// The 128x128 kernel of a layout.
+const char* gemm_kernel_name(int a_kcontig, int b_kcontig) {
+  if (a_kcontig) return b_kcontig ? "ld_gemm_bf16_nt" : "ld_gemm_bf16_nn";
+  return b_kcontig ? "ld_gemm_bf16_tt" : "ld_gemm_bf16_tn";
+}
 
 // A last round of tiles that leaves most of the 256 CUs idle costs as much as a
 // full one; 128-row tiles halve what a round costs, at 0.56-0.6 of a 256-row
@@ -1400,7 +1430,7 @@ static int64_t big_tiles_of(int64_t M, int64_t N, int bm) { return ((M + bm - 1)
 constexpr double kHalfTile = 0.59;
 
 int plan_rows(int64_t m, int64_t n) {
-  auto rounds = [&](int bm) { return static_cast<double>((big_tiles_of(m, n, bm) + 255) / 256); };
+  auto rounds = [&](int bm) { return static_cast<double>((big_tiles_of(m, n, bm) + kCus - 1) / kCus); };
   return kHalfTile * rounds(128) < rounds(256) ? 128 : 256;
 }
 
@@ -1410,7 +1440,7 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
   p.splits = 1;
   p.bm = GB;
   if (dtype != LD_BF16) {
-    p.name = "ld_gemm_f32_k";
+    p.name = f32_vec(a_kcontig, b_kcontig, g, max_m) ? "ld_gemm_f32_vec_k" : "ld_gemm_f32_k";
     return p;
   }
   const int64_t big_tiles = ((max_m + GB - 1) / GB) * ((g.N + GB - 1) / GB);
@@ -1436,7 +1466,7 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
       double best = 0;
       for (int s = 1; s <= kMaxSplits; ++s) {
         const int64_t wg = big_tiles * s;
-        const double eff = static_cast<double>(wg) / (256.0 * ((wg + 255) / 256)) - 0.02 * (s - 1);
+        const double eff = static_cast<double>(wg) / (1.0 * kCus * ((wg + kCus - 1) / kCus)) - 0.02 * (s - 1);
         if (eff > best + 1e-9 && max_k / s >= 8 * kPlanK) {
           best = eff;
           p.splits = s;
@@ -1449,10 +1479,7 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
              : b_kcontig            ? "ld_gemm_bf16_tt_256"
                                     : "ld_gemm_bf16_tn_256";
   } else {
-    p.name = a_kcontig && b_kcontig ? "ld_gemm_bf16_nt"
-             : a_kcontig            ? "ld_gemm_bf16_nn"
-             : b_kcontig            ? "ld_gemm_bf16_tt"
-                                    : "ld_gemm_bf16_tn";
+    p.name = gemm_kernel_name(a_kcontig, b_kcontig);
   }
   return p;
 }
@@ -1473,11 +1500,11 @@ GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, i
 bool gemm_prefers_small(const GemmPlan& p, int a_kcontig, int b_kcontig, const GemmArgs& g, int64_t max_m) {
   if (!p.big || p.splits > 1 || g.kv || (g.dev_count && g.count_dim)) return false;
   if (a_kcontig && b_kcontig)
-    return g.N <= 96 && g.N % (p.bm == 128 ? 64 : 128) != 0 && big_tiles_of(max_m, g.N, 128) > 256 &&
+    return g.N <= 96 && g.N % (p.bm == 128 ? 64 : 128) != 0 && big_tiles_of(max_m, g.N, 128) > kCus &&
            g.K <= (g.N <= 64 ? 1024 : 192);
   const int64_t tiles = ((max_m + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   const int most_k = g.N <= 32 ? (a_kcontig || b_kcontig ? 384 : 128) : a_kcontig || b_kcontig ? 128 : 64;
-  return g.N % BN != 0 && tiles <= (g.N <= 32 ? 512 : 256) && g.K <= most_k;
+  return g.N % BN != 0 && tiles <= (g.N <= 32 ? 2 * kCus : kCus) && g.K <= most_k;
 }
 
 // Whole block rows and columns only (an edge is stored on another path), and
@@ -1489,16 +1516,6 @@ bool gemm_stores_kv(const GemmPlan& p, const GemmArgs& g) {
 
 size_t gemm_part_bytes(const GemmPlan& p, int64_t M, int64_t N) {
   return p.splits > 1 ? 4ull * p.splits * M * N : 0;
-}
-
-const char* gemm_kernel_name(int dtype, int a_kcontig, int b_kcontig) {
-  if (dtype == LD_BF16) {
-    if (a_kcontig && b_kcontig) return "ld_gemm_bf16_nt";
-    if (a_kcontig) return "ld_gemm_bf16_nn";
-    if (b_kcontig) return "ld_gemm_bf16_tt";
-    return "ld_gemm_bf16_tn";
-  }
-  return "ld_gemm_f32_k";
 }
 
 hipError_t launch_gemm_plan(int dtype, int a_kcontig, int b_kcontig, const GemmPlan& p, GemmArgs g,
@@ -1537,12 +1554,12 @@ hipError_t launch_gemm_plan(int dtype, int a_kcontig, int b_kcontig, const GemmP
     hipLaunchKernelGGL(ld_splitk_reduce, dim3(blocks), dim3(256), 0, s, g.part, p.splits, mn, C);
     return hipGetLastError();
   }
-  return launch_gemm(dtype, a_kcontig, b_kcontig, g, max_m, 0, s);
+  return launch_gemm(dtype, a_kcontig, b_kcontig, g, max_m, s);
 }
 
-// Estimated finish time, in k tiles of 32 (~1 us each at these shapes), of
-// classes of workgroups (count, cost each) dealt in launch order to n_cu
-// CUs, one workgroup per CU, each CU taking the next when it frees.
+// Estimated finish time, in k tiles of 32, of classes of workgroups (count, cost
+// each) dealt in launch order to n_cu CUs, one workgroup per CU, each CU taking
+// the next when it frees.
 static double list_schedule(std::initializer_list<std::pair<int64_t, double>> classes, int n_cu) {
   std::priority_queue<double, std::vector<double>, std::greater<double>> cu;
   for (int i = 0; i < n_cu; ++i) cu.push(0.0);
@@ -1559,10 +1576,6 @@ static double list_schedule(std::initializer_list<std::pair<int64_t, double>> cl
 
 PairPlan plan_gemm_pair(int64_t m1, int64_t n1, int64_t k1, int64_t m3, int64_t n3, int64_t m2, int64_t n2,
                         int64_t k2, int max_splits) {
-  int dev = 0, n_cu = 256;
-  if (hipGetDevice(&dev) == hipSuccess)
-    (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-  if (n_cu <= 0) n_cu = 256;
   struct Entry {
     int64_t key[9];
     PairPlan plan;
@@ -1570,9 +1583,11 @@ PairPlan plan_gemm_pair(int64_t m1, int64_t n1, int64_t k1, int64_t m3, int64_t 
   constexpr int kEntries = 64;  // the kept counts of a step give a few dozen shapes
   thread_local Entry cache[kEntries];
   thread_local int next = 0;
-  const int64_t key[9] = {m1, n1, k1, m3, n3, m2, n2, k2, max_splits * 4096ll + n_cu};
+  const int64_t key[9] = {m1, n1, k1, m3, n3, m2, n2, k2, max_splits};
   for (const Entry& e : cache)
     if (std::equal(key, key + 9, e.key)) return e.plan;
+  // Fitted to the four-wave kernel with k tiles of 32 that the ring kernel replaced
+  // (which takes about 0.78 us per 32 k); only their ratios weigh in the choice.
   constexpr double kEpi = 8.0;       // epilogue of one tile, in k-tile times
   constexpr double kLaunch = 4.0;    // a second (reduction) launch
   constexpr double kTileUs = 0.95;   // one k tile of 32 on one CU
@@ -1587,8 +1602,8 @@ PairPlan plan_gemm_pair(int64_t m1, int64_t n1, int64_t k1, int64_t m3, int64_t 
   for (int sp = 1; sp <= (tiles1 > 0 ? max_splits : 1); ++sp) {
     const double c1 = static_cast<double>((nkt1 + sp - 1) / sp) + kEpi;
     for (int order = 0; order < 2; ++order) {
-      double t = order ? list_schedule({{tiles2, c2}, {tiles3, c3}, {tiles1 * sp, c1}}, n_cu)
-                       : list_schedule({{tiles3, c3}, {tiles1 * sp, c1}, {tiles2, c2}}, n_cu);
+      double t = order ? list_schedule({{tiles2, c2}, {tiles3, c3}, {tiles1 * sp, c1}}, kCus)
+                       : list_schedule({{tiles3, c3}, {tiles1 * sp, c1}, {tiles2, c2}}, kCus);
       if (sp > 1)  // partials written and read back at ~5 TB/s, plus a launch
         t += kLaunch + (sp + 1.0) * 4.0 * m1 * n1 / 5e12 / (kTileUs * 1e-6);
       if ((sp == 1 && order == 0) || t < best_t - 1e-9) {
@@ -1677,9 +1692,7 @@ static hipError_t launch_f32_vec(int a_kcontig, int b_kcontig, const GemmArgs& g
   return hipGetLastError();
 }
 
-hipError_t launch_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, int64_t max_m,
-                       int64_t max_k, hipStream_t s) {
-  (void)max_k;
+hipError_t launch_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, int64_t max_m, hipStream_t s) {
   if (max_m <= 0 || g.N <= 0) return hipSuccess;
   if (dtype == LD_BF16) {
     set_attrs();
@@ -1695,21 +1708,11 @@ hipError_t launch_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& 
       hipLaunchKernelGGL(ld_gemm_bf16_tn, grid, block, kGemmLds, s, g);
     return hipGetLastError();
   }
-  // 16-byte aligned rows whose ends the 4-wide loads meet exactly
-  const bool vec = reinterpret_cast<uintptr_t>(g.A) % 16 == 0 && reinterpret_cast<uintptr_t>(g.B) % 16 == 0 &&
-                   g.lda % 4 == 0 && g.ldb % 4 == 0 && ((!a_kcontig && !b_kcontig) || g.K % 4 == 0) &&
-                   (a_kcontig || g.M % 4 == 0) && (b_kcontig || g.N % 4 == 0);
-  // At K <= 16 half of their k tile is padding and there is no next one to load
-  // ahead: with tiles for every CU the plain kernel takes less (16384 x 2048 x 16
-  // 66 -> 53 us; 16384 x 64 x 16, B not k-contiguous, 13.4 -> 9.2; both operands
-  // mn-contiguous, where its loads are the slower ones, from 1024 tiles up)
-  const int64_t t64 = ((max_m + 63) / 64) * ((g.N + 63) / 64);
-  const bool shallow = g.K <= FK && !(g.dev_count && g.count_dim) && t64 >= (a_kcontig || b_kcontig ? 256 : 1024);
-  if (vec && !shallow) {
+  if (f32_vec(a_kcontig, b_kcontig, g, max_m)) {
     // 64 x 64 tiles do twice the arithmetic per LDS read; below a tile per CU
     // the latency of a tile counts, and 32 x 32 ones spread it over more CUs
-    return t64 >= 256 ? launch_f32_vec<64>(a_kcontig, b_kcontig, g, max_m, s)
-                      : launch_f32_vec<32>(a_kcontig, b_kcontig, g, max_m, s);
+    return f32_tiles(g, max_m) >= kCus ? launch_f32_vec<64>(a_kcontig, b_kcontig, g, max_m, s)
+                                       : launch_f32_vec<32>(a_kcontig, b_kcontig, g, max_m, s);
   }
   const int64_t tiles = ((max_m + FT - 1) / FT) * ((g.N + FT - 1) / FT);
   const dim3 grid(static_cast<unsigned>(tiles)), block(256);

@@ -244,16 +244,16 @@ struct GemmArgs {
   //     C receives [u v] rows (ldc = 2 glu_f) and aux the rows of
   //     s = silu(u) v (ld glu_f);
   //   backward (NN part of ld_gemm_bf16_tn_nn_glu_256): N = glu_f; the
-  //     product (gs, rounded to bf16) is not stored: aux holds the [u v] rows
+  //     product (gs, kept in float32) is not stored: aux holds the [u v] rows
   //     (ld 2 glu_f) and C receives [gu gv] rows (ldc = 2 glu_f).
   void* aux;
   int32_t glu_f;
   // Squared-ReLU epilogues (256x256 kernels only) when relu2 is set; aux
   // has leading dimension glu_f (= d_ff):
   //   forward (ld_gemm_bf16_nt_relu2_256): C receives u and aux the rows of
-  //     s = relu(u)^2 of the bf16 u;
+  //     s = relu(u)^2 of the float32 u;
   //   backward (NN part of ld_gemm_bf16_tn_nn_relu2_256): the product (gs,
-  //     rounded to bf16) is not stored: aux holds the u rows and C receives
+  //     kept in float32) is not stored: aux holds the u rows and C receives
   //     gu = gs 2 relu(u).
   // Both forward epilogues leave out [u v] or u when C is null.
   int32_t relu2;
@@ -264,8 +264,8 @@ struct GemmArgs {
   int32_t kv_d, kv_S, kv_s_max;
 };
 
-// Kernel choice for one GEMM: the 256x256 MFMA kernel (optionally split
-// along K) or the 128x128 one; fp32 uses the SIMT kernel.
+// Kernel choice for one GEMM: a ring kernel (optionally split along K) or the
+// 128x128 one; fp32 a SIMT kernel.
 struct GemmPlan {
   const char* name;
   int big;
@@ -395,9 +395,9 @@ hipError_t launch_relu2_fwd(int dtype, const EltArgs& a, hipStream_t s);
 hipError_t launch_relu2_bwd(int dtype, const EltArgs& a, hipStream_t s);
 hipError_t launch_swiglu_fwd(int dtype, const EltArgs& a, hipStream_t s);
 hipError_t launch_swiglu_bwd(int dtype, const EltArgs& a, hipStream_t s);
-hipError_t launch_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, int64_t max_m,
-                       int64_t max_k, hipStream_t s);
-const char* gemm_kernel_name(int dtype, int a_kcontig, int b_kcontig);
+hipError_t launch_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, int64_t max_m, hipStream_t s);
+// Name of the 128x128 kernel of a layout.
+const char* gemm_kernel_name(int a_kcontig, int b_kcontig);
 // allow_split: split-K may be chosen (the caller then provides g.part of
 // gemm_part_bytes bytes).
 GemmPlan plan_gemm(int dtype, int a_kcontig, int b_kcontig, const GemmArgs& g, int64_t max_m,
