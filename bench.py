@@ -66,9 +66,7 @@ SWEEP_P_UNIFORM = (0.25, 0.5, 0.75, 0.9)
 
 
 # Kernel -> source file it is built from (for the traffic record's hash check).
-KERNEL_SOURCES = {
-    "ld_gemm": "paper_2609_05275_amd/csrc/k_gemm.hip+paper_2609_05275_amd/csrc/ld_internal.h",
-    "ld_attn": "paper_2609_05275_amd/csrc/k_attn.hip+paper_2609_05275_amd/csrc/ld_internal.h"}
+KERNEL_SOURCES = {k: profsum.kernel_source(k) for k in ("ld_gemm", "ld_attn")}
 
 
 def traffic_record(kernel, workload):
@@ -439,6 +437,7 @@ def main():
 
     # pick the dominant kernel: one profiled step per candidate (untimed)
     cands = ["ld_gemm_bf16_nt_256", "ld_gemm_bf16_nt_glu_256", "ld_gemm_bf16_nt_relu2_256",
+             "ld_gemm_bf16_nt_128", "ld_gemm_bf16_nt_glu_128", "ld_gemm_bf16_nt_relu2_128",
              "ld_gemm_bf16_tn_nn_256", "ld_gemm_bf16_tn_nn_glu_256", "ld_gemm_bf16_tn_nn_relu2_256",
              "ld_attn_fwd_bf16", "ld_attn_bwd_dkdv_bf16", "ld_attn_bwd_dq_bf16"]
     prof_kernel = args.prof_kernel

@@ -135,7 +135,8 @@ def kernel_source(kernel: str) -> str | None:
     """The sources a kernel is built from ('+'-separated, repository paths)."""
     for prefix, f in KERNEL_FILES.items():
         if kernel.startswith(prefix):
-            return f"paper_2609_05275_amd/csrc/{f}+paper_2609_05275_amd/csrc/ld_internal.h"
+            names = [f] + (["gemm_extent.h"] if f == "k_gemm.hip" else []) + ["ld_internal.h"]
+            return "+".join(f"paper_2609_05275_amd/csrc/{n}" for n in names)
     return None
 
 
