@@ -365,7 +365,8 @@ int ld_gemm_skinny(int32_t M, int32_t N, int32_t K, const void* A, int32_t lda, 
  * evaluation equation; Inference Optimizations section) in one launch,
  *   C[m, n] = act(R[m, n] + alpha * sum_k A'[m, k] W[n, k]),
  * A' = A when g is NULL, else the RMSNorm of A's rows with gain g [K]:
- * A'[m, k] = bf16(A[m, k] * rstd_m * g[k]), rstd_m = 1/sqrt(mean_k A[m, k]^2 + eps).
+ * A'[m, k] = A[m, k] * rstd_m * g[k], rstd_m = 1/sqrt(mean_k A[m, k]^2 + eps),
+ * where the gain's product rounds to bf16 and rstd_m multiplies the sums.
  *   act 0: none (R optional, [M, N] with leading dimension ldr);
  *   act 1: SwiGLU; W holds 2N rows (gate rows 0..N-1, then up rows N..2N-1)
  *          and C = silu(u) v for u, v = bf16(alpha * A' W_gate^T), likewise
