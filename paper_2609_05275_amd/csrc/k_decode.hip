@@ -866,13 +866,40 @@ bool dec_gemm_fuses_norm(int64_t M, int64_t K) {
 // each) for up to 48 rows, of K <= 4096 (8 chunks) for up to 16, beyond which
 // they would spill, one workgroup per CU, each CU taking the same number of
 // tiles; else streamed activations, 16 waves while their registers allow.
+// Up to 8 rows of K <= 1024 and more than four tiles per CU: four workgroups of
+// four waves per CU, the activations of K <= 512 in half the registers.  A tile
+// of few chunks costs its latency and its barrier, about 0.9 us a pair of tiles
+// whatever K is, which a lone workgroup pays in turn (8 rows, W of 32768 x 64:
+// 18.0 -> 10.3 us; 131072 x 64, 512, 1024: 60 -> 19, 61 -> 23, 62 -> 41 us;
+// SwiGLU of 11008 and 131072 x 512: 14.2 -> 8.9, 115 -> 42).  Up to 4 tiles per
+// CU both are at the launch's 9 to 10 us.
+// Streamed, 8 rows without SwiGLU: a fifth chunk in flight where two passes
+// then hold all of K, 8192 < K <= 10240 (9664 at 8 rows: 13.2 -> 11.6 us for up
+// to 512 columns, 71 -> 59 for 11008, 787 -> 657 for 131072).
 // Decoding passes a gain with every activation, ld_gemm_dec (8 rows) either.
 template <int MB, int ACT>
 hipError_t gemm_dec_t(const SkinnyArgs& g, hipStream_t s) {
   constexpr bool kBare = MB == 1 || ACT == kDecActNone;  // without a gain
   const int tiles = (g.N + kDecCols - 1) / kDecCols;
-  const int rounds = (tiles + kDecCus - 1) / kDecCus;
-  const dim3 block(512), grid((tiles + rounds - 1) / rounds);
+  auto grid_of = [&](int wgs) {
+    const int rounds = (tiles + wgs - 1) / wgs;
+    return dim3((tiles + rounds - 1) / rounds);
+  };
+  if constexpr (MB == 1) {
+    if (g.K <= 1024 && tiles > 4 * kDecCus) {
+      const dim3 grid = grid_of(4 * kDecCus), block(256);
+      if (g.K <= 512 && g.g)
+        hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, true, 4, 2>), grid, block, 0, s, g);
+      else if (g.K <= 512)
+        hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, false, 4, 2>), grid, block, 0, s, g);
+      else if (g.g)
+        hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, true, 4, 4>), grid, block, 0, s, g);
+      else
+        hipLaunchKernelGGL((ld_gemm_bf16_dec<MB, ACT, false, 4, 4>), grid, block, 0, s, g);
+      return hipGetLastError();
+    }
+  }
+  const dim3 block(512), grid = grid_of(kDecCus);
   if (dec_gemm_fuses_norm(g.M, g.K)) {
     if (g.K <= 2048) {
       if (g.g)
@@ -892,6 +919,12 @@ hipError_t gemm_dec_t(const SkinnyArgs& g, hipStream_t s) {
   } else if constexpr (kBare) {
     if (g.g) return hipErrorInvalidValue;
     constexpr int NW = MB <= 3 ? 16 : 8, U = MB <= 2 && ACT != kDecActSwiglu ? 4 : 2;
+    if constexpr (MB == 1 && U == 4) {
+      if (g.K > 2 * 64 * NW * U && g.K <= 2 * 64 * NW * (U + 1)) {
+        hipLaunchKernelGGL((ld_gemm_bf16_dec_long<MB, ACT, NW, U + 1>), dim3(tiles), dim3(NW * 64), 0, s, g);
+        return hipGetLastError();
+      }
+    }
     hipLaunchKernelGGL((ld_gemm_bf16_dec_long<MB, ACT, NW, U>), dim3(tiles), dim3(NW * 64), 0, s, g);
   } else {
     return hipErrorInvalidValue;

@@ -118,6 +118,42 @@ def test_gemm_dec(M, N, K, mode):
     assert rel(f64(outs[0]), want) < 1e-2
 
 
+@pytest.mark.parametrize("M", [1, 8])
+@pytest.mark.parametrize("N,K", [(8192, 1024), (8193, 64), (8200, 512), (11008, 520), (8201, 1024), (8200, 1032),
+                                 (16389, 40), (24, 8192), (130, 8200), (24, 9664)])
+@pytest.mark.parametrize("mode", ["resid", "norm_resid", "swiglu", "norm_swiglu", "norm_relu2"])
+def test_gemm_dec_variants(M, N, K, mode):
+    """The decoding projection on both sides of its launch rule's lines: 1024
+    column tiles, k of 512 and 1024 (several workgroups per CU and the
+    activations' registers), k of 8192 (the chunks in flight); ragged last
+    tiles and k, a second round of tiles.  Each output against float64: products
+    rounded twice to bf16 at most before the activation (2^-9 each), 1e-2 of the
+    row's largest."""
+    norm, resid = mode.startswith("norm"), mode.endswith("resid")
+    if norm and K > 4096:
+        norm = False
+    act = ld.DEC_ACT_SWIGLU if "swiglu" in mode else ld.DEC_ACT_RELU2 if "relu2" in mode else ld.DEC_ACT_NONE
+    rng = np.random.default_rng(M * 131 + N * 7 + K + len(mode))
+    A = _rng_bf16(rng, (M, K))
+    W = _rng_bf16(rng, (2 * N if act == ld.DEC_ACT_SWIGLU else N, K), 0.05)
+    G = _bf16(1.0 + 0.2 * rng.standard_normal(K)) if norm else None
+    R = _rng_bf16(rng, (M, N)) if resid else None
+    dev = lambda t: None if t is None else t.to(DEV)
+    C = torch.full((M + 1, N), 3.0, dtype=torch.bfloat16, device=DEV)
+    ld.ld_gemm_dec(dev(A), dev(W), C[:M], g=dev(G), eps=1e-5, alpha=0.75, R=dev(R), act=act)
+    torch.cuda.synchronize()
+    a = block.rmsnorm(f64(A), f64(G), 1e-5)[0] if norm else f64(A)
+    y = 0.75 * (a @ f64(W).T)
+    if act == ld.DEC_ACT_SWIGLU:
+        want = block.silu(y[:, :N]) * y[:, N:]
+    else:
+        want = block.relu2(y) if act else y + (f64(R) if resid else 0.0)
+    got = f64(C)
+    for m in range(M):
+        assert np.abs(got[m] - want[m]).max() < 1e-2 * np.abs(want[m]).max(), m
+    assert (got[M] == 3.0).all()
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 40, 64), (3, 264, 200), (8, 2056, 2048), (7, 520, 4096), (8, 24, 4088)])
 @pytest.mark.parametrize("act", [0, 1])
 def test_gemm_dec_norm_row_scales(M, N, K, act):
